@@ -763,6 +763,7 @@ void efem_destroy(efem_ctx *ctx)
     mlp_release(*ctx);
     sparse_release(*ctx);
     for (void *p : ctx->owned) (void)hipFree(p);
+    if (ctx->uniform) (void)hipHostFree(ctx->uniform);
     delete ctx;
 }
 
@@ -980,7 +981,12 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
     m.lam = nullptr;
     m.mu0 = 1.0;
     m.lam0 = 1.5;
-    if ((rc = dalloc(*ctx, &ctx->flags, 2)) || (rc = dalloc(*ctx, &ctx->partials, m.n_blocks))
+    {
+        const hipError_t e = hipHostMalloc((void **)&ctx->uniform, sizeof(UniformRecord), hipHostMallocDefault);
+        if (e != hipSuccess) return fail(hip_fail(e, "hipHostMalloc"));
+        *ctx->uniform = UniformRecord{};
+    }
+    if ((rc = dalloc(*ctx, &ctx->flags, 1)) || (rc = dalloc(*ctx, &ctx->partials, m.n_blocks))
         || (rc = dalloc(*ctx, &ctx->counter, 1)))
         return fail(rc);
     if (hipMemset(ctx->flags, 0, sizeof(int32_t)) != hipSuccess
@@ -1050,24 +1056,17 @@ int efem_set_material(efem_ctx *ctx, const double *mu, const double *lam)
     }
     DeviceGuard dg(ctx->device);
     // a uniform field is passed to the kernels as two scalars (no per-element loads)
-    int32_t *flag = ctx->flags + 1;
-    const int32_t one = 1;
-    HIP_TRY(hipMemcpyAsync(flag, &one, sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(launch_uniform_check(mu, lam, ctx->n_elems, flag, ctx->stream));
-    int32_t uni = 0;
-    double v0[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(&uni, flag, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(&v0[0], mu, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(&v0[1], lam, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    UniformRecord *rec = ctx->uniform;
+    ctx->uniform_calls = ctx->uniform_calls == INT32_MAX ? 1 : ctx->uniform_calls + 1;
+    HIP_TRY(launch_uniform_check(mu, lam, ctx->n_elems, ctx->uniform_calls, rec, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
-    if (uni) {
+    if (rec->differs != ctx->uniform_calls) {
         ctx->m.mu = ctx->m.lam = nullptr;
-        ctx->m.mu0 = v0[0];
-        ctx->m.lam0 = v0[1];
+        ctx->m.mu0 = rec->a0;
+        ctx->m.lam0 = rec->b0;
         return EFEM_OK;
     }
-    HIP_TRY(launch_permute_elems(*ctx, mu, ctx->mu));
-    HIP_TRY(launch_permute_elems(*ctx, lam, ctx->lam));
+    HIP_TRY(launch_permute_elems(*ctx, mu, lam, ctx->mu, ctx->lam));
     ctx->m.mu = ctx->mu;
     ctx->m.lam = ctx->lam;
     return EFEM_OK;

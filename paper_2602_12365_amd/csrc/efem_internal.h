@@ -153,15 +153,21 @@ hipError_t launch_vjp_material(const Ctx &c, const double *u, const double *w, d
 hipError_t launch_grad_coords(const Ctx &c, const double *u, double *g);
 
 // small utility kernels (kernels_util.hip)
-hipError_t launch_permute_elems(const Ctx &c, const double *src, double *dst);
+// ao, bo = a, b in the internal element order
+hipError_t launch_permute_elems(const Ctx &c, const double *a, const double *b, double *ao, double *bo);
 hipError_t launch_build_nmask(const Ctx &c, const uint8_t *dofmask, uint8_t *nmask);
 // xrec[6 i + c] = X[3 i + c], xrec[6 i + 3 + c] = X[3 i + c] + u[3 i + c]
 hipError_t launch_lin_record(const Ctx &c, const double *u, double *xrec);
 hipError_t launch_cast_f32(const double *src, float *dst, int64_t n, hipStream_t s);
 // staging words of the chunk slots from cnode and the node mask (null = none)
 hipError_t launch_chunk_words(const Ctx &c);
-// flag = 1 if a[i] == a[0] and b[i] == b[0] for all i (flag must hold 1 on entry)
-hipError_t launch_uniform_check(const double *a, const double *b, int64_t n, int32_t *flag,
+// Answer of a uniform check, in pinned host memory: differs == the call's
+// number if some a[i] != a[0] or b[i] != b[0]; a0 = a[0], b0 = b[0].
+struct UniformRecord {
+    double a0, b0;
+    int32_t differs;
+};
+hipError_t launch_uniform_check(const double *a, const double *b, int64_t n, int32_t call, UniformRecord *rec,
                                 hipStream_t s);
 
 // ---- context ---------------------------------------------------------------
@@ -196,6 +202,8 @@ struct Ctx {
     double *mu = nullptr, *lam = nullptr;
     uint8_t *nmask = nullptr;
     int32_t *flags = nullptr;
+    UniformRecord *uniform = nullptr;   // pinned host memory, written by the uniform check
+    int32_t uniform_calls = 0;
     // external nodal forces of the final load step (efem_set_load)
     double *fext = nullptr;
     bool have_load = false;
