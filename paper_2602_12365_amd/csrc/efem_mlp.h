@@ -21,9 +21,8 @@ static_assert(kP == EFEM_MLP_PARAMS, "parameter count");
 
 // Per-context state of the learned preconditioner.
 struct MlpState {
-    int64_t *ptr = nullptr;      // [n_nodes+1] node 1-ring CSR
-    int32_t *idx = nullptr;
-    int32_t *ell = nullptr;      // [max_deg][n_nodes] the same 1-ring, column-major,
+    int64_t *ptr = nullptr;      // [n_nodes+1] node 1-ring offsets (degrees)
+    int32_t *ell = nullptr;      // [max_deg][n_nodes] the 1-ring, column-major,
     int32_t max_deg = 0;         //   padded with n_nodes (a zero record of g4)
     uint16_t *W = nullptr;       // bf16 parameters [kP]
     bool have_weights = false;

@@ -80,8 +80,7 @@ MlpState *mlp_state(Ctx &c, int *rc)
     build_ring(c, ptr, idx);
     const int64_t nn = c.n_nodes;
     int r;
-    if ((r = malloc_into(*M, &M->ptr, ptr.size())) || (r = malloc_into(*M, &M->idx, idx.size()))
-        || (r = malloc_into(*M, &M->W, kP)) || (r = malloc_into(*M, &M->X, (size_t)nn * kInPad))
+    if ((r = malloc_into(*M, &M->ptr, ptr.size())) || (r = malloc_into(*M, &M->W, kP)) || (r = malloc_into(*M, &M->X, (size_t)nn * kInPad))
         || (r = malloc_into(*M, &M->scale, (size_t)nn)) || (r = malloc_into(*M, &M->g4, (size_t)nn + 1))
         || (r = malloc_into(*M, &M->dinv, 3 * (size_t)nn))
         || (r = malloc_into(*M, &M->z, 3 * (size_t)nn)) || (r = malloc_into(*M, &M->zold, 3 * (size_t)nn))
@@ -93,8 +92,8 @@ MlpState *mlp_state(Ctx &c, int *rc)
         *rc = r;
         return nullptr;
     }
-    // the 1-ring again, column-major and padded to the largest degree, so that
-    // the per-iteration feature gather reads its indices coalesced
+    // the 1-ring column-major and padded to the largest degree, so that
+    // the feature gathers read their indices coalesced
     int32_t max_deg = 0;
     for (int64_t i = 0; i < nn; ++i) max_deg = std::max<int32_t>(max_deg, (int32_t)(ptr[(size_t)i + 1] - ptr[(size_t)i]));
     std::vector<int32_t> ell((size_t)max_deg * (size_t)nn, (int32_t)nn);
@@ -110,9 +109,7 @@ MlpState *mlp_state(Ctx &c, int *rc)
         *rc = r ? r : hip_fail(hipGetLastError(), "hipMemcpy");
         return nullptr;
     }
-    if (hipMemcpy(M->ptr, ptr.data(), ptr.size() * sizeof(int64_t), hipMemcpyHostToDevice) != hipSuccess
-        || (!idx.empty()
-            && hipMemcpy(M->idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)) {
+    if (hipMemcpy(M->ptr, ptr.data(), ptr.size() * sizeof(int64_t), hipMemcpyHostToDevice) != hipSuccess) {
         for (void *p : M->owned) (void)hipFree(p);
         delete M;
         *rc = hip_fail(hipGetLastError(), "hipMemcpy");
