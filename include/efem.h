@@ -394,9 +394,9 @@ int efem_mlp_forward_layers(efem_ctx *ctx, int64_t rows, const uint16_t *X, uint
 
 /* Loss sum_rows w |m (g + s MLP_params(X)) - m t|^2 and its gradient with respect
  * to params (DEVICE float32 [EFEM_MLP_PARAMS]) into grad (DEVICE float32
- * [EFEM_MLP_PARAMS], overwritten) and loss (DEVICE float64 [1]); forward and
- * backward on the vector units, the bfloat16 roundings of the forward treated
- * as identity in the backward pass.  Deterministic. */
+ * [EFEM_MLP_PARAMS], overwritten) and loss (DEVICE float64 [1]); FP32
+ * arithmetic throughout, the bfloat16 roundings of the forward treated as
+ * identity in the backward pass.  Deterministic. */
 int efem_mlp_loss_grad(efem_ctx *ctx, int64_t rows, const uint16_t *X, const float *aux,
                        const float *params, float *grad, double *loss);
 

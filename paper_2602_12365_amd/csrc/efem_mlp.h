@@ -39,7 +39,7 @@ struct MlpState {
     double *tt = nullptr;        // scalar
     std::vector<void *> owned;
 };
-constexpr int kGradBlocks = 1024;
+constexpr int kGradBlocks = 512;   // two workgroups per CU resident at once
 constexpr int kEnergyBlocks = 512;
 
 hipError_t mlp_features_static(hipStream_t s, const MlpState &M, int64_t n, const double *diag,

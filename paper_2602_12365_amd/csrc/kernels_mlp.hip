@@ -1,6 +1,6 @@
 // Learned CG preconditioner kernels: node features over the 1-ring, the
 // per-node MLP 12 -> 64 -> 64 -> 3 (softplus) on bf16 matrix cores, and its
-// training (forward + backward on the vector units, Adam).
+// training (forward + backward, Adam).
 //
 // Preconditioner (per node i, N(i) = nodes sharing an element with i):
 //   g_i = D_i^-1 r_i (0 on prescribed DOFs), s_i = 1-ring RMS of g,
@@ -37,7 +37,6 @@ __device__ __forceinline__ float softplus(float x)
     const float e = t - (u - 1.f);
     return fmaxf(x, 0.f) + fmaf(0.6931471805599453f, __builtin_amdgcn_logf(u), e);
 }
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.f / (1.f + __expf(-x)); }
 
 // ------------------------------------------------------------------ features
 
@@ -403,153 +402,426 @@ __global__ void k_rows_aux(int64_t n, const float *__restrict__ b, const float *
     a[11] = 0.f;
 }
 
-// Forward + backward on the vector units for rows of (X, aux); each workgroup
-// loops over chunks of 16 rows and accumulates its share of the parameter
-// gradient in registers, then writes one partial row [kP] and a loss partial.
-// Matches the matrix-core forward: bf16 weights and layer inputs, FP32 sums;
-// the roundings are treated as identity in the backward pass.
-constexpr int kRowsPerChunk = 16;
-constexpr int kGradPerThread = (kP + 255) / 256;
+// ---- gradient of the training loss, on the matrix cores
+//
+// 16 rows per wave step (rows on the N dimension).  The forward runs on the
+// FP32 matrix instruction, which adds its four products one after another, as
+// four FMAs would: with the contraction in ascending order from the bias, the
+// sums are those of the plain FP32 loop bit for bit, so no activation rounds to
+// another bfloat16 than it would there.
+// The backward treats the forward's roundings as identity.  Its four
+// contractions run on bf16 matrix cores at FP32 accuracy: one factor of each
+// (W3, W2, the layer inputs x, h1, h2) is a bfloat16 number to begin with, and
+// the other (the FP32 deltas) is split into three bfloat16 terms hi + mid + lo
+// that together hold its 24 bits, so every product is exact and only the FP32
+// accumulation rounds.
+//   delta chain:       dz2[h][row] = sum_c W3[c][h] do[c][row] * sigmoid(a2),
+//                      dz1[j][row] = sum_h W2[h][j] dz2[h][row] * sigmoid(a1):
+//                      the accumulator layout is again the B-operand layout;
+//   weight gradients:  dW2[h][j] += sum_row dz2[h][row] h1[row][j] and the same
+//                      for W1, W3: the contraction is over rows, so both
+//                      operands go through a per-wave LDS transpose (planes
+//                      [unit][16 rows]).  b1 rides as a feature that is 1.
+// What bounds it: issue and latency at 2 waves per SIMD (the gradient's 112
+// accumulators take the registers of a third): 1,650 VALU instructions, 208
+// matrix instructions (4,800 cycles) and 185 LDS instructions per 16 rows.
+// Weight fragments lie in LDS in lane order.  179,685 rows: 80 us, against 667
+// us for a form on the vector units whose weight reads met 16-way LDS bank
+// conflicts.  The gradient's error against float64 is unchanged.
+typedef uint32_t __attribute__((may_alias)) u32a;
+typedef s4 __attribute__((may_alias)) s4a;
+typedef f4 __attribute__((may_alias)) f4a;
 
-__global__ void __launch_bounds__(256) k_mlp_grad(int64_t rows, const uint16_t *__restrict__ X,
+constexpr int kPlane = kHid * 32 + (kHid / 8) * 16;   // bytes of a [64 units][16 rows] bf16 plane
+// plane row of a unit: 32 bytes, 16 more after every 8 units (bank spread)
+__device__ __forceinline__ int plane_off(int unit) { return unit * 32 + (unit >> 3) * 16; }
+constexpr int kSmallPlane = 16 * 32 + 2 * 16;         // 16 units
+constexpr int kGradWaves = 4;
+constexpr int kFrags = 4 + 16 + 4 + 4 + 16;           // W1, W2, W3, W3^T, W2^T
+constexpr int kFragBytes = kFrags * 512;
+constexpr int kBiasBytes = (2 * kHid + 4) * 4;
+constexpr int kWaveBytes = 5 * kPlane + 2 * kSmallPlane;   // three delta planes, h1, h2, x, do
+constexpr int kGradLds = kFragBytes + kBiasBytes + kGradWaves * kWaveBytes;
+static_assert(2 * kP * 4 <= kFragBytes + kBiasBytes + kGradWaves * kWaveBytes, "two sets of gradient sums share the LDS");
+static_assert(kP * 4 <= kGradWaves * kWaveBytes, "the parameters are staged in the planes' space");
+
+// orders LDS accesses within the wave for the compiler (the LDS itself serves
+// a wave's accesses in order)
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// four consecutive units of this lane's row into a plane: lane pairs (rows
+// 2k, 2k + 1) swap values so that each lane writes two rows of two units at
+// once.  p: the plane row of the first unit, plus 4 (row / 2), plus 32 in odd lanes
+__device__ __forceinline__ void put_rows(unsigned char *p, uint2 own, uint32_t sel)
+{
+    uint2 nb;   // the neighbouring row's (lane ^ 1) values
+    nb.x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own.x, 0xB1, 0xF, 0xF, false);
+    nb.y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own.y, 0xB1, 0xF, 0xF, false);
+    *reinterpret_cast<u32a *>(p) = __builtin_amdgcn_perm(nb.x, own.x, sel);
+    *reinterpret_cast<u32a *>(p + 64) = __builtin_amdgcn_perm(nb.y, own.y, sel);
+}
+// byte selections: even lanes write units 0 and 2 (low halves: own, neighbour),
+// odd lanes units 1 and 3 (high halves: neighbour, own)
+constexpr uint32_t kSelEven = 0x05040100u, kSelOdd = 0x03020706u;
+
+// two bfloat16 values, a in the low half
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, bf2_t));
+}
+__device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ s4 as_s4(uint2 w) { return __builtin_bit_cast(s4, w); }
+
+// x = hi + mid + lo in bfloat16.  An infinite x is hi alone: the median of
+// (NaN, NaN, 0) is 0, and of (r, r, 0) it is r.
+__device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t &mid, uint32_t &lo)
+{
+    hi = pack_bf(x, y);
+    const float dx = x - lo_bf(hi), dy = y - hi_bf(hi);
+    const float rx = __builtin_amdgcn_fmed3f(dx, dx, 0.f), ry = __builtin_amdgcn_fmed3f(dy, dy, 0.f);
+    mid = pack_bf(rx, ry);
+    lo = pack_bf(rx - lo_bf(mid), ry - hi_bf(mid));
+}
+__device__ __forceinline__ void split3(const float x[4], uint2 &hi, uint2 &mid, uint2 &lo)
+{
+    split2(x[0], x[1], hi.x, mid.x, lo.x);
+    split2(x[2], x[3], hi.y, mid.y, lo.y);
+}
+
+// softplus(x) (as softplus()) and its derivative 1 / (1 + e^-x) from the same exponential
+__device__ __forceinline__ float softplus_d(float x, float &dx)
+{
+    const float t = __builtin_amdgcn_exp2f(-fabsf(x) * 1.4426950408889634f);
+    const float u = 1.f + t;
+    const float e = t - (u - 1.f);
+    const float r = __builtin_amdgcn_rcpf(u);
+    dx = x >= 0.f ? r : t * r;
+    return fmaxf(x, 0.f) + fmaf(0.6931471805599453f, __builtin_amdgcn_logf(u), e);
+}
+
+__device__ __forceinline__ f4 mfma16(s4 a, s4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// one value of a plane: unit `u` of row `row`
+typedef uint16_t __attribute__((may_alias)) u16a;
+__device__ __forceinline__ float unit_row(const unsigned char *p, int u, int row)
+{
+    return bf2f(*reinterpret_cast<const u16a *>(p + plane_off(u) + 2 * row));
+}
+
+__global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(int64_t rows, const uint16_t *__restrict__ X,
                                                   const float *__restrict__ aux,
                                                   const float *__restrict__ params,
                                                   float *__restrict__ gpart, double *__restrict__ lpart)
 {
-    __shared__ float Wl[kP];
-    __shared__ float X0[kRowsPerChunk][kIn];
-    __shared__ float A1[kRowsPerChunk][kHid], H1[kRowsPerChunk][kHid];
-    __shared__ float A2[kRowsPerChunk][kHid], H2[kRowsPerChunk][kHid];
-    __shared__ float DZ[kRowsPerChunk][kHid];
-    __shared__ float DO[kRowsPerChunk][4];
-    __shared__ double red[256];
-    const int tid = threadIdx.x;
-    for (int k = tid; k < kP; k += 256) Wl[k] = bfr(params[k]);
-    float gacc[kGradPerThread];
+    __shared__ __align__(16) unsigned char smem[kGradLds];
+    __shared__ double lred[kGradWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, quad = lane >> 4;
+    s4a *F1 = reinterpret_cast<s4a *>(smem), *F2 = F1 + 4 * 64, *F3 = F2 + 16 * 64, *F3T = F3 + 4 * 64,
+        *F2T = F3T + 4 * 64;
+    float *bias = reinterpret_cast<float *>(smem + kFragBytes);   // b1, b2, b3 (padded to 4)
+    unsigned char *mine = smem + kFragBytes + kBiasBytes + wave * kWaveBytes;
+    unsigned char *pd = mine, *ph1 = mine + 3 * kPlane, *ph2 = ph1 + kPlane, *px = ph2 + kPlane, *pdo = px + kSmallPlane;
+    // operand fragments: entry f * 64 + l holds lane l's four values, for the
+    // forward (W1, W2, W3) those of four FP32 steps v (m = l % 16, k = 4 v +
+    // l / 16 of its 16), else one bf16 operand (m = l % 16, k = 4 (l / 16) + v)
+    // (from a copy of the parameters in the planes' space: the gathers then cost
+    // LDS reads instead of memory latencies)
+    float *pl = reinterpret_cast<float *>(smem + kFragBytes + kBiasBytes);
+    for (int k = tid; k < kP; k += 64 * kGradWaves) pl[k] = bfr(params[k]);
+    __syncthreads();
+    for (int i = tid; i < kFrags * 64; i += 64 * kGradWaves) {
+        const int f = i >> 6, c = i & 15, q = (i & 63) >> 4;
+        s4 w;
 #pragma unroll
-    for (int q = 0; q < kGradPerThread; ++q) gacc[q] = 0.f;
+        for (int v = 0; v < 4; ++v) {
+            const int k = 4 * q + v, kf = 4 * v + q;
+            int at;
+            if (f < 4) at = kf < kIn ? kOffW1 + (16 * f + c) * kIn + kf : -1;
+            else if (f < 20) at = kOffW2 + (16 * ((f - 4) & 3) + c) * kHid + 16 * ((f - 4) >> 2) + kf;   // group, tile
+            else if (f < 24) at = c < kOut ? kOffW3 + c * kHid + 16 * (f - 20) + kf : -1;
+            else if (f < 28) at = k < 9 ? kOffW3 + (k % 3) * kHid + 16 * (f - 24) + c : -1;   // k = 3 term + c
+            else at = kOffW2 + (16 * ((f - 28) & 3) + k) * kHid + 16 * ((f - 28) >> 2) + c;   // tile t1, t
+            w[v] = at >= 0 ? (short)f2bf(pl[at]) : (short)0;
+        }
+        F1[i] = w;
+    }
+    if (tid < kHid) {
+        bias[tid] = pl[kOffB1 + tid];
+        bias[kHid + tid] = pl[kOffB2 + tid];
+    }
+    if (tid < 4) bias[2 * kHid + tid] = tid < kOut ? pl[kOffB3 + tid] : 0.f;
+    __syncthreads();
+    // rows 9..15 of the output-delta plane stay 0
+    for (int i = lane; i < kSmallPlane / 4; i += 64) *reinterpret_cast<u32a *>(pdo + 4 * i) = 0u;
+    __syncthreads();
+
+    const uint32_t sel = (lane & 1) ? kSelOdd : kSelEven;
+    // this lane's place in a plane for put_rows (of the units 4 quad + ...) and
+    // for an operand read (unit l % 16 of a tile, rows 4 quad + ...)
+    const int wr = plane_off(4 * quad) + (col >> 1) * 4 + (lane & 1) * 32, rd = plane_off(col) + 8 * quad;
+    constexpr int kTile = 16 * 32 + 2 * 16;   // bytes of a plane's tile of 16 units
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 g2[4][4], g1[4], g3[4];      // dW2 [h tile][j tile], dW1 (and b1), dW3 (three terms)
+    float gb2[4][4], gb3[kOut] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        g1[t] = g3[t] = zero;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g2[t][j] = zero, gb2[t][j] = 0.f;
+    }
     double loss = 0.0;
-    const int rr = tid / 16;     // row of the chunk handled by this thread
-    const int part = tid % 16;   // 4 hidden units each: 4*part .. 4*part+3
-    __syncthreads();
-    for (int64_t c0 = (int64_t)blockIdx.x * kRowsPerChunk; c0 < rows;
-         c0 += (int64_t)gridDim.x * kRowsPerChunk) {
-        const int64_t row = c0 + rr;
-        const bool valid = row < rows;
-        if (part < kIn) X0[rr][part] = valid ? bf2f(X[row * kInPad + part]) : 0.f;
-        __syncthreads();
+    const int64_t nw = (int64_t)gridDim.x * kGradWaves, first = (int64_t)blockIdx.x * kGradWaves + wave;
+    s4 xn = load_x(X, first * 16 + col, rows);
+    for (int64_t r0 = first * 16; r0 < rows; r0 += nw * 16) {
+        const int64_t row = r0 + col;
+        s4 xb = xn;
+        xn = load_x(X, row + nw * 16, rows);
+        // this row's training data, used by the quad that holds the outputs
+        float ax[11];
+        const bool mine_out = quad == 0 && row < rows;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int h = 4 * part + u;
-            float a = Wl[kOffB1 + h];
+        for (int k = 0; k < 11; ++k) ax[k] = mine_out ? aux[row * kAux + k] : 0.f;
+        if (quad == 3) xb[0] = 0x3f80;   // feature 12 = 1: its weight is 0, its gradient that of b1
+        put_rows(px + wr, __builtin_bit_cast(uint2, xb), sel);
+        wave_fence();
+        // forward
+        float s1[4][4], s2[4][4];
+        f4 a[4];
 #pragma unroll
-            for (int k = 0; k < kIn; ++k) a += Wl[kOffW1 + h * kIn + k] * X0[rr][k];
-            A1[rr][h] = a;
-            H1[rr][h] = bfr(softplus(a));
+        for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const f4a *>(bias + 16 * t + 4 * quad);
+#pragma unroll
+        for (int v = 0; v < kIn / 4; ++v) {
+            const float b = unit_row(px, 4 * v + quad, col);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = mfma4(bf2f((uint16_t)F1[t * 64 + lane][v]), b, a[t]);
         }
-        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int h = 4 * part + u;
-            float a = Wl[kOffB2 + h];
-            for (int k = 0; k < kHid; ++k) a += Wl[kOffW2 + h * kHid + k] * H1[rr][k];
-            A2[rr][h] = a;
-            H2[rr][h] = bfr(softplus(a));
+        for (int t = 0; t < 4; ++t) {
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = softplus_d(a[t][v], s1[t][v]);
+            put_rows(ph1 + t * kTile + wr, make_uint2(pack_bf(h[0], h[1]), pack_bf(h[2], h[3])), sel);
         }
-        __syncthreads();
-        if (part < kOut) {
-            float o = Wl[kOffB3 + part];
-            for (int k = 0; k < kHid; ++k) o += Wl[kOffW3 + part * kHid + k] * H2[rr][k];
-            float d = 0.f;
-            if (valid) {
-                const float *a = aux + row * kAux;
-                const float z = a[6 + part] * (a[part] + a[9] * o);
-                const float e = z - a[6 + part] * a[3 + part];
-                loss += (double)a[10] * (double)e * (double)e;
-                d = 2.f * a[10] * a[9] * a[6 + part] * e;
+        wave_fence();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const f4a *>(bias + kHid + 16 * t + 4 * quad);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            s4 w[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) w[t] = F2[(4 * g + t) * 64 + lane];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float b = unit_row(ph1, 16 * g + 4 * v + quad, col);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) a[t] = mfma4(bf2f((uint16_t)w[t][v]), b, a[t]);
             }
-            DO[rr][part] = d;
         }
-        __syncthreads();
-        // dz2 = (W3^T dout) * sigmoid(a2)
-        float dz2[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int h = 4 * part + u;
-            const float dh = Wl[kOffW3 + h] * DO[rr][0] + Wl[kOffW3 + kHid + h] * DO[rr][1]
-                           + Wl[kOffW3 + 2 * kHid + h] * DO[rr][2];
-            dz2[u] = dh * sigmoidf_(A2[rr][h]);
+        for (int t = 0; t < 4; ++t) {
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = softplus_d(a[t][v], s2[t][v]);
+            put_rows(ph2 + t * kTile + wr, make_uint2(pack_bf(h[0], h[1]), pack_bf(h[2], h[3])), sel);
         }
-        __syncthreads();   // A2 is reused below as the dz2 store
+        wave_fence();
+        f4 o = *reinterpret_cast<const f4a *>(bias + 2 * kHid);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) A2[rr][4 * part + u] = dz2[u];
-        __syncthreads();
-        // dz1 = (W2^T dz2) * sigmoid(a1)
+        for (int g = 0; g < 4; ++g) {
+            const s4 w = F3[g * 64 + lane];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = 4 * part + u;
-            float dh = 0.f;
-            for (int h = 0; h < kHid; ++h) dh += Wl[kOffW2 + h * kHid + j] * A2[rr][h];
-            DZ[rr][j] = dh * sigmoidf_(A1[rr][j]);
+            for (int v = 0; v < 4; ++v)
+                o = mfma4(bf2f((uint16_t)w[v]), unit_row(ph2, 16 * g + 4 * v + quad, col), o);
         }
-        __syncthreads();
-        // parameter gradients over the chunk's rows (A2 now holds dz2)
+        // loss and output deltas (quad 0 holds outputs 0..2 of its row)
+        float dout[4] = {0.f, 0.f, 0.f, 0.f};
+        if (mine_out) {
 #pragma unroll
-        for (int q = 0; q < kGradPerThread; ++q) {
-            const int k = tid + 256 * q;
-            if (k >= kP) continue;
-            float g = 0.f;
-            if (k < kOffB1) {
-                const int h = k / kIn, c = k % kIn;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += DZ[r2][h] * X0[r2][c];
-            } else if (k < kOffW2) {
-                const int h = k - kOffB1;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += DZ[r2][h];
-            } else if (k < kOffB2) {
-                const int h = (k - kOffW2) / kHid, j = (k - kOffW2) % kHid;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += A2[r2][h] * H1[r2][j];
-            } else if (k < kOffW3) {
-                const int h = k - kOffB2;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += A2[r2][h];
-            } else if (k < kOffB3) {
-                const int c = (k - kOffW3) / kHid, h = (k - kOffW3) % kHid;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += DO[r2][c] * H2[r2][h];
-            } else {
-                const int c = k - kOffB3;
-                for (int r2 = 0; r2 < kRowsPerChunk; ++r2) g += DO[r2][c];
+            for (int c = 0; c < kOut; ++c) {
+                const float z = ax[6 + c] * (ax[c] + ax[9] * o[c]);
+                const float e = z - ax[6 + c] * ax[3 + c];
+                loss += (double)ax[10] * (double)e * (double)e;
+                dout[c] = 2.f * ax[10] * ax[9] * ax[6 + c] * e;
+                gb3[c] += dout[c];
             }
-            gacc[q] += g;
         }
-        __syncthreads();
-    }
+        uint2 dh, dm, dl;
+        split3(dout, dh, dm, dl);
+        // the three terms of the three outputs in k = 3 term + c order: quad q
+        // gets k = 4 q .. 4 q + 3 of its row
+        uint2 db;
+        {
+            const uint32_t w[5] = {dh.x, dh.y | dm.x << 16, dm.x >> 16 | dm.y << 16, dl.x, dl.y};
+            uint32_t g[5];
 #pragma unroll
-    for (int q = 0; q < kGradPerThread; ++q) {
-        const int k = tid + 256 * q;
-        if (k < kP) gpart[(int64_t)blockIdx.x * kP + k] = gacc[q];
+            for (int k = 0; k < 5; ++k) g[k] = (uint32_t)__shfl((int)w[k], col, 64);
+            db.x = quad == 0 ? g[0] : quad == 1 ? g[2] : quad == 2 ? g[4] : 0u;
+            db.y = quad == 0 ? g[1] : quad == 1 ? g[3] : 0u;
+        }
+        put_rows(pdo + wr, db, sel);
+        // dz2 = (W3^T do) sigmoid(a2), its terms to the planes
+        uint2 dz[3][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const f4 d = mfma16(F3T[t * 64 + lane], as_s4(db), zero);
+            float z[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                z[v] = d[v] * s2[t][v];
+                gb2[t][v] += z[v];
+            }
+            split3(z, dz[0][t], dz[1][t], dz[2][t]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) put_rows(pd + k * kPlane + t * kTile + wr, dz[k][t], sel);
+        }
+        wave_fence();
+        // dW3 += do h2, dW2 += dz2 h1: units on both sides, contraction over the 16 rows
+        const s4 ado = *reinterpret_cast<const s4a *>(pdo + rd);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            g3[t] = mfma16(ado, *reinterpret_cast<const s4a *>(ph2 + t * kTile + rd), g3[t]);
+        }
+        s4 bh1[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) bh1[t] = *reinterpret_cast<const s4a *>(ph1 + t * kTile + rd);
+#pragma unroll
+        for (int t2 = 0; t2 < 4; ++t2)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const s4 ad = *reinterpret_cast<const s4a *>(pd + k * kPlane + t2 * kTile + rd);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) g2[t2][t] = mfma16(ad, bh1[t], g2[t2][t]);
+            }
+        wave_fence();
+        // dz1 = (W2^T dz2) sigmoid(a1), its terms to the planes
+#pragma unroll
+        for (int t1 = 0; t1 < 4; ++t1) {
+            f4 d = zero;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const s4 w = F2T[(4 * t1 + t) * 64 + lane];
+#pragma unroll
+                for (int k = 2; k >= 0; --k) d = mfma16(w, as_s4(dz[k][t]), d);
+            }
+            float z[4];
+            uint2 e[3];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z[v] = d[v] * s1[t1][v];
+            split3(z, e[0], e[1], e[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) put_rows(pd + k * kPlane + t1 * kTile + wr, e[k], sel);
+        }
+        wave_fence();
+        const s4 bx = *reinterpret_cast<const s4a *>(px + rd);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                g1[t] = mfma16(*reinterpret_cast<const s4a *>(pd + k * kPlane + t * kTile + rd), bx,
+                               g1[t]);
+        wave_fence();
     }
-    red[tid] = loss;
+
+    // the wave's sums of the row-wise parts
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gb2[t][v] += __shfl_xor(gb2[t][v], off, 64);
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) gb3[c] += __shfl_xor(gb3[c], off, 64);
+        loss += __shfl_xor(loss, off, 64);
+    }
+    if (lane == 0) lred[wave] = loss;
+    // dW3: the terms of output c lie in rows c, 3 + c, 6 + c (quads 0, 1, 2)
+    float w3[4][kOut];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        float q1[4], q2;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) q1[v] = __shfl(g3[t][v], col + 16, 64);
+        q2 = __shfl(g3[t][0], col + 32, 64);
+        w3[t][0] = g3[t][0] + (g3[t][3] + q1[2]);
+        w3[t][1] = g3[t][1] + (q1[0] + q1[3]);
+        w3[t][2] = g3[t][2] + (q1[1] + q2);
+    }
+    // the four waves' sums in a fixed order, (0 + 1) + (2 + 3), through two sets in LDS
+    float *gs = reinterpret_cast<float *>(smem) + (wave >> 1) * kP;
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int h = 16 * t + 4 * quad + v;
+                if (col <= kIn) f(col < kIn ? kOffW1 + h * kIn + col : kOffB1 + h, g1[t][v]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f(kOffW2 + h * kHid + 16 * j + col, g2[t][j][v]);
+                if (col == 0) f(kOffB2 + h, gb2[t][v]);
+            }
+            if (quad == 0)
+#pragma unroll
+                for (int c = 0; c < kOut; ++c) f(kOffW3 + c * kHid + 16 * t + col, w3[t][c]);
+        }
+        if (lane == 0)
+#pragma unroll
+            for (int c = 0; c < kOut; ++c) f(kOffB3 + c, gb3[c]);
+    };
     __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (tid < k) red[tid] += red[tid + k];
-        __syncthreads();
-    }
-    if (tid == 0) lpart[blockIdx.x] = red[0];
+    if (wave & 1) each([&](int k, float g) { gs[k] = g; });
+    __syncthreads();
+    if (!(wave & 1)) each([&](int k, float g) { gs[k] = g + gs[k]; });
+    __syncthreads();
+    gs = reinterpret_cast<float *>(smem);
+    for (int k = tid; k < kP; k += 64 * kGradWaves) gpart[(int64_t)blockIdx.x * kP + k] = gs[k] + gs[kP + k];
+    if (tid == 0) lpart[blockIdx.x] = (lred[0] + lred[1]) + (lred[2] + lred[3]);
 }
 
-// column sums of gpart [G][kP] (fixed order) and the loss partials
-__global__ void k_grad_reduce(int G, const float *__restrict__ gpart, const double *__restrict__ lpart,
-                              float *__restrict__ grad, double *__restrict__ loss)
+// Column sums of gpart [G][kP] and the loss partials, in a fixed order: 64
+// columns per workgroup, 16 threads per column, so the partials stream in
+// parallel rows (one thread per column read them one after another: 299 us for
+// 1024 partials; 12 us for 512 here).  The last workgroup sums the loss.
+__global__ void __launch_bounds__(1024) k_grad_reduce(int G, const float *__restrict__ gpart,
+                                                      const double *__restrict__ lpart,
+                                                      float *__restrict__ grad, double *__restrict__ loss)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kP) {
-        double s = 0.0;
-        for (int b = 0; b < G; ++b) s += gpart[(int64_t)b * kP + k];
-        grad[k] = (float)s;
+    __shared__ double red[16][64];
+    const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
+    double s = 0.0;
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int b = threadIdx.x; b < G; b += 1024) s += lpart[b];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+        if (c == 0) red[q][0] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+            for (int k = 0; k < 16; ++k) t += red[k][0];
+            *loss = t;
+        }
+        return;
     }
-    if (k == 0) {
-        double s = 0.0;
-        for (int b = 0; b < G; ++b) s += lpart[b];
-        *loss = s;
+    const int k = blockIdx.x * 64 + c;
+    if (k < kP)
+        for (int b = q; b < G; b += 512) {   // 32 loads in flight: all 512 partials in one latency
+            float p[32];
+#pragma unroll
+            for (int j = 0; j < 32; ++j) p[j] = b + 16 * j < G ? gpart[(int64_t)(b + 16 * j) * kP + k] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 32; ++j) s += p[j];
+        }
+    red[q][c] = s;
+    __syncthreads();
+    if (q == 0 && k < kP) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t += red[j][c];
+        grad[k] = (float)t;
     }
 }
 
@@ -650,8 +922,8 @@ hipError_t mlp_loss_grad(hipStream_t s, int64_t rows, const uint16_t *X, const f
                          const float *params, float *gpart, double *lpart, int G, float *grad,
                          double *loss)
 {
-    hipLaunchKernelGGL(k_mlp_grad, dim3(G), dim3(256), 0, s, rows, X, aux, params, gpart, lpart);
-    hipLaunchKernelGGL(k_grad_reduce, dim3(g256(kP)), dim3(256), 0, s, G, gpart, lpart, grad, loss);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(G), dim3(64 * kGradWaves), 0, s, rows, X, aux, params, gpart, lpart);
+    hipLaunchKernelGGL(k_grad_reduce, dim3((kP + 63) / 64 + 1), dim3(1024), 0, s, G, gpart, lpart, grad, loss);
     return hipGetLastError();
 }
 

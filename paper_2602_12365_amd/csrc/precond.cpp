@@ -227,7 +227,7 @@ int efem_mlp_loss_grad(efem_ctx *ctx, int64_t rows, const uint16_t *X, const flo
     int rc;
     MlpState *M = mlp_state(*ctx, &rc);
     if (!M) return rc;
-    const int G = (int)std::max<int64_t>(1, std::min<int64_t>(kGradBlocks, (rows + 15) / 16));
+    const int G = (int)std::max<int64_t>(1, std::min<int64_t>(kGradBlocks, (rows + 63) / 64));   // 4 waves of 16 rows
     TRY(mlp_loss_grad(ctx->stream, rows, X, aux, params, M->gpart, M->lpart, G, grad, loss));
     return EFEM_OK;
 }

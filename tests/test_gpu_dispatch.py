@@ -37,3 +37,57 @@ def test_uniform_check_finds_one_element(at):
         op.set_material(dev(mu), dev(lam))
         ref = F.FEM(I.TET4, m.X, m.conn, mu, lam).energy(u)
         assert abs(float(op.energy(dev(u))) - ref) <= 1e-12 * abs(ref)
+
+
+@pytest.mark.parametrize("rows", [1, 15, 17, 64, 65, 2048 * 16 + 5])
+def test_mlp_gradient_at_row_remainders(rows):
+    """Loss gradient at the edges of the 16-row steps, the 64-row workgroups
+    and the grid's 2048 waves, against the float64 backward pass on the bf16
+    activations of the library's own forward (hidden activations are equal to
+    the last bit but for roundings at a bfloat16 boundary, so only FP32 sums
+    differ: each parameter's gradient within (rows + 130) 2^-24 of its sum of
+    absolute terms, rows capped at a wave's 512)."""
+    from paper_2602_12365_amd import Operator, _lib as L, precond as PC
+    g = np.random.default_rng(rows)
+    m = I.hex_mesh(2)
+    op = Operator(I.HEX8, m.X, m.conn)
+    theta = PC.init_params(3)
+    k = L.EFEM_MLP_OUT * (L.EFEM_MLP_HID + 1)
+    theta[-k:] += dev(0.2 * g.standard_normal(k), torch.float32)
+    x = np.zeros((rows, 16), dtype=np.float32)
+    x[:, :12] = g.standard_normal((rows, 12))
+    xb = torch.as_tensor(x).bfloat16()
+    aux = np.zeros((rows, L.EFEM_MLP_AUX), dtype=np.float32)
+    aux[:, :6] = g.standard_normal((rows, 6))
+    aux[:, 6:9] = g.random((rows, 3)) > 0.1
+    aux[:, 9] = np.exp(0.3 * g.standard_normal(rows))
+    aux[:, 10] = 1.0 / rows
+    op.set_mlp(theta)
+    X = xb.view(torch.int16).cuda()
+    h1, h2, out = op.mlp_forward_layers(X)
+    grad, loss = op.mlp_loss_grad(X, dev(aux), theta)
+    d = lambda t: t.cpu().double().numpy()  # noqa: E731
+    h1, h2, out = (d(t.view(torch.bfloat16) if t.dtype == torch.int16 else t) for t in (h1, h2, out))
+    t = d(theta.bfloat16())
+    W1, b1, W2, b2, W3 = (t[:768].reshape(64, 12), t[768:832], t[832:4928].reshape(64, 64), t[4928:4992],
+                          t[4992:5184].reshape(3, 64))
+    xd, ad = d(xb)[:, :12], aux.astype(np.float64)
+    e = ad[:, 6:9] * (ad[:, 0:3] + ad[:, 9:10] * out) - ad[:, 6:9] * ad[:, 3:6]
+    do = 2.0 * ad[:, 10:11] * ad[:, 9:10] * ad[:, 6:9] * e
+    sig = lambda a: 1.0 / (1.0 + np.exp(-a))  # noqa: E731
+    s2, s1 = sig(h1 @ W2.T + b2), sig(xd @ W1.T + b1)
+    d2 = (do @ W3) * s2
+    d1 = (d2 @ W2) * s1
+    parts = ((d1, xd), (d1, None), (d2, h1), (d2, None), (do, h2), (do, None))
+    ref = np.concatenate([(a.T @ b if b is not None else a.sum(0)).ravel() for a, b in parts])
+    # magnitudes of the terms, cancellation inside the deltas included
+    m_do = 2.0 * np.abs(ad[:, 10:11] * ad[:, 9:10] * ad[:, 6:9]) * (
+        np.abs(ad[:, 0:3]) + np.abs(ad[:, 9:10]) * (np.abs(h2) @ np.abs(W3).T + 1.0) + np.abs(ad[:, 3:6]))
+    m2 = (m_do @ np.abs(W3)) * (s2 + 1e-3)
+    m1 = (m2 @ np.abs(W2)) * (s1 + 1e-3)
+    mags = ((m1, xd), (m1, None), (m2, h1), (m2, None), (m_do, h2), (m_do, None))
+    mag = np.concatenate([(np.abs(a).T @ np.abs(b) if b is not None else a.sum(0)).ravel() for a, b in mags])
+    err = np.abs(d(grad) - ref)
+    tol = (min(rows, 512) + 130) * 2.0 ** -24 * mag + 1e-30
+    assert (err <= tol).all(), (err / tol).max()
+    assert abs(float(loss) - (ad[:, 10:11] * e * e).sum()) <= 1e-5 * float(loss)
