@@ -20,6 +20,14 @@ __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(ui
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ __forceinline__ float bfr(float f) { return bf2f(f2bf(f)); }
 
+// two bfloat16 values, a in the low half (one conversion for both)
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, bf2_t));
+}
+
 // softplus(x) = max(x, 0) + ln(1 + t), t = e^-|x| in (0, 1], with the
 // hardware base-2 exponential and logarithm (the exponent is <= 0 and the
 // logarithm's argument lies in [1, 2], so neither needs range reduction).
@@ -142,24 +150,28 @@ struct MlpRegs {
     float B1[4][4], B2[4][4], B3[4];
 };
 
+// Four consecutive parameters per load: every operand and bias of a lane starts
+// at a multiple of four in the parameter vector (kOff* and the row lengths 12
+// and 64 are), and W is the context's own 256-byte aligned copy.
 __device__ __forceinline__ void load_weights(const uint16_t *__restrict__ W, MlpRegs &R)
 {
+    static_assert(kIn % 4 == 0 && kHid % 4 == 0 && kOffB1 % 4 == 0 && kOffW2 % 4 == 0 && kOffB2 % 4 == 0
+                      && kOffW3 % 4 == 0, "four-wide weight loads");
     const int lane = threadIdx.x & 63, col = lane & 15, quad = lane >> 4;
+    const s4 none = {0, 0, 0, 0};
+    auto at = [&](int k) { return *reinterpret_cast<const s4 *>(W + k); };
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
+        R.A1[t] = quad < 3 ? at(kOffW1 + (16 * t + col) * kIn + 4 * quad) : none;
+        R.A3[t] = col < kOut ? at(kOffW3 + col * kHid + 16 * t + 4 * quad) : none;
+        const s4 b1 = at(kOffB1 + 16 * t + 4 * quad), b2 = at(kOffB2 + 16 * t + 4 * quad);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int k = 4 * quad + v;
-            R.A1[t][v] = k < kIn ? (short)W[kOffW1 + (16 * t + col) * kIn + k] : (short)0;
-            R.A3[t][v] = col < kOut ? (short)W[kOffW3 + col * kHid + 16 * t + k] : (short)0;
-            R.B1[t][v] = bf2f(W[kOffB1 + 16 * t + k]);
-            R.B2[t][v] = bf2f(W[kOffB2 + 16 * t + k]);
+            R.B1[t][v] = bf2f((uint16_t)b1[v]);
+            R.B2[t][v] = bf2f((uint16_t)b2[v]);
         }
 #pragma unroll
-        for (int t2 = 0; t2 < 4; ++t2)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                R.A2[t2][t][v] = (short)W[kOffW2 + (16 * t2 + col) * kHid + 16 * t + 4 * quad + v];
+        for (int t2 = 0; t2 < 4; ++t2) R.A2[t2][t] = at(kOffW2 + (16 * t2 + col) * kHid + 16 * t + 4 * quad);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) R.B3[v] = (4 * quad + v < kOut) ? bf2f(W[kOffB3 + 4 * quad + v]) : 0.f;
@@ -176,6 +188,15 @@ __device__ __forceinline__ void store_layer(uint16_t *__restrict__ H, const s4 h
     for (int t = 0; t < 4; ++t) *reinterpret_cast<s4 *>(H + node * kHid + 16 * t + 4 * quad) = h[t];
 }
 
+// four activations, bf16(softplus(d + b))
+__device__ __forceinline__ s4 act4(const f4 d, const float b[4])
+{
+    uint2 w;
+    w.x = pack_bf(softplus(d[0] + b[0]), softplus(d[1] + b[1]));
+    w.y = pack_bf(softplus(d[2] + b[2]), softplus(d[3] + b[3]));
+    return __builtin_bit_cast(s4, w);
+}
+
 // out[v] for v < 3 is valid in lanes 0..15 (node = lane).  LAYERS: the two
 // hidden layers' bf16 activations also go to H1 and H2 ([n][64]) for this
 // lane's node.
@@ -188,8 +209,7 @@ __device__ __forceinline__ f4 mlp16(const MlpRegs &R, s4 xb, uint16_t *H1 = null
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const f4 d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.A1[t], xb, zero, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) hb[t][v] = (short)f2bf(softplus(d[v] + R.B1[t][v]));
+        hb[t] = act4(d, R.B1[t]);
     }
     if constexpr (LAYERS) store_layer(H1, hb, node, n);
     s4 h2[4];
@@ -198,8 +218,7 @@ __device__ __forceinline__ f4 mlp16(const MlpRegs &R, s4 xb, uint16_t *H1 = null
         f4 d = zero;
 #pragma unroll
         for (int t = 0; t < 4; ++t) d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.A2[t2][t], hb[t], d, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) h2[t2][v] = (short)f2bf(softplus(d[v] + R.B2[t2][v]));
+        h2[t2] = act4(d, R.B2[t2]);
     }
     if constexpr (LAYERS) store_layer(H2, h2, node, n);
     f4 o = zero;
@@ -464,13 +483,6 @@ __device__ __forceinline__ void put_rows(unsigned char *p, uint2 own, uint32_t s
 // odd lanes units 1 and 3 (high halves: neighbour, own)
 constexpr uint32_t kSelEven = 0x05040100u, kSelOdd = 0x03020706u;
 
-// two bfloat16 values, a in the low half
-typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
-typedef float f2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf(float a, float b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, bf2_t));
-}
 __device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ s4 as_s4(uint2 w) { return __builtin_bit_cast(s4, w); }
