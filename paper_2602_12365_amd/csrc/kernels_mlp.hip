@@ -51,31 +51,48 @@ __device__ __forceinline__ float softplus(float x)
 // Static features (depend on the Jacobi diagonal and the mask only): slots
 // 6..15.  Bound by the gather of the neighbours' diagonals from L2.  The
 // 1-ring comes column-major (ell, as in k_feat_dyn), so each step's indices are
-// one coalesced load: by the row-wise lists, where every lane walked its own
-// range, the pass took 63 us for 274,625 nodes of 26 neighbours.
+// one coalesced load, and eight neighbours are in flight at once: 18.6 us for
+// 274,625 nodes of 26 neighbours (24.7 us with four loads between waits; 63 us
+// by row-wise lists, where every lane walked its own range).
+template <bool MASK>
 __global__ void __launch_bounds__(256) k_feat_static(int64_t n, const int64_t *__restrict__ ptr,
                                                      const int32_t *__restrict__ ell,
                                                      const double *__restrict__ diag,
                                                      const uint8_t *__restrict__ nmask, uint16_t *__restrict__ X)
 {
+    constexpr int kB = 8;   // neighbours in flight
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int deg = (int)(ptr[i + 1] - ptr[i]);
     const double di[3] = {diag[3 * i], diag[3 * i + 1], diag[3 * i + 2]};
     double sd[3] = {di[0], di[1], di[2]};
-    int sm = 0;
-#pragma unroll 4
-    for (int k = 0; k < deg; ++k) {
+    int sm = 0, k = 0;
+    for (; k + kB <= deg; k += kB) {
+        int64_t j[kB];
+        double d[kB][3];
+        int m[kB];
+#pragma unroll
+        for (int b = 0; b < kB; ++b) j[b] = ell[(int64_t)(k + b) * n + i];
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            d[b][0] = diag[3 * j[b]], d[b][1] = diag[3 * j[b] + 1], d[b][2] = diag[3 * j[b] + 2];
+            m[b] = MASK ? nmask[j[b]] : 0;
+        }
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            sd[0] += d[b][0], sd[1] += d[b][1], sd[2] += d[b][2];
+            if (MASK) sm += __popc(m[b]);
+        }
+    }
+    for (; k < deg; ++k) {
         const int64_t j = ell[(int64_t)k * n + i];
-        sd[0] += diag[3 * j];
-        sd[1] += diag[3 * j + 1];
-        sd[2] += diag[3 * j + 2];
-        if (nmask) sm += __popc(nmask[j]);
+        sd[0] += diag[3 * j], sd[1] += diag[3 * j + 1], sd[2] += diag[3 * j + 2];
+        if (MASK) sm += __popc(nmask[j]);
     }
     uint16_t x[10];
 #pragma unroll
     for (int c = 0; c < 3; ++c) x[c] = f2bf((float)log(di[c] / (sd[c] / (deg + 1))));
-    const float mi = nmask ? (float)__popc(nmask[i]) : 0.f;
+    const float mi = MASK ? (float)__popc(nmask[i]) : 0.f;
     x[3] = f2bf(mi / 3.f);
     x[4] = f2bf((float)sm / (3.f * (float)max(deg, 1)));
     x[5] = f2bf((float)deg / 26.f);
@@ -111,6 +128,21 @@ __global__ void k_feat_dyn(int64_t n, const int64_t *__restrict__ ptr, const int
     const float g0 = gi.x, g1 = gi.y, g2 = gi.z;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, q = gi.w;
     int k = 0;
+    for (; k + 8 <= max_deg; k += 8) {   // four pairs in flight
+        int32_t j[8];
+        float4 v[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) j[b] = ell[(int64_t)(k + b) * n + i];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) v[b] = g4[j[b]];
+#pragma unroll
+        for (int b = 0; b < 8; b += 2) {
+            s0 += v[b].x + v[b + 1].x;
+            s1 += v[b].y + v[b + 1].y;
+            s2 += v[b].z + v[b + 1].z;
+            q += v[b].w + v[b + 1].w;
+        }
+    }
     for (; k + 2 <= max_deg; k += 2) {
         const float4 a = g4[ell[(int64_t)k * n + i]], b = g4[ell[(int64_t)(k + 1) * n + i]];
         s0 += a.x + b.x;
@@ -881,6 +913,25 @@ __global__ void k_dinv_f32(int64_t n, const double *__restrict__ diag, const uin
     dinv[i] = fixed ? 0.f : (float)(1.0 / diag[i]);
 }
 
+// dinv of the diagonal and g4 of r in one pass over the nodes (the values of
+// k_dinv_f32 and k_g4): an apply at a new diagonal starts with one launch
+__global__ void __launch_bounds__(256) k_dinv_g4(int64_t n, const double *__restrict__ diag,
+                                                 const uint8_t *__restrict__ nmask, const float *__restrict__ r,
+                                                 float *__restrict__ dinv, float4 *__restrict__ g4)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int m = nmask ? nmask[i] : 0;
+    float g[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float d = (m >> c) & 1 ? 0.f : (float)(1.0 / diag[3 * i + c]);
+        dinv[3 * i + c] = d;
+        g[c] = r[3 * i + c] * d;
+    }
+    g4[i] = make_float4(g[0], g[1], g[2], g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
+}
+
 // ---------------------------------------------------------------- launchers
 
 static unsigned g256(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -891,14 +942,22 @@ static unsigned mlp_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std:
 hipError_t mlp_features_static(hipStream_t s, const MlpState &M, int64_t n, const double *diag,
                                const uint8_t *nmask, uint16_t *X)
 {
-    hipLaunchKernelGGL(k_feat_static, dim3(g256(n)), dim3(256), 0, s, n, M.ptr, M.ell, diag, nmask, X);
+    auto kern = nmask ? k_feat_static<true> : k_feat_static<false>;
+    hipLaunchKernelGGL(kern, dim3(g256(n)), dim3(256), 0, s, n, M.ptr, M.ell, diag, nmask, X);
+    return hipGetLastError();
+}
+
+hipError_t mlp_dinv_g4(hipStream_t s, int64_t n, const double *diag, const uint8_t *nmask, const float *r,
+                       float *dinv, float4 *g4)
+{
+    hipLaunchKernelGGL(k_dinv_g4, dim3(g256(n)), dim3(256), 0, s, n, diag, nmask, r, dinv, g4);
     return hipGetLastError();
 }
 
 hipError_t mlp_features_dyn(hipStream_t s, const MlpState &M, int64_t n, const float *r,
                             const float *dinv, uint16_t *X, float *scale, float4 *g4)
 {
-    hipLaunchKernelGGL(k_g4, dim3(g256(n)), dim3(256), 0, s, n, r, dinv, g4);
+    if (r) hipLaunchKernelGGL(k_g4, dim3(g256(n)), dim3(256), 0, s, n, r, dinv, g4);
     hipLaunchKernelGGL(k_feat_dyn, dim3(g256(n)), dim3(256), 0, s, n, M.ptr, M.ell, M.max_deg, g4, X, scale);
     return hipGetLastError();
 }

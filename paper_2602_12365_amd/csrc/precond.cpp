@@ -169,8 +169,11 @@ int efem_precond_apply(efem_ctx *ctx, const float *r, const double *diag, float 
         set_error("efem_precond_apply: call efem_set_mlp first");
         return EFEM_ERR_STATE;
     }
-    TRY(mlp_prepare(*ctx, *M, diag));
-    TRY(mlp_precondition(*ctx, *M, r, z));
+    const int64_t n = ctx->n_nodes;
+    TRY(mlp_dinv_g4(ctx->stream, n, diag, ctx->m.nmask, r, M->dinv, M->g4));
+    TRY(mlp_features_static(ctx->stream, *M, n, diag, ctx->m.nmask, M->X));
+    TRY(mlp_features_dyn(ctx->stream, *M, n, nullptr, M->dinv, M->X, M->scale, M->g4));
+    TRY(mlp_apply(ctx->stream, M->W, n, M->X, r, M->dinv, M->scale, z, M->prz));
     return EFEM_OK;
 }
 
