@@ -499,9 +499,11 @@ int efem_sparse_setup(efem_ctx *ctx, efem_sparse_info *info);
  * [nnz], dof_colour DEVICE int32 [n_rows].  EFEM_ERR_STATE before setup. */
 int efem_sparse_pattern(efem_ctx *ctx, int64_t *row_ptr, int32_t *col, int32_t *dof_colour);
 
-/* values (DEVICE float64 [nnz], in pattern order) = K(u) from n_colours FP64
- * tangent actions at u (DEVICE float64 [3*n_nodes]; the context's FP64
- * linearization is set to u). */
+/* values (DEVICE float64 [nnz], in pattern order) = K(u) in FP64 at u (DEVICE
+ * float64 [3*n_nodes]; the context's FP64 linearization is set to u): the
+ * entries that the n_colours tangent actions of the colouring recover,
+ * evaluated by node rows from the elements' tangent columns, or, where a
+ * node's ring exceeds 255 nodes, by those actions themselves. */
 int efem_sparse_assemble(efem_ctx *ctx, const double *u, double *values);
 
 /* The same pattern by 3x3 blocks: block_ptr DEVICE int64 [n_nodes+1],

@@ -24,6 +24,7 @@
 #include <mutex>
 
 #include "efem_internal.h"
+#include "efem_sparse.h"
 
 namespace efem {
 
@@ -2748,6 +2749,282 @@ hipError_t launch_vjp_material(const Ctx &c, const double *u, const double *w, d
     else
         lin ? vjp_material_pass<Hex8, true>(c, u, w, dmu, dlam, lds)
             : vjp_material_pass<Hex8, false>(c, u, w, dmu, dlam, lds);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------- sparse tangent by node rows
+
+// One element at a quadrature point as a row visit sees it: set(q) the point,
+// grad the gradient of a nodal field, n(b, J) the shape-function derivatives
+// and N(b) the values, n_at / N_at those of a run-time node.
+struct VisitSimplex {
+    static constexpr int NPOS = 4, NQ = 1;
+    __device__ __forceinline__ void set(int) {}
+    __device__ static __forceinline__ double n_at(int a, int J) { return a == 0 ? -1.0 : (a == J + 1 ? 1.0 : 0.0); }
+};
+struct VisitTet4 : VisitSimplex {
+    static constexpr int NEN = 4;
+    static constexpr double w = 1.0 / 6.0;
+    __device__ static constexpr double n(int b, int J) { return b == 0 ? -1.0 : (b == J + 1 ? 1.0 : 0.0); }
+    __device__ static __forceinline__ void grad(const double f[4][3], double G[9])
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int J = 0; J < 3; ++J) G[i * 3 + J] = f[J + 1][i] - f[0][i];
+    }
+    __device__ static __forceinline__ void geom(double *) {}
+    __device__ static constexpr double N(int) { return 0.25; }
+    __device__ static constexpr double N_at(int) { return 0.25; }
+};
+struct VisitTri3 : VisitSimplex {
+    static constexpr int NEN = 3;
+    static constexpr double w = 0.5;
+    __device__ static constexpr double n(int b, int J)
+    {
+        return J == 2 ? 0.0 : (b == 0 ? -1.0 : (b == J + 1 ? 1.0 : 0.0));
+    }
+    __device__ static __forceinline__ double n_at(int a, int J) { return J == 2 ? 0.0 : VisitSimplex::n_at(a, J); }
+    __device__ static __forceinline__ void grad(const double f[3][3], double G[9])
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            G[i * 3 + 0] = f[1][i] - f[0][i];
+            G[i * 3 + 1] = f[2][i] - f[0][i];
+            G[i * 3 + 2] = 0.0;
+        }
+    }
+    __device__ static __forceinline__ void geom(double *G) { G[8] += 1.0; }
+    __device__ static constexpr double N(int) { return 1.0 / 3.0; }
+    __device__ static constexpr double N_at(int) { return 1.0 / 3.0; }
+};
+// The points run in a loop that is not unrolled: the 72 accumulators of a
+// visit's eight blocks leave no registers for several points at once.
+struct VisitHex8 {
+    static constexpr int NEN = 8, NPOS = 8, NQ = 8;
+    static constexpr double w = 1.0;
+    double p[3];      // coordinates of the point
+    double D[3][4];   // (1 + s1 p1)(1 + s2 p2) / 8 of the four edges of direction J
+    __device__ __forceinline__ void set(int q)
+    {
+        const double g = 0.57735026918962576451;
+#pragma unroll
+        for (int J = 0; J < 3; ++J) p[J] = ((q >> J) & 1) ? g : -g;
+#pragma unroll
+        for (int J = 0; J < 3; ++J) {
+            const double a = p[Hex8::oth1(J)], b = p[Hex8::oth2(J)];
+            D[J][0] = 0.125 * (1.0 - a) * (1.0 - b);
+            D[J][1] = 0.125 * (1.0 + a) * (1.0 - b);
+            D[J][2] = 0.125 * (1.0 - a) * (1.0 + b);
+            D[J][3] = 0.125 * (1.0 + a) * (1.0 + b);
+        }
+    }
+    __device__ __forceinline__ void grad(const double u[8][3], double G[9]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int J = 0; J < 3; ++J) {
+                double t = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t += D[J][k] * (u[kHexEdge[J][k][1]][i] - u[kHexEdge[J][k][0]][i]);
+                G[i * 3 + J] = t;
+            }
+    }
+    __device__ static __forceinline__ void geom(double *) {}
+    __device__ __forceinline__ double n(int b, int J) const { return kHexS[b][J] * D[J][Hex8::edge_of(J, b)]; }
+    __device__ __forceinline__ double N(int b) const { return D[0][Hex8::edge_of(0, b)] * (1.0 + kHexS[b][0] * p[0]); }
+    // bit J: whether local node a lies on the + side of direction J
+    __device__ static __forceinline__ int side(int a, int J)
+    {
+        return (J == 2 ? a >> 2 : (J == 1 ? a >> 1 : a ^ (a >> 1))) & 1;
+    }
+    __device__ __forceinline__ double at(int a, int J) const { return 1.0 + (side(a, J) ? p[J] : -p[J]); }
+    __device__ __forceinline__ double n_at(int a, int J) const
+    {
+        return (side(a, J) ? 0.125 : -0.125) * at(a, Hex8::oth1(J)) * at(a, Hex8::oth2(J));
+    }
+    __device__ __forceinline__ double N_at(int a) const { return 0.125 * at(a, 0) * at(a, 1) * at(a, 2); }
+};
+
+// Values of K by node rows: a wave owns whole rows (RowVisits), 64 / R lanes
+// per row take its visits in turn.  A visit evaluates the 3x3 blocks of its
+// node against all nodes of the element (with t = Ae^T n and k = Ad^T n, n the
+// shape functions' xi-gradients:
+//   neo-Hookean  w [mu/De t_a.t_b I + lam De/Dd^2 k_a k_b^T + c1 De/Dd^2 k_b k_a^T],
+//   linear       w/De [mu t_a.t_b I + lam t_a t_b^T + mu t_b t_a^T],
+//   transport    w [D/De t_a.t_b + (b.t_b + k De N_b) N_a] I)
+// and adds them into the rows in LDS, in the order the values are stored in, so
+// that each row leaves as one coalesced run and is written once.
+// Bound by FP64 issue and the LDS atomics: an element is evaluated once per
+// node (4 or 8 times), where recovery by colouring evaluated it once per
+// colour (90 on Kuhn tetrahedra, 81 on hexahedra) with four launches each.
+// Assembly by colours against rows: 1,356 and 43 us at 32^3 Kuhn tetrahedra,
+// 3,718 and 250 us at 64^3 (writing the values alone takes 57 us at the copy
+// rate), 5,425 and 800 us at 64^3 hexahedra (one wave per SIMD).  Eight nodes
+// per wave: sixteen took 55 and 283 us on the tetrahedra (half the waves, and
+// twice the LDS each).
+template <class E, int MODEL>
+__global__ void __launch_bounds__(256) k_assemble_rows(BlockMesh m, RowVisits rv, const double *__restrict__ xrec,
+                                                       double om0, double om1, double om2,
+                                                       double *__restrict__ values)
+{
+    extern __shared__ __align__(16) double rows_lds[];
+    constexpr int R = kRowNodes, PH = 64 / R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int W = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6)) + wave);
+    if (W >= rv.n_waves) return;   // no barrier below: every wave works on its own rows
+    double *acc = rows_lds + (size_t)wave * rv.max_blocks * 9;
+    const int r0 = rv.wstart[W], nr = rv.wstart[W + 1] - r0;
+    const int k = lane % R, ph = lane / R;
+    const int node = k < nr ? rv.node[r0 + k] : 0;
+    const int len = k < nr ? (int)(rv.bptr[node + 1] - rv.bptr[node]) : 0;
+    int base = 0, total = 0;   // blocks in front of this lane's row, and in all rows
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int l = __shfl(len, j, 64);
+        base += j < k ? l : 0;
+        total += l;
+    }
+    for (int i = lane; i < 9 * total; i += 64) acc[i] = 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double *row = acc + 9 * base;
+    bool bad = false;
+    const int v1 = k < nr ? rv.vptr[r0 + k + 1] : 0;
+    for (int v = k < nr ? rv.vptr[r0 + k] + ph : 0; v < v1; v += PH) {
+        const uint32_t word = rv.visit[v];
+        const int e = (int)(word >> 3), a = (int)(word & 7u);
+        double X[E::NEN][3], x[E::NEN][3];
+#pragma unroll
+        for (int b = 0; b < E::NEN; ++b) {
+            const double *p = xrec + 6 * (int64_t)rv.conn[(int64_t)e * E::NEN + b];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                X[b][i] = p[i];
+                x[b][i] = p[3 + i];
+            }
+        }
+        const double mu = m.mu ? m.mu[e] : m.mu0, lam = m.lam ? m.lam[e] : m.lam0;
+        double B[E::NEN][3][3];
+#pragma unroll
+        for (int b = 0; b < E::NEN; ++b)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) B[b][i][j] = 0.0;
+#pragma unroll 1
+        for (int q = 0; q < E::NQ; ++q) {
+            E pt;
+            pt.set(q);
+            double Jx[9], Ae[9], Ad[9];
+            pt.grad(X, Jx);
+            E::geom(Jx);
+            const double De = adj_det(Jx, Ae);
+            const double rDe = rcp(De), w = E::w;
+            double cI, cA = 0.0, cB = 0.0, bx = 0.0, by = 0.0, bz = 0.0, kDe = 0.0;
+            if constexpr (MODEL == EFEM_MODEL_NEO_HOOKE) {
+                double Jd[9];
+                pt.grad(x, Jd);
+                E::geom(Jd);
+                const double Dd = adj_det(Jd, Ad);
+                bad |= !(Dd > 0.0);
+                const double rDd = rcp(Dd), s2 = w * De * rDd * rDd;
+                cI = w * mu * rDe;
+                cA = lam * s2;
+                cB = (mu - lam * log_(Dd * rDe)) * s2;
+            } else if constexpr (MODEL == EFEM_MODEL_LINEAR) {
+                const double c = w * rDe;
+                cI = cB = c * mu;
+                cA = c * lam;
+            } else {
+                cI = w * mu * rDe;
+                kDe = w * lam * De;
+                double xq[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int b = 0; b < E::NEN; ++b)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) xq[i] += pt.N(b) * X[b][i];
+                bx = w * (om1 * xq[2] - om2 * xq[1]);
+                by = w * (om2 * xq[0] - om0 * xq[2]);
+                bz = w * (om0 * xq[1] - om1 * xq[0]);
+            }
+            const double *A = MODEL == EFEM_MODEL_NEO_HOOKE ? Ad : Ae;
+            double ta[3], ai[3], bi[3], ka[3];
+            {
+                const double g0 = pt.n_at(a, 0), g1 = pt.n_at(a, 1), g2 = pt.n_at(a, 2);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    ta[i] = cI * (Ae[i] * g0 + Ae[3 + i] * g1 + Ae[6 + i] * g2);
+                    ka[i] = A[i] * g0 + A[3 + i] * g1 + A[6 + i] * g2;
+                    ai[i] = cA * ka[i];
+                    bi[i] = cB * ka[i];
+                }
+            }
+            const double Na = pt.N_at(a);
+#pragma unroll
+            for (int b = 0; b < E::NEN; ++b) {
+                const double n0 = pt.n(b, 0), n1 = pt.n(b, 1), n2 = pt.n(b, 2);
+                double tb[3], kb[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    tb[i] = Ae[i] * n0 + Ae[3 + i] * n1 + Ae[6 + i] * n2;
+                    kb[i] = MODEL == EFEM_MODEL_NEO_HOOKE ? Ad[i] * n0 + Ad[3 + i] * n1 + Ad[6 + i] * n2 : tb[i];
+                }
+                double d = ta[0] * tb[0] + ta[1] * tb[1] + ta[2] * tb[2];
+                if constexpr (MODEL == EFEM_MODEL_TRANSPORT) d += (bx * tb[0] + by * tb[1] + bz * tb[2] + kDe * pt.N(b)) * Na;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    B[b][i][i] += d;
+                    if constexpr (MODEL != EFEM_MODEL_TRANSPORT)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) B[b][i][j] += ai[i] * kb[j] + bi[j] * kb[i];
+                }
+            }
+        }
+        const uint8_t *ps = rv.pos + (int64_t)v * E::NPOS;
+#pragma unroll
+        for (int b = 0; b < E::NEN; ++b) {
+            double *d = row + 3 * ps[b];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (MODEL != EFEM_MODEL_TRANSPORT || i == j) atomicAdd(d + i * 3 * len + j, B[b][i][j]);
+        }
+    }
+    if (bad) flag_inverted(m.flags);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // the rows out, one after another; prescribed rows and columns are 0
+    for (int j = 0; j < nr; ++j) {
+        const int lj = __builtin_amdgcn_readlane(len, j), bj = __builtin_amdgcn_readlane(base, j);
+        const int64_t g = __builtin_amdgcn_readlane(node, j), b0 = rv.bptr[g];
+        for (int i = lane; i < 9 * lj; i += 64) {
+            double val = acc[9 * bj + i];
+            if (m.nmask) {
+                const int comp = i / (3 * lj), c = i - comp * 3 * lj, blk = c / 3;
+                if (((m.nmask[g] >> comp) & 1) || ((m.nmask[rv.bcol[b0 + blk]] >> (c - 3 * blk)) & 1)) val = 0.0;
+            }
+            values[9 * b0 + i] = val;
+        }
+    }
+}
+
+template <class E>
+static void assemble_rows(const Ctx &c, const RowVisits &rv, const double *xrec, double *values)
+{
+    const size_t lds = 4 * (size_t)rv.max_blocks * 9 * sizeof(double);
+    auto kern = c.model == EFEM_MODEL_TRANSPORT ? k_assemble_rows<E, EFEM_MODEL_TRANSPORT>
+                : c.model == EFEM_MODEL_LINEAR  ? k_assemble_rows<E, EFEM_MODEL_LINEAR>
+                                                : k_assemble_rows<E, EFEM_MODEL_NEO_HOOKE>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((rv.n_waves + 3) / 4)), dim3(256), lds, c.stream, c.m, rv, xrec,
+                       c.omega[0], c.omega[1], c.omega[2], values);
+}
+
+hipError_t launch_assemble_rows(const Ctx &c, const RowVisits &rv, const double *xrec, double *values)
+{
+    if (c.elem == EFEM_TET4) assemble_rows<VisitTet4>(c, rv, xrec, values);
+    else if (c.elem == EFEM_TRI3) assemble_rows<VisitTri3>(c, rv, xrec, values);
+    else assemble_rows<VisitHex8>(c, rv, xrec, values);
     return hipGetLastError();
 }
 

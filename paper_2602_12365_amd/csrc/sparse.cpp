@@ -5,6 +5,13 @@
 // graph) and they are not components of one node; the product of K with the
 // indicator vector of a colour then holds, in each row, the single entry of
 // that colour.  The pattern is the node 1-ring in 3x3 blocks.
+//
+// The same entries come directly from the elements: a unit vector of one
+// colour is zero on all but one node of an element, so an element's action on
+// it is one column of its tangent, and 78 of the 90 actions of a tetrahedral
+// mesh contribute nothing to a given tetrahedron.  The assembly therefore
+// evaluates each element's columns once, by node rows (k_assemble_rows), where
+// the rows allow it.
 #include <algorithm>
 #include <chrono>
 #include <cstring>
@@ -78,6 +85,77 @@ void node_ring(const Ctx &c, std::vector<int64_t> &ptr, std::vector<int32_t> &id
     }
 }
 
+// The visits of every node row (rp, ri: the node rings), rows in the order in
+// which the element blocks first meet their nodes.
+int build_visits(Ctx &c, SparseState &S, const std::vector<int64_t> &rp, const std::vector<int32_t> &ri)
+{
+    const int64_t nn = c.n_nodes, ne = c.n_elems;
+    const int nen = c.nen, npos = nen == 8 ? 8 : 4;
+    std::vector<int32_t> eorig((size_t)ne);
+    TRY(hipMemcpy(eorig.data(), c.m.eorig, (size_t)ne * sizeof(int32_t), hipMemcpyDeviceToHost));
+    int32_t nb = 0;
+    TRY(hipMemcpy(&nb, c.m.nstart + c.m.n_blocks, sizeof(int32_t), hipMemcpyDeviceToHost));
+    std::vector<uint32_t> bnode((size_t)nb);
+    TRY(hipMemcpy(bnode.data(), c.m.bnode, (size_t)nb * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    std::vector<int32_t> node, row_of((size_t)nn, -1);
+    node.reserve((size_t)nn);
+    for (uint32_t w : bnode) {
+        const int32_t g = (int32_t)(w & kGidMask);
+        if (row_of[(size_t)g] >= 0) continue;
+        row_of[(size_t)g] = (int32_t)node.size();
+        node.push_back(g);
+    }
+    std::vector<int32_t> conn((size_t)(ne * nen)), vptr((size_t)nn + 1, 0);
+    for (int64_t e = 0; e < ne; ++e)
+        for (int a = 0; a < nen; ++a) {
+            const int32_t g = c.conn_host[(size_t)eorig[(size_t)e] * nen + a];
+            conn[(size_t)(e * nen + a)] = g;
+            vptr[(size_t)row_of[(size_t)g] + 1] += 1;
+        }
+    for (int64_t r = 0; r < nn; ++r) vptr[(size_t)r + 1] += vptr[(size_t)r];
+    std::vector<uint32_t> visit((size_t)(ne * nen));
+    std::vector<int32_t> fill(vptr.begin(), vptr.end() - 1);
+    for (int64_t e = 0; e < ne; ++e)
+        for (int a = 0; a < nen; ++a)
+            visit[(size_t)fill[(size_t)row_of[(size_t)conn[(size_t)(e * nen + a)]]]++] = (uint32_t)e << 3 | (uint32_t)a;
+    std::vector<uint8_t> pos(visit.size() * (size_t)npos, 0);
+    std::vector<int32_t> at((size_t)nn, 0), wstart{0};
+    int32_t blocks = 0, max_blocks = 0;
+    for (int64_t r = 0; r < nn; ++r) {
+        const int64_t b = rp[(size_t)node[(size_t)r]], len = rp[(size_t)node[(size_t)r] + 1] - b;
+        for (int64_t t = 0; t < len; ++t) at[(size_t)ri[(size_t)(b + t)]] = (int32_t)t;
+        for (int32_t v = vptr[(size_t)r]; v < vptr[(size_t)r + 1]; ++v)
+            for (int a = 0; a < nen; ++a)
+                pos[(size_t)v * npos + a] = (uint8_t)at[(size_t)conn[(size_t)(visit[(size_t)v] >> 3) * nen + a]];
+        if (r - wstart.back() == kRowNodes || blocks + len > kRowBlocks) {
+            wstart.push_back((int32_t)r);
+            blocks = 0;
+        }
+        blocks += (int32_t)len;
+        max_blocks = std::max(max_blocks, blocks);
+    }
+    wstart.push_back((int32_t)nn);
+    int32_t *p_w, *p_n, *p_v, *p_c;
+    uint32_t *p_vi;
+    uint8_t *p_p;
+    int rc;
+    if ((rc = upload_into(S, &p_w, wstart)) || (rc = upload_into(S, &p_n, node)) || (rc = upload_into(S, &p_v, vptr))
+        || (rc = upload_into(S, &p_vi, visit)) || (rc = upload_into(S, &p_p, pos)) || (rc = upload_into(S, &p_c, conn)))
+        return rc;
+    RowVisits &R = S.rows;
+    R.n_waves = (int32_t)wstart.size() - 1;
+    R.max_blocks = max_blocks;
+    R.wstart = p_w;
+    R.node = p_n;
+    R.vptr = p_v;
+    R.visit = p_vi;
+    R.pos = p_p;
+    R.conn = p_c;
+    R.bptr = S.bptr;
+    R.bcol = S.bcol;
+    return EFEM_OK;
+}
+
 int build(Ctx &c, SparseState &S)
 {
     const auto t0 = std::chrono::steady_clock::now();
@@ -124,32 +202,37 @@ int build(Ctx &c, SparseState &S)
                 for (int b = 0; b < 3; ++b) col[(size_t)k++] = 3 * ri[(size_t)t] + b;
             dcol[(size_t)(3 * i + a)] = 3 * ncol[(size_t)i] + a;
         }
-    // entries grouped by the colour of their column (counting sort)
     const int32_t n_colours = 3 * n_node_colours;
-    std::vector<int64_t> cstart((size_t)n_colours + 1, 0);
-    for (int64_t k = 0; k < nnz; ++k) cstart[(size_t)dcol[(size_t)col[(size_t)k]] + 1] += 1;
-    for (int32_t q = 0; q < n_colours; ++q) cstart[(size_t)q + 1] += cstart[(size_t)q];
-    std::vector<int64_t> ent((size_t)nnz), pos(cstart.begin(), cstart.end() - 1);
-    std::vector<int32_t> ent_row((size_t)nnz);
-    for (int64_t r = 0; r < n_rows; ++r)
-        for (int64_t k = row_ptr[(size_t)r]; k < row_ptr[(size_t)r + 1]; ++k) {
-            const int64_t p = pos[(size_t)dcol[(size_t)col[(size_t)k]]]++;
-            ent[(size_t)p] = k;
-            ent_row[(size_t)p] = (int32_t)r;
-        }
     int rc;
     if ((rc = upload_into(S, &S.row_ptr, row_ptr)) || (rc = upload_into(S, &S.col, col))
-        || (rc = upload_into(S, &S.dof_colour, dcol)) || (rc = upload_into(S, &S.ent, ent))
-        || (rc = upload_into(S, &S.ent_row, ent_row)) || (rc = alloc_into(S, &S.seed, (size_t)n_rows))
-        || (rc = alloc_into(S, &S.y, (size_t)n_rows)) || (rc = upload_into(S, &S.bptr, rp))
+        || (rc = upload_into(S, &S.dof_colour, dcol)) || (rc = upload_into(S, &S.bptr, rp))
         || (rc = upload_into(S, &S.bcol, ri)))
         return rc;
+    if (max_row <= 3 * 255) {
+        if ((rc = build_visits(c, S, rp, ri))) return rc;
+    } else {
+        // entries grouped by the colour of their column (counting sort)
+        std::vector<int64_t> cstart((size_t)n_colours + 1, 0);
+        for (int64_t k = 0; k < nnz; ++k) cstart[(size_t)dcol[(size_t)col[(size_t)k]] + 1] += 1;
+        for (int32_t q = 0; q < n_colours; ++q) cstart[(size_t)q + 1] += cstart[(size_t)q];
+        std::vector<int64_t> ent((size_t)nnz), pos(cstart.begin(), cstart.end() - 1);
+        std::vector<int32_t> ent_row((size_t)nnz);
+        for (int64_t r = 0; r < n_rows; ++r)
+            for (int64_t k = row_ptr[(size_t)r]; k < row_ptr[(size_t)r + 1]; ++k) {
+                const int64_t p = pos[(size_t)dcol[(size_t)col[(size_t)k]]]++;
+                ent[(size_t)p] = k;
+                ent_row[(size_t)p] = (int32_t)r;
+            }
+        if ((rc = upload_into(S, &S.ent, ent)) || (rc = upload_into(S, &S.ent_row, ent_row))
+            || (rc = alloc_into(S, &S.seed, (size_t)n_rows)) || (rc = alloc_into(S, &S.y, (size_t)n_rows)))
+            return rc;
+        S.cstart = std::move(cstart);
+    }
     S.n_blocks = (int64_t)ri.size();
     S.n_rows = n_rows;
     S.nnz = nnz;
     S.n_colours = n_colours;
     S.max_row = max_row;
-    S.cstart = std::move(cstart);
     S.setup_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return EFEM_OK;
 }
@@ -232,6 +315,10 @@ int efem_sparse_assemble(efem_ctx *ctx, const double *u, double *values)
     const int rc = efem_linearize(ctx, u, EFEM_F64);
     if (rc) return rc;
     const SparseState &S = *static_cast<SparseState *>(ctx->sparse);
+    if (S.rows.n_waves > 0) {
+        TRY(launch_assemble_rows(*ctx, S.rows, ctx->xlin, values));
+        return EFEM_OK;
+    }
     for (int32_t q = 0; q < S.n_colours; ++q) {
         const int64_t b = S.cstart[(size_t)q], cnt = S.cstart[(size_t)q + 1] - b;
         if (cnt == 0) continue;

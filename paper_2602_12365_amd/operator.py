@@ -339,7 +339,7 @@ class Operator:
         return bp, bc
 
     def sparse_assemble(self, u, values=None):
-        """K(u) values (float64 [nnz], pattern order) from n_colours tangent actions."""
+        """K(u) values (float64 [nnz], pattern order)."""
         info = self._sparse if getattr(self, "_sparse", None) else self.sparse_setup()
         if values is None:
             values = torch.empty(info["nnz"], dtype=torch.float64, device=self.device)

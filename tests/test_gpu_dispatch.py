@@ -91,3 +91,45 @@ def test_mlp_gradient_at_row_remainders(rows):
     tol = (min(rows, 512) + 130) * 2.0 ** -24 * mag + 1e-30
     assert (err <= tol).all(), (err / tol).max()
     assert abs(float(loss) - (ad[:, 10:11] * e * e).sum()) <= 1e-5 * float(loss)
+
+
+def _fan(n):
+    """n triangles around one hub node (its ring holds n + 1 nodes)."""
+    a = 2.0 * np.pi * np.arange(n) / n
+    X = np.concatenate([[[0.0, 0.0, 0.0]], np.stack([np.cos(a), np.sin(a), 0.0 * a], axis=1)])
+    k = np.arange(n)
+    conn = np.stack([0 * k, 1 + k, 1 + (k + 1) % n], axis=1).astype(np.int32)
+    return I.Mesh(I.TRI3, n, X, conn)
+
+
+@pytest.mark.parametrize("model", ["neo_hookean", "linear"])
+@pytest.mark.parametrize("mesh", ["fan254", "fan255", "fan300", "tet1", "tet5s", "hex1", "hex5s"])
+def test_assembly_by_rows_and_by_colours(mesh, model):
+    """Sparse assembly at the rule's line (a ring of 255 nodes goes by rows,
+    256 by colours), on one cell and on meshes that leave partly filled waves,
+    free and with prescribed DOFs, against the oracle's tangent (1e-10)."""
+    from paper_2602_12365_amd import Operator
+    if mesh.startswith("fan"):
+        m = _fan(int(mesh[3:]))
+    else:
+        m = I.make_mesh(I.TET4 if mesh[0] == "t" else I.HEX8, int(mesh[3]))
+        m = I.scrambled_mesh(m, 5) if mesh.endswith("s") else m
+    g = np.random.default_rng(4)
+    mu = np.exp(0.3 * g.standard_normal(m.n_elems))
+    u = 0.02 / max(m.n, 1) * g.standard_normal((m.n_nodes, 3))
+    if mesh.startswith("fan"):
+        u = 1e-4 * g.standard_normal((m.n_nodes, 3))
+    op = Operator(m.elem, m.X, m.conn, model=model)
+    op.set_material(dev(mu), dev(1.5 * mu))
+    K = F.FEM(m.elem, m.X, m.conn, mu, 1.5 * mu, model=model).tangent_matrix(u)
+    K.sort_indices()
+    got = op.sparse_assemble(dev(u)).cpu().numpy()
+    assert np.abs(got - K.data).max() <= 1e-10 * np.abs(K.data).max()
+    mask = (g.random(3 * m.n_nodes) < 0.3).astype(np.uint8)
+    op.set_dirichlet(dev(mask))
+    got = op.sparse_assemble(dev(u)).cpu().numpy()
+    C = K.tocoo()
+    C.data = np.where((mask[C.row] == 0) & (mask[C.col] == 0), C.data, 0.0)
+    C = C.tocsr()
+    C.sort_indices()
+    assert np.abs(got - C.data).max() <= 1e-10 * np.abs(K.data).max()
