@@ -230,6 +230,26 @@ static int pair_tets(const double *X, const int32_t *conn, std::vector<int32_t> 
     return np;
 }
 
+// Default elements per block.
+// Tetrahedra: 1536 (768 pairs) within 600 nodes; triangles: 768 within 600 nodes
+// (measured on 64^3 and 1024^2 cells).
+// Hexahedra (an element on four lanes, so 64 of them fill a workgroup's four
+// waves): the smallest of 64, 128 and 256 that leaves at most two blocks per
+// CU, else 256.  A mesh in few blocks leaves CUs idle, small blocks stage more
+// shared nodes, and 256 keeps three workgroups' LDS per CU where 512 keeps two.
+// FP64 tangent action: 16^3 7.5 us in 64s, 13.1 in 256s, 20.7 in 512s; 32^3
+// 10.0, 13.9, 21.3; 64^3 39.8, 37.8, 38.5; 96^3 102 in 256s, 159 in 512s.
+// Beyond 2^23 hexahedra 512 (even at 128^3: 231 and 234), which keeps the block
+// count of every mesh that efem_energy_noalloc's 65,536 partials can hold.
+static int default_block_elems(int elem, int64_t ne)
+{
+    if (elem == EFEM_TET4) return 1536;
+    if (elem == EFEM_TRI3) return 768;
+    for (int be : {64, 128})
+        if (ne <= 512 * (int64_t)be) return be;
+    return ne <= ((int64_t)1 << 23) ? 256 : 512;
+}
+
 static void build_blocks(int elem, int64_t nn, int64_t ne, const double *X, const int32_t *conn,
                          int be, int bn, bool colour, bool pairs, HostBlocks &hb)
 {
@@ -652,7 +672,9 @@ static void spread_items_chunks(HostBlocks &hb, HostChunks &hc)
 
 // For the block pass: item k runs on lane k / S in column k % S, S = ceil(ni
 // / 64), the 64 lanes of one column together; the slots are the block's node
-// ids.
+// ids.  A hexahedron runs on four lanes, whose four edges spread over the banks
+// by themselves: this order is worth 1% of its FP64 action at 128^3, and one
+// dealt for those lane groups gave no more.
 static void spread_items_blocks(HostBlocks &hb, int elem)
 {
     const int nb = (int)hb.estart.size() - 1;
@@ -803,10 +825,7 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
         set_error("efem_create: reference element with det J <= 0");
         return EFEM_ERR_INVERTED;
     }
-    // defaults measured on the 64^3 workloads: 1536 tets (768 pairs) within 600
-    // nodes, or 512 hexes within 768 nodes, per block; triangles (1024^2 cells):
-    // 768 within 600 nodes
-    int be = elem == EFEM_TET4 ? 1536 : (elem == EFEM_TRI3 ? 768 : 512);
+    int be = default_block_elems(elem, n_elems);
     int bn = elem == EFEM_HEX8 ? 768 : 600;
     int scatter = EFEM_SCATTER_HALO;
     int threads = 256;

@@ -183,7 +183,6 @@ __device__ __forceinline__ void flag_inverted(int32_t *flags) { atomicOr(flags, 
 // Each tetrahedron: N0 = 1 - xi - eta - zeta, N_k = xi_k; one point, w = 1/6.
 struct Tet4Pair {
     static constexpr int NEN = 5, NQ = 2, NSUB = 2;
-    using Lean = Tet4Pair;   // the form with the fewest live registers
     // completes the gradient of a coordinate field (planar elements only)
     template <class T> __device__ static __forceinline__ void geom(T *) {}
     template <class T> __device__ static constexpr T weight() { return T(1.0 / 6.0); }
@@ -304,7 +303,6 @@ struct Tet4Pair {
 // makes Jx = [Jx_2D 0; 0 1] and, with u_z held, F = [F_2D 0; 0 1] (plane strain).
 struct Tri3 {
     static constexpr int NEN = 3, NQ = 1, NSUB = 1;
-    using Lean = Tri3;
     template <class T> __device__ static constexpr T weight() { return T(0.5); }
     __device__ static constexpr int sub(int) { return 0; }
     __device__ static constexpr bool skip(int, bool) { return false; }
@@ -377,105 +375,9 @@ struct Tri3 {
     template <class T> __device__ static __forceinline__ T N(int, int) { return T(1.0 / 3.0); }
 };
 
-// Hex8 in node form: the same element with gradients and forces as sums over
-// the 8 nodes (8 terms per entry).  It keeps 24 values per field live instead
-// of 36, which is what the three-field FP64 tangent action needs to stay out
-// of scratch memory.
-__device__ constexpr int kHexSgn[8][3] = {{-1, -1, -1}, {1, -1, -1}, {1, 1, -1}, {-1, 1, -1},
-                                          {-1, -1, 1},  {1, -1, 1},  {1, 1, 1},  {-1, 1, 1}};
-struct Hex8Nodes {
-    static constexpr int NEN = 8;
-    template <class T> __device__ static __forceinline__ void geom(T *) {}
-    template <class T> __device__ static __forceinline__ T dN(int q, int a, int J)
-    {
-        const T g = T(0.57735026918962576451);
-        const T p0 = (q & 1) ? g : -g, p1 = (q & 2) ? g : -g, p2 = (q & 4) ? g : -g;
-        const T f0 = T(1) + T(kHexSgn[a][0]) * p0;
-        const T f1 = T(1) + T(kHexSgn[a][1]) * p1;
-        const T f2 = T(1) + T(kHexSgn[a][2]) * p2;
-        const T s = T(0.125) * T(kHexSgn[a][J]);
-        return J == 0 ? s * f1 * f2 : (J == 1 ? s * f0 * f2 : s * f0 * f1);
-    }
-    // N_a at Gauss point q
-    template <class T> __device__ static __forceinline__ T N(int q, int a)
-    {
-        const T g = T(0.57735026918962576451);
-        const T p0 = (q & 1) ? g : -g, p1 = (q & 2) ? g : -g, p2 = (q & 4) ? g : -g;
-        return T(0.125) * (T(1) + T(kHexSgn[a][0]) * p0) * (T(1) + T(kHexSgn[a][1]) * p1)
-             * (T(1) + T(kHexSgn[a][2]) * p2);
-    }
-    template <class T> struct Field {
-        T f[NEN][3];
-    };
-    template <class T>
-    __device__ static __forceinline__ void prep(const T f[NEN][3], Field<T> &F)
-    {
-#pragma unroll
-        for (int a = 0; a < NEN; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) F.f[a][i] = f[a][i];
-    }
-    template <class T>
-    __device__ static __forceinline__ void grad(const Field<T> &F, int q, T G[9])
-    {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int J = 0; J < 3; ++J) {
-                T t = T(0);
-#pragma unroll
-                for (int a = 0; a < NEN; ++a) t += F.f[a][i] * dN<T>(q, a, J);
-                G[i * 3 + J] = t;
-            }
-    }
-    template <class T> struct Acc {
-        T f[NEN][3];
-    };
-    template <class T> __device__ static __forceinline__ void zero(Acc<T> &A)
-    {
-#pragma unroll
-        for (int a = 0; a < NEN; ++a) A.f[a][0] = A.f[a][1] = A.f[a][2] = T(0);
-    }
-    template <bool INIT, class T>
-    __device__ static __forceinline__ void add_forces_to(const T Q[9], int q, T out[NEN][3])
-    {
-#pragma unroll
-        for (int a = 0; a < NEN; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                if (INIT && q == 0) out[a][i] = T(0);
-                out[a][i] += Q[i * 3 + 0] * dN<T>(q, a, 0) + Q[i * 3 + 1] * dN<T>(q, a, 1)
-                           + Q[i * 3 + 2] * dN<T>(q, a, 2);
-            }
-    }
-    template <bool INIT, class T>
-    __device__ static __forceinline__ void add_forces(const T Q[9], int q, Acc<T> &A)
-    {
-        add_forces_to<INIT>(Q, q, A.f);
-    }
-    template <class T>
-    __device__ static __forceinline__ void finish(const Acc<T> &A, T out[NEN][3])
-    {
-#pragma unroll
-        for (int a = 0; a < NEN; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) out[a][i] = A.f[a][i];
-    }
-};
-
 // Hex8: trilinear on [-1,1]^3, nodes (0,0,0),(1,0,0),(1,1,0),(0,1,0) then z=1;
-// 2x2x2 Gauss points at +-1/sqrt(3), point q = qx + 2 qy + 4 qz, w = 1.
-//
-// The derivative of a trilinear field along one reference direction depends
-// only on the differences along the four element edges of that direction,
-// interpolated bilinearly in the other two coordinates:
-//   d f / d xi_J (q) = sum_e w_J(e, q) (f[e+] - f[e-]),
-//   w_J(e, q) = (1 + s1_e p1_q)(1 + s2_e p2_q) / 8,
-// with (s1_e, s2_e) the signs of edge e in the two other directions and p_q
-// the point's coordinates.  So the gradient is formed from 12 edge
-// differences per field (36 subtractions per element, shared by the 8
-// points) and 4 terms per entry instead of 8; the nodal forces take the
-// transposed route through 12 edge accumulators.
+// 2x2x2 Gauss points at +-1/sqrt(3), point q = qx + 2 qy + 4 qz, w = 1.  Its
+// passes run an element on four lanes (Hex8Quad).
 __device__ constexpr int kHexS[8][3] = {{-1, -1, -1}, {1, -1, -1}, {1, 1, -1}, {-1, 1, -1},
                                         {-1, -1, 1},  {1, -1, 1},  {1, 1, 1},  {-1, 1, 1}};
 // edges (e-, e+) of each direction J, ordered by the signs of the other two
@@ -485,137 +387,161 @@ __device__ constexpr int kHexEdge[3][4][2] = {{{0, 1}, {3, 2}, {4, 5}, {7, 6}},
                                               {{0, 4}, {1, 5}, {3, 7}, {2, 6}}};
 struct Hex8 {
     static constexpr int NEN = 8, NQ = 8, NSUB = 1;
-    using Lean = Hex8Nodes;   // the form with the fewest live registers
-    template <class T> __device__ static __forceinline__ void geom(T *) {}
-    template <class T> __device__ static constexpr T weight() { return T(1); }
-    __device__ static constexpr int sub(int) { return 0; }
-    __device__ static constexpr bool skip(int, bool) { return false; }
-    static constexpr double kG = 0.57735026918962576451;   // 1/sqrt(3)
     // the two directions other than J
     __device__ static constexpr int oth1(int J) { return J == 0 ? 1 : 0; }
     __device__ static constexpr int oth2(int J) { return J == 2 ? 1 : 2; }
-    // which of the 4 columns of direction J point q uses: its coordinate
-    // signs in the two other directions
-    __device__ static constexpr int col(int J, int q)
-    {
-        return ((q >> oth1(J)) & 1) + 2 * ((q >> oth2(J)) & 1);
-    }
-    // (1 + s p g) for edge sign s and point coordinate sign p, and its eighth
-    __device__ static constexpr double lw(int s_pos, int p_pos)
-    {
-        return 1.0 + ((s_pos == p_pos) ? kG : -kG);
-    }
-    __device__ static constexpr double lw8(int s_pos, int p_pos) { return 0.125 * lw(s_pos, p_pos); }
     // index of the edge of direction J that node a ends
     __device__ static constexpr int edge_of(int J, int a)
     {
         return (kHexS[a][oth1(J)] > 0 ? 1 : 0) + (kHexS[a][oth2(J)] > 0 ? 2 : 0);
     }
-    // The 12 distinct gradient columns of a field: c[J][k] = d f / d xi_J at
-    // the points whose other two coordinates have signs k (4 combinations),
-    // from the 4 edge differences of direction J by one interpolation along
-    // each of the two other directions.
+};
+
+// Hex8 on four lanes.  Lane l of a quad of lanes owns the element's x-edge at
+// (y, z) = (l & 1, l >> 1), its two nodes f0 (x-), f1 (x+), and the two Gauss
+// points (qx, y, z) nearest that edge.  A trilinear field's gradient at the
+// points is a tensor product of one-dimensional steps: along x within the
+// lane, along y and z by exchanges with the lanes l ^ 1 and l ^ 2 (quad
+// permutes of registers).  The forces take the transposed route.
+//
+// Gradients are taken in reference coordinates of the lane's own,
+// xi' = (2 xi, -2 sy eta, -2 sz zeta) with sy, sz the signs of the lane's side:
+// every step is then a difference to the partner lane, with no signs.  The
+// element formulas hold in any reference coordinates when the weight carries
+// the determinant of the change, w' = w sy sz / 8 (both Jacobian determinants
+// change sign with it).
+//
+// Why four lanes: one lane's element holds 36 gradient values of each of three
+// fields and 36 force accumulators, which in FP64 took 256 VGPRs and 252 AGPRs,
+// one wave per SIMD, and 821 of its 3,729 instructions were moves between the
+// two files.  A lane of a quad holds 15 values per field and 142 VGPRs, three
+// waves per SIMD, and a small mesh fills four times the lanes.  The exchanges
+// cost 144 register moves per lane (FP32: folded into the subtractions).
+// Bound by vector issue.  One lane against four, FP64 tangent action: 96^3
+// 162 and 101 us, 128^3 342 and 231, 12^3 21 and 8; FP32 79 and 72, 144 and
+// 152 (both at the issue limit there; the smaller blocks stage more), 17 and 7;
+// 96^3 residual 122 and 81, energy 90 and 60, material gradient 84 and 56.
+struct Hex8Quad {
+    static constexpr double kWm = 0.5 * (1.0 - 0.57735026918962576451);   // weight of the far side
+    static constexpr double kWp = 0.5 * (1.0 + 0.57735026918962576451);
+    // the x-difference at the two points is sqrt(3) times that of the x-interpolated
+    // values, so it needs no exchange of its own: wm sqrt(3)
+    static constexpr double kKx = 0.5 * (1.7320508075688772935 - 1.0);
+    // the value of lane l ^ M (M = 1 or 2); mov_dpp, whose result has no
+    // earlier value to keep (update_dpp clears its register first: 192 moves)
+    template <int M> __device__ static __forceinline__ int peer_bits(int v)
+    {
+        return __builtin_amdgcn_mov_dpp(v, M == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);   // quad_perm [1,0,3,2], [2,3,0,1]
+    }
+    template <int M> __device__ static __forceinline__ float peer(float v)
+    {
+        return __int_as_float(peer_bits<M>(__float_as_int(v)));
+    }
+    template <int M> __device__ static __forceinline__ double peer(double v)
+    {
+        return __hiloint2double(peer_bits<M>(__double2hiint(v)), peer_bits<M>(__double2loint(v)));
+    }
+    // sign of det(d xi / d xi') times 1/8: the weight of a point
+    template <class T> __device__ static __forceinline__ T weight(int l)
+    {
+        return (l == 0 || l == 3) ? T(0.125) : T(-0.125);
+    }
+    // gradient columns of a field at the lane's points: gx (both), gy[qx], gz[qx]
     template <class T> struct Field {
-        T c[3][4][3];   // [direction][column][component]
+        T gx[3], gy[2][3], gz[2][3];
     };
+    // VAL: the field's values at the points as well
+    template <bool VAL = false, class T>
+    __device__ static __forceinline__ void prep(const T f0[3], const T f1[3], Field<T> &F, T (*val)[3] = nullptr)
+    {
+        constexpr T wm = T(kWm), wp = T(kWp), kx = T(kKx);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const T d = f1[i] - f0[i];
+            const T u0 = fma(wm, d, f0[i]), u1 = fma(wp, d, f0[i]);
+            const T e0 = peer<1>(u0) - u0, e1 = peer<1>(u1) - u1;
+            const T dy = fma(kx, e1 - e0, d), v0 = fma(wm, e0, u0), v1 = fma(wm, e1, u1);
+            const T h0 = peer<2>(v0) - v0, h1 = peer<2>(v1) - v1;
+            F.gx[i] = fma(kx, h1 - h0, dy);
+            F.gy[0][i] = fma(wm, peer<2>(e0) - e0, e0);
+            F.gy[1][i] = fma(wm, peer<2>(e1) - e1, e1);
+            F.gz[0][i] = h0;
+            F.gz[1][i] = h1;
+            if constexpr (VAL) {
+                val[0][i] = fma(wm, h0, v0);
+                val[1][i] = fma(wm, h1, v1);
+            }
+        }
+    }
+    template <class T> __device__ static __forceinline__ void grad(const Field<T> &F, int qx, T G[9])
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            G[i * 3 + 0] = F.gx[i];
+            G[i * 3 + 1] = F.gy[qx][i];
+            G[i * 3 + 2] = F.gz[qx][i];
+        }
+    }
+    // nodal forces of the lane's two nodes from the two points' Q
     template <class T>
-    __device__ static __forceinline__ void prep(const T f[NEN][3], Field<T> &F)
+    __device__ static __forceinline__ void forces(const T Q0[9], const T Q1[9], T f0[3], T f1[3])
     {
+        constexpr T wm = T(kWm), wp = T(kWp), kx = T(kKx);
 #pragma unroll
-        for (int J = 0; J < 3; ++J)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                T d[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) d[e] = f[kHexEdge[J][e][1]][i] - f[kHexEdge[J][e][0]][i];
-                // along the first other direction: A[p1][lev], lev = edge sign in the second
-                T A[2][2];
-#pragma unroll
-                for (int p1 = 0; p1 < 2; ++p1)
-#pragma unroll
-                    for (int lev = 0; lev < 2; ++lev)
-                        A[p1][lev] = fma(T(lw(1, p1)), d[1 + 2 * lev], T(lw(0, p1)) * d[2 * lev]);
-#pragma unroll
-                for (int p1 = 0; p1 < 2; ++p1)
-#pragma unroll
-                    for (int p2 = 0; p2 < 2; ++p2)
-                        F.c[J][p1 + 2 * p2][i] = fma(T(lw8(1, p2)), A[p1][1], T(lw8(0, p2)) * A[p1][0]);
-            }
+        for (int i = 0; i < 3; ++i) {
+            const T g = Q0[i * 3] + Q1[i * 3], kg = kx * g;
+            const T h0 = Q0[i * 3 + 2] - kg, h1 = Q1[i * 3 + 2] + kg;
+            const T v0 = peer<2>(h0) - h0, v1 = peer<2>(h1) - h1;
+            const T e0 = fma(wm, peer<2>(Q0[i * 3 + 1]), fma(wp, Q0[i * 3 + 1], -kg));
+            const T e1 = fma(wm, peer<2>(Q1[i * 3 + 1]), fma(wp, Q1[i * 3 + 1], kg));
+            const T u0 = fma(wp, v0, peer<1>(fma(wm, v0, e0)) - e0);
+            const T u1 = fma(wp, v1, peer<1>(fma(wm, v1, e1)) - e1);
+            const T t = fma(wm, u0, fma(wp, u1, g));
+            f1[i] = t;
+            f0[i] = (u0 + u1) - t;
+        }
     }
+    // the transpose of VAL: g0, g1 at the points times N_a onto the lane's nodes
     template <class T>
-    __device__ static __forceinline__ void grad(const Field<T> &F, int q, T G[9])
+    __device__ static __forceinline__ void add_values(const T g0[3], const T g1[3], T f0[3], T f1[3])
     {
+        constexpr T wm = T(kWm), wp = T(kWp);
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int J = 0; J < 3; ++J) G[i * 3 + J] = F.c[J][col(J, q)][i];
+        for (int i = 0; i < 3; ++i) {
+            const T v0 = fma(wm, peer<2>(g0[i]), wp * g0[i]), v1 = fma(wm, peer<2>(g1[i]), wp * g1[i]);
+            const T u0 = fma(wm, peer<1>(v0), wp * v0), u1 = fma(wm, peer<1>(v1), wp * v1);
+            f0[i] += fma(wm, u1, wp * u0);
+            f1[i] += fma(wm, u0, wp * u1);
+        }
     }
-    // forces: the transposed route, columns -> edges -> nodes
-    template <class T> struct Acc {
-        T c[3][4][3];
-    };
-    template <class T> __device__ static __forceinline__ void zero(Acc<T> &A)
+    // shape function of node (ix, jy, jz) at the lane's point qx, with jy, jz =
+    // 1 on the far side: one factor, and the derivatives in the lane's coordinates
+    __device__ static constexpr double n1(int near) { return near ? kWp : kWm; }
+    __device__ static constexpr double N(int q, int ix, int jy, int jz) { return n1(ix == q) * n1(!jy) * n1(!jz); }
+    __device__ static constexpr double dN(int q, int ix, int jy, int jz, int J)
     {
-#pragma unroll
-        for (int J = 0; J < 3; ++J)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) A.c[J][k][0] = A.c[J][k][1] = A.c[J][k][2] = T(0);
+        return J == 0   ? (ix ? 1.0 : -1.0) * n1(!jy) * n1(!jz)
+               : J == 1 ? n1(ix == q) * (jy ? 1.0 : -1.0) * n1(!jz)
+                        : n1(ix == q) * n1(!jy) * (jz ? 1.0 : -1.0);
     }
-    // INIT: points arrive in ascending order from an uninitialised accumulator,
-    // so a column is assigned at its first point (coordinate J negative)
-    template <bool INIT, class T>
-    __device__ static __forceinline__ void add_forces(const T Q[9], int q, Acc<T> &A)
+    // sums d[ix][jy][jz] that the four lanes hold for the element's nodes, to
+    // the lanes that own them
+    __device__ static __forceinline__ void collect(const double d[2][2][2][3], double f0[3], double f1[3])
     {
 #pragma unroll
-        for (int J = 0; J < 3; ++J)
+        for (int ix = 0; ix < 2; ++ix)
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                T &a = A.c[J][col(J, q)][i];
-                if (INIT && !((q >> J) & 1)) a = Q[i * 3 + J];
-                else a += Q[i * 3 + J];
+                const double e0 = d[ix][0][0][i] + peer<1>(d[ix][1][0][i]);
+                const double e1 = d[ix][0][1][i] + peer<1>(d[ix][1][1][i]);
+                (ix ? f1 : f0)[i] = e0 + peer<2>(e1);
             }
     }
-    template <class T>
-    __device__ static __forceinline__ void finish(const Acc<T> &A, T out[NEN][3])
+    // sum over the four lanes
+    template <class T> __device__ static __forceinline__ T sum(T v)
     {
-        T E[3][4][3];   // edge forces: +E to the edge's + end, -E to its - end
-#pragma unroll
-        for (int J = 0; J < 3; ++J)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                T B[2][2];   // [p1][lev]
-#pragma unroll
-                for (int p1 = 0; p1 < 2; ++p1)
-#pragma unroll
-                    for (int lev = 0; lev < 2; ++lev)
-                        B[p1][lev] = fma(T(lw8(lev, 1)), A.c[J][p1 + 2][i], T(lw8(lev, 0)) * A.c[J][p1][i]);
-#pragma unroll
-                for (int s1 = 0; s1 < 2; ++s1)
-#pragma unroll
-                    for (int lev = 0; lev < 2; ++lev)
-                        E[J][s1 + 2 * lev][i] = fma(T(lw(s1, 1)), B[1][lev], T(lw(s1, 0)) * B[0][lev]);
-            }
-        // every node ends exactly one edge of each direction: its + end where
-        // its sign in that direction is +, else its - end
-#pragma unroll
-        for (int a = 0; a < NEN; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int e0 = edge_of(0, a), e1 = edge_of(1, a), e2 = edge_of(2, a);
-                const T t0 = kHexS[a][0] > 0 ? E[0][e0][i] : -E[0][e0][i];
-                const T t1 = kHexS[a][1] > 0 ? t0 + E[1][e1][i] : t0 - E[1][e1][i];
-                out[a][i] = kHexS[a][2] > 0 ? t1 + E[2][e2][i] : t1 - E[2][e2][i];
-            }
-    }
-    template <class T> __device__ static __forceinline__ T dN(int q, int a, int J)
-    {
-        const T g = T(kG);
-        const T p0 = (q & 1) ? g : -g, p1 = (q & 2) ? g : -g, p2 = (q & 4) ? g : -g;
-        const T f0 = T(1) + T(kHexS[a][0]) * p0;
-        const T f1 = T(1) + T(kHexS[a][1]) * p1;
-        const T f2 = T(1) + T(kHexS[a][2]) * p2;
-        const T s = T(0.125) * T(kHexS[a][J]);
-        return J == 0 ? s * f1 * f2 : (J == 1 ? s * f0 * f2 : s * f0 * f1);
+        v += peer<1>(v);
+        return v + peer<2>(v);
     }
 };
 
@@ -628,11 +554,10 @@ struct Hex8 {
 // W20, W21 (the last row of Ad against the face's two edges of v).
 // ROW2 = 1: those go out to r2x = {Ae row 2, S22}, r2d = {Ad row 2, W20,
 // W21}; ROW2 = 2: they are taken from there, signs and columns swapped.
-// FOLD: the scalars a, b, c enter the matrix products (S scaled by a, W
-// replaced by c W + b I; 12 fewer operations, but each entry of Q becomes
-// one six-term chain).  The Hex8 kernels, at 1 or 2 waves per SIMD, keep
-// the separate terms: there the longer chains cost more than they save.
-template <class T, int ROW2 = 0, bool FOLD = true>
+// The scalars a, b, c enter the matrix products (S scaled by a, W replaced by
+// c W + b I): 12 operations fewer than separate terms.
+// SIGNED: w carries the sign of det Jx (and of det Jd where it is positive).
+template <class T, int ROW2 = 0, bool SIGNED = false>
 __device__ __forceinline__ bool qp_hvp(T w, const T Jx[9], const T Jd[9], const T dJ[9], T mu,
                                        T lam, T Q[9], T *r2x = nullptr, T *r2d = nullptr)
 {
@@ -655,18 +580,17 @@ __device__ __forceinline__ bool qp_hvp(T w, const T Jx[9], const T Jd[9], const 
     const T s2 = w * De * rDd * rDd;
     const T lnJ = log_(Dd * rDe);
     const T c1 = mu - lam * lnJ;
-    // S = Ae Ae^T (symmetric), times a when FOLD
+    // S = a Ae Ae^T (symmetric)
     T S22;
     if constexpr (ROW2 == 2) S22 = r2x[3];
     else S22 = Ae[6] * Ae[6] + Ae[7] * Ae[7] + Ae[8] * Ae[8];
     if constexpr (ROW2 == 1) r2x[3] = S22;
-    const T sa = FOLD ? a : T(1);
-    const T S00 = sa * (Ae[0] * Ae[0] + Ae[1] * Ae[1] + Ae[2] * Ae[2]);
-    const T S01 = sa * (Ae[0] * Ae[3] + Ae[1] * Ae[4] + Ae[2] * Ae[5]);
-    const T S02 = sa * (Ae[0] * Ae[6] + Ae[1] * Ae[7] + Ae[2] * Ae[8]);
-    const T S11 = sa * (Ae[3] * Ae[3] + Ae[4] * Ae[4] + Ae[5] * Ae[5]);
-    const T S12 = sa * (Ae[3] * Ae[6] + Ae[4] * Ae[7] + Ae[5] * Ae[8]);
-    S22 = sa * S22;
+    const T S00 = a * (Ae[0] * Ae[0] + Ae[1] * Ae[1] + Ae[2] * Ae[2]);
+    const T S01 = a * (Ae[0] * Ae[3] + Ae[1] * Ae[4] + Ae[2] * Ae[5]);
+    const T S02 = a * (Ae[0] * Ae[6] + Ae[1] * Ae[7] + Ae[2] * Ae[8]);
+    const T S11 = a * (Ae[3] * Ae[3] + Ae[4] * Ae[4] + Ae[5] * Ae[5]);
+    const T S12 = a * (Ae[3] * Ae[6] + Ae[4] * Ae[7] + Ae[5] * Ae[8]);
+    S22 = a * S22;
     const T S[9] = {S00, S01, S02, S01, S11, S12, S02, S12, S22};
     // W = Ad dJ
     T W[9];
@@ -689,39 +613,23 @@ __device__ __forceinline__ bool qp_hvp(T w, const T Jx[9], const T Jd[9], const 
     const T tr = W[0] + W[4] + W[8];
     const T b = lam * tr * s2;
     const T c = c1 * s2;
-    if constexpr (FOLD) {
-        // V = c W + b I: the two Ad^T terms of dP become one product
-        T V[9];
+    // V = c W + b I: the two Ad^T terms of dP become one product
+    T V[9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) V[k] = (k % 4 == 0) ? fma(c, W[k], b) : c * W[k];
-        // Q[i][J] = (dJ S)[i][J] + (V Ad)[J][i]
+    for (int k = 0; k < 9; ++k) V[k] = (k % 4 == 0) ? fma(c, W[k], b) : c * W[k];
+    // Q[i][J] = (dJ S)[i][J] + (V Ad)[J][i]
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int J = 0; J < 3; ++J)
-                Q[i * 3 + J] = dJ[i * 3 + 0] * S[0 * 3 + J] + dJ[i * 3 + 1] * S[1 * 3 + J]
-                             + dJ[i * 3 + 2] * S[2 * 3 + J] + V[J * 3 + 0] * Ad[0 * 3 + i]
-                             + V[J * 3 + 1] * Ad[1 * 3 + i] + V[J * 3 + 2] * Ad[2 * 3 + i];
-    } else {
-        // Q[i][J] = a (dJ S)[i][J] + b Ad[J][i] + c (W Ad)[J][i]
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const T d0 = dJ[i * 3 + 0], d1 = dJ[i * 3 + 1], d2 = dJ[i * 3 + 2];
-            const T dS[3] = {d0 * S[0] + d1 * S[3] + d2 * S[6], d0 * S[1] + d1 * S[4] + d2 * S[7],
-                             d0 * S[2] + d1 * S[5] + d2 * S[8]};
-#pragma unroll
-            for (int J = 0; J < 3; ++J) {
-                const T Mji = W[J * 3 + 0] * Ad[0 * 3 + i] + W[J * 3 + 1] * Ad[1 * 3 + i]
-                            + W[J * 3 + 2] * Ad[2 * 3 + i];
-                Q[i * 3 + J] = a * dS[J] + b * Ad[J * 3 + i] + c * Mji;
-            }
-        }
-    }
-    return Dd > T(0);
+        for (int J = 0; J < 3; ++J)
+            Q[i * 3 + J] = dJ[i * 3 + 0] * S[0 * 3 + J] + dJ[i * 3 + 1] * S[1 * 3 + J]
+                         + dJ[i * 3 + 2] * S[2 * 3 + J] + V[J * 3 + 0] * Ad[0 * 3 + i]
+                         + V[J * 3 + 1] * Ad[1 * 3 + i] + V[J * 3 + 2] * Ad[2 * 3 + i];
+    return (SIGNED ? w * Dd : Dd) > T(0);
 }
 
 // Residual at one point: Q = w det Jx P Jx^-T = w [mu/De Jd S + (lam lnJ - mu) De/Dd Ad^T].
-template <class T>
+template <bool SIGNED = false, class T>
 __device__ __forceinline__ bool qp_residual(T w, const T Jx[9], const T Jd[9], T mu, T lam, T Q[9])
 {
     T Ae[9], Ad[9];
@@ -745,7 +653,7 @@ __device__ __forceinline__ bool qp_residual(T w, const T Jx[9], const T Jd[9], T
             Q[i * 3 + J] = a * (Jd[i * 3 + 0] * S[0 * 3 + J] + Jd[i * 3 + 1] * S[1 * 3 + J]
                                 + Jd[i * 3 + 2] * S[2 * 3 + J])
                          + c * Ad[J * 3 + i];
-    return Dd > T(0);
+    return (SIGNED ? w * Dd : Dd) > T(0);
 }
 
 // ---- small-strain linear elasticity (the second material model)
@@ -955,37 +863,34 @@ template <> struct HvpOp<double> {
         }
         return compute<E>(Xe, xe, ve, mu, lam, pair, f);
     }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, double mu, double lam, double f0[3],
+                                         double f1[3]) const
+    {
+        Hex8Quad::Field<double> FX, Fx, Fv;
+        Hex8Quad::prep(n0.X, n1.X, FX);
+        Hex8Quad::prep(n0.x, n1.x, Fx);
+        Hex8Quad::prep(n0.v, n1.v, Fv);
+        const double w = Hex8Quad::weight<double>(l);
+        double Q[2][9];
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            double Jx[9], Jd[9], dJ[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Hex8Quad::grad(Fx, q, Jd);
+            Hex8Quad::grad(Fv, q, dJ);
+            ok &= qp_hvp<double, 0, true>(w, Jx, Jd, dJ, mu, lam, Q[q]);
+        }
+        Hex8Quad::forces(Q[0], Q[1], f0, f1);
+        return ok;
+    }
     // the element's forces from its nodal X, x and v
     template <class E>
     __device__ static __forceinline__ bool compute(const double Xe[E::NEN][3], const double xe[E::NEN][3],
                                                    const double ve[E::NEN][3], const double *mu,
                                                    const double *lam, bool pair, double f[E::NEN][3])
     {
-        if constexpr (std::is_same<E, Hex8>::value) {
-            // Hex8 in the column form (gradients from edge differences,
-            // forces back through the columns): half the operations of the
-            // node form; at one wave per SIMD the accumulation registers
-            // hold it
-            typename E::template Field<double> FX, Fx, Fv;
-            E::prep(Xe, FX);
-            E::prep(xe, Fx);
-            E::prep(ve, Fv);
-            typename E::template Acc<double> A;
-            bool ok = true;
-#pragma unroll
-            for (int q = 0; q < E::NQ; ++q) {
-                double Jx[9], Jd[9], dJ[9], Q[9];
-                E::grad(FX, q, Jx);
-                E::grad(Fx, q, Jd);
-                E::grad(Fv, q, dJ);
-                ok &= qp_hvp<double, 0, false>(E::template weight<double>(), Jx, Jd, dJ, mu[0], lam[0], Q);
-                E::template add_forces<true>(Q, q, A);
-            }
-            E::finish(A, f);
-            return ok;
-        }
-        // three fields: the register-lean form (node sums for Hex8)
-        using G = typename E::Lean;
+        using G = E;
         typename G::template Field<double> FX, Fx, Fv;
         G::prep(Xe, FX);
         G::prep(xe, Fx);
@@ -1081,14 +986,36 @@ template <> struct HvpOp<float> {
                 else
                     ok &= qp_hvp<float, 2>(E::template weight<float>(), Jx, Jd, dJ, mu[1], lam[1], Q, r2x, r2d);
             } else {
-                ok &= qp_hvp<float, 0, !std::is_same<E, Hex8>::value>(E::template weight<float>(), Jx, Jd, dJ,
-                                                                      mu[E::sub(q)], lam[E::sub(q)], Q);
+                ok &= qp_hvp<float>(E::template weight<float>(), Jx, Jd, dJ, mu[E::sub(q)], lam[E::sub(q)], Q);
             }
             if constexpr (std::is_same<E, Tet4Pair>::value) E::add_forces_open(Q, q, A.f);
             else E::template add_forces<true>(Q, q, A);
         }
         if constexpr (std::is_same<E, Tet4Pair>::value) E::close0(A.f);
         E::finish(A, f);
+        return ok;
+    }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, float mu, float lam, float f0[3],
+                                         float f1[3]) const
+    {
+        Hex8Quad::Field<float> FX, Fu, Fv;
+        Hex8Quad::prep(n0.X, n1.X, FX);
+        Hex8Quad::prep(n0.u, n1.u, Fu);
+        Hex8Quad::prep(n0.v, n1.v, Fv);
+        const float w = Hex8Quad::weight<float>(l);
+        float Q[2][9];
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            float Jx[9], Jd[9], dJ[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Hex8Quad::grad(Fu, q, Jd);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) Jd[k] += Jx[k];
+            Hex8Quad::grad(Fv, q, dJ);
+            ok &= qp_hvp<float, 0, true>(w, Jx, Jd, dJ, mu, lam, Q[q]);
+        }
+        Hex8Quad::forces(Q[0], Q[1], f0, f1);
         return ok;
     }
 };
@@ -1132,39 +1059,76 @@ struct XUWStage {
     }
 };
 
-struct ResidualOp : XUStage {
-    using Node = NodeXU;
+// X and a direction v: the linear and transport tangents do not depend on u.
+template <class T> struct alignas(16) NodeXV {
+    T X[3], v[3];
+};
+// the second field of a two-field record
+__device__ __forceinline__ const double *field2(const NodeXU &n) { return n.u; }
+template <class T> __device__ __forceinline__ const T *field2(const NodeXV<T> &n) { return n.v; }
+
+// Element form of the operations whose forces come from X and one more field:
+// Op::point(w, Jx, G, mu, lam, Q), G the second field's reference gradient,
+// gives the point's Q (SIGNED as in qp_hvp) and whether det F > 0.
+template <class Op, class Rec, class T> struct ForceForm {
+    using Node = Rec;
     template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const T *mu, const T *lam, bool pair,
+                                            T f[E::NEN][3]) const
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        typename E::template Acc<double> A;
+        T Xe[E::NEN][3], ge[E::NEN][3];
+#pragma unroll
+        for (int a = 0; a < E::NEN; ++a)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                Xe[a][i] = sn[lc[a]].X[i];
+                ge[a][i] = field2(sn[lc[a]])[i];
+            }
+        typename E::template Field<T> FX, Fg;
+        E::prep(Xe, FX);
+        E::prep(ge, Fg);
+        typename E::template Acc<T> A;
         bool ok = true;
 #pragma unroll
         for (int q = 0; q < E::NQ; ++q) {
             if (E::skip(q, pair)) continue;
-            double Jx[9], Jd[9], Q[9];
+            T Jx[9], G[9], Q[9];
             E::grad(FX, q, Jx);
             E::geom(Jx);
-            E::grad(Fu, q, Jd);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Jd[k] += Jx[k];
-            ok &= qp_residual(E::template weight<double>(), Jx, Jd, mu[E::sub(q)], lam[E::sub(q)], Q);
+            E::grad(Fg, q, G);
+            ok &= Op::template point<false>(E::template weight<T>(), Jx, G, mu[E::sub(q)], lam[E::sub(q)], Q);
             E::template add_forces<true>(Q, q, A);
         }
         E::finish(A, f);
         return ok;
     }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, T mu, T lam, T f0[3], T f1[3]) const
+    {
+        Hex8Quad::Field<T> FX, Fg;
+        Hex8Quad::prep(n0.X, n1.X, FX);
+        Hex8Quad::prep(field2(n0), field2(n1), Fg);
+        T Q[2][9];
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            T Jx[9], G[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Hex8Quad::grad(Fg, q, G);
+            ok &= Op::template point<true>(Hex8Quad::weight<T>(l), Jx, G, mu, lam, Q[q]);
+        }
+        Hex8Quad::forces(Q[0], Q[1], f0, f1);
+        return ok;
+    }
 };
 
-// diag K: w [ mu/De n^T S n + (lam + c1) De/Dd^2 ((Ad^T n)_i)^2 ], n = dN_a/dxi
-struct DiagOp : XUStage {
+// Element form of the nodal sums over X and u that are not forces (the
+// diagonal blocks): Op::Coef set by point(), and node(c, n, f) adds the
+// contribution of a node with reference derivatives n.
+template <class Op> struct NodeForm : XUStage {
     using Node = NodeXU;
     template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu, const double *lam,
+                                            bool pair, double f[E::NEN][3]) const
     {
         typename E::template Field<double> FX, Fu;
         gather_xu<E>(sn, lc, FX, Fu);
@@ -1174,38 +1138,99 @@ struct DiagOp : XUStage {
 #pragma unroll
         for (int q = 0; q < E::NQ; ++q) {
             if (E::skip(q, pair)) continue;
-            const double mq = mu[E::sub(q)], lq = lam[E::sub(q)];
-            double Jx[9], Jd[9], Ae[9], Ad[9];
+            double Jx[9], G[9];
             E::grad(FX, q, Jx);
             E::geom(Jx);
-            E::grad(Fu, q, Jd);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Jd[k] += Jx[k];
-            const double De = adj_det(Jx, Ae);
-            const double Dd = adj_det(Jd, Ad);
-            ok &= Dd > 0.0;
-            const double w = E::template weight<double>();
-            const double lnJ = log_(Dd / De);
-            const double a = w * mq / De;
-            const double b = w * (lq + mq - lq * lnJ) * De / (Dd * Dd);
+            E::grad(Fu, q, G);
+            typename Op::Coef c;
+            ok &= Op::template point<false>(E::template weight<double>(), Jx, G, mu[E::sub(q)], lam[E::sub(q)], c);
 #pragma unroll
             for (int n = 0; n < E::NEN; ++n) {
-                const double g0 = E::template dN<double>(q, n, 0);
-                const double g1 = E::template dN<double>(q, n, 1);
-                const double g2 = E::template dN<double>(q, n, 2);
-                // Ae^T n, |.|^2 = n^T S n
-                const double t0 = Ae[0] * g0 + Ae[3] * g1 + Ae[6] * g2;
-                const double t1 = Ae[1] * g0 + Ae[4] * g1 + Ae[7] * g2;
-                const double t2 = Ae[2] * g0 + Ae[5] * g1 + Ae[8] * g2;
-                const double nSn = t0 * t0 + t1 * t1 + t2 * t2;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const double k = Ad[0 * 3 + i] * g0 + Ad[1 * 3 + i] * g1 + Ad[2 * 3 + i] * g2;
-                    f[n][i] += a * nSn + b * k * k;
-                }
+                const double d[3] = {E::template dN<double>(q, n, 0), E::template dN<double>(q, n, 1),
+                                     E::template dN<double>(q, n, 2)};
+                Op::node(c, d, f[n]);
             }
         }
         return ok;
+    }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, double mu, double lam, double f0[3],
+                                         double f1[3]) const
+    {
+        Hex8Quad::Field<double> FX, Fu;
+        Hex8Quad::prep(n0.X, n1.X, FX);
+        Hex8Quad::prep(n0.u, n1.u, Fu);
+        double d[2][2][2][3] = {};
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            double Jx[9], G[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Hex8Quad::grad(Fu, q, G);
+            typename Op::Coef c;
+            ok &= Op::template point<true>(Hex8Quad::weight<double>(l), Jx, G, mu, lam, c);
+#pragma unroll
+            for (int ix = 0; ix < 2; ++ix)
+#pragma unroll
+                for (int jy = 0; jy < 2; ++jy)
+#pragma unroll
+                    for (int jz = 0; jz < 2; ++jz) {
+                        const double n[3] = {Hex8Quad::dN(q, ix, jy, jz, 0), Hex8Quad::dN(q, ix, jy, jz, 1),
+                                             Hex8Quad::dN(q, ix, jy, jz, 2)};
+                        Op::node(c, n, d[ix][jy][jz]);
+                    }
+        }
+        Hex8Quad::collect(d, f0, f1);
+        return ok;
+    }
+};
+
+struct ResidualOp : XUStage, ForceForm<ResidualOp, NodeXU, double> {
+    using Node = NodeXU;
+    template <bool SIGNED>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double G[9], double mu, double lam,
+                                                 double Q[9])
+    {
+        double Jd[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Jd[k] = G[k] + Jx[k];
+        return qp_residual<SIGNED>(w, Jx, Jd, mu, lam, Q);
+    }
+};
+
+// M^T n of a reference-derivative triple
+__device__ __forceinline__ void transposed(const double M[9], const double n[3], double t[3])
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i) t[i] = M[i] * n[0] + M[3 + i] * n[1] + M[6 + i] * n[2];
+}
+
+// diag K: w [ mu/De n^T S n + (lam + c1) De/Dd^2 ((Ad^T n)_i)^2 ], n = dN_a/dxi
+struct DiagOp : NodeForm<DiagOp> {
+    struct Coef {
+        double a, b, Ae[9], Ad[9];
+    };
+    template <bool SIGNED>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double G[9], double mu, double lam,
+                                                 Coef &c)
+    {
+        double Jd[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Jd[k] = G[k] + Jx[k];
+        const double De = adj_det(Jx, c.Ae);
+        const double Dd = adj_det(Jd, c.Ad);
+        const double lnJ = log_(Dd / De);
+        c.a = w * mu / De;
+        c.b = w * (lam + mu - lam * lnJ) * De / (Dd * Dd);
+        return (SIGNED ? w * Dd : Dd) > 0.0;
+    }
+    __device__ static __forceinline__ void node(const Coef &c, const double n[3], double f[3])
+    {
+        double t[3], k[3];
+        transposed(c.Ae, n, t);   // |.|^2 = n^T S n
+        transposed(c.Ad, n, k);
+        const double nSn = t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) f[i] += c.a * nSn + c.b * k[i] * k[i];
     }
 };
 
@@ -1214,131 +1239,91 @@ struct DiagOp : XUStage {
 // Ad^T grad_xi N_n (DiagOp keeps the diagonal of it), so its off-diagonal
 // entries are b k_i k_j; out [n][3] = (K01, K02, K12).  The linear model's
 // block is (w / De) (mu (t.t) I + (mu + lam) t t^T), t = Ae^T grad_xi N_n.
-template <bool LIN>
-struct OffDiagOp : XUStage {
-    using Node = NodeXU;
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+template <bool LIN> struct OffDiagOp : NodeForm<OffDiagOp<LIN>> {
+    struct Coef {
+        double b, A[9];
+    };
+    template <bool SIGNED>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double G[9], double mu, double lam,
+                                                 Coef &c)
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-#pragma unroll
-        for (int a = 0; a < E::NEN; ++a) f[a][0] = f[a][1] = f[a][2] = 0.0;
-        bool ok = true;
-#pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            const double mq = mu[E::sub(q)], lq = lam[E::sub(q)];
-            double Jx[9], A[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            double b;
-            if (LIN) {
-                const double De = adj_det(Jx, A);
-                b = E::template weight<double>() * (mq + lq) / De;
-            } else {
-                double Jd[9], Ae[9];
-                E::grad(Fu, q, Jd);
-#pragma unroll
-                for (int k = 0; k < 9; ++k) Jd[k] += Jx[k];
-                const double De = adj_det(Jx, Ae);
-                const double Dd = adj_det(Jd, A);
-                ok &= Dd > 0.0;
-                const double lnJ = log_(Dd / De);
-                b = E::template weight<double>() * (lq + mq - lq * lnJ) * De / (Dd * Dd);
-            }
-#pragma unroll
-            for (int n = 0; n < E::NEN; ++n) {
-                const double g0 = E::template dN<double>(q, n, 0);
-                const double g1 = E::template dN<double>(q, n, 1);
-                const double g2 = E::template dN<double>(q, n, 2);
-                double k[3];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) k[i] = A[0 * 3 + i] * g0 + A[1 * 3 + i] * g1 + A[2 * 3 + i] * g2;
-                f[n][0] += b * k[0] * k[1];
-                f[n][1] += b * k[0] * k[2];
-                f[n][2] += b * k[1] * k[2];
-            }
+        if (LIN) {
+            const double De = adj_det(Jx, c.A);
+            c.b = w * (mu + lam) / De;
+            return true;
         }
-        return ok;
+        double Jd[9], Ae[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Jd[k] = G[k] + Jx[k];
+        const double De = adj_det(Jx, Ae);
+        const double Dd = adj_det(Jd, c.A);
+        const double lnJ = log_(Dd / De);
+        c.b = w * (lam + mu - lam * lnJ) * De / (Dd * Dd);
+        return (SIGNED ? w * Dd : Dd) > 0.0;
+    }
+    __device__ static __forceinline__ void node(const Coef &c, const double n[3], double f[3])
+    {
+        double k[3];
+        transposed(c.A, n, k);
+        f[0] += c.b * k[0] * k[1];
+        f[1] += c.b * k[0] * k[2];
+        f[2] += c.b * k[1] * k[2];
     }
 };
 
-// dPsi/dX at fixed nodal u: Q = w det Jx (psi I - H^T P) Jx^-T
-struct GradCoordsOp : XUStage {
+// dPsi/dX at fixed nodal u: Q = w det Jx (psi I - H^T P) Jx^-T (0 where det F <= 0)
+struct GradCoordsOp : XUStage, ForceForm<GradCoordsOp, NodeXU, double> {
     using Node = NodeXU;
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+    template <bool>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double Hxi[9], double mu, double lam,
+                                                 double Q[9])
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        typename E::template Acc<double> A;
-        E::zero(A);   // a point may be skipped (inverted), so no point initialises
-        bool ok = true;
+        Kin k;
+        kinematics(w, Jx, Hxi, k);
+        if (!(1.0 + k.Jm1 > 0.0)) {
 #pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            const double mu_ = mu[E::sub(q)], lam_ = lam[E::sub(q)];
-            double Jx[9], Hxi[9], Ae[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            Kin k;
-            kinematics(E::template weight<double>(), Jx, Hxi, k);
-            if (!(1.0 + k.Jm1 > 0.0)) {
-                ok = false;
-                continue;
-            }
-            const double lnJ = log1p_(k.Jm1);
-            const double psi = 0.5 * mu_ * k.I1m3 - mu_ * lnJ + 0.5 * lam_ * lnJ * lnJ;
-            double F[9], Fa[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) F[i] = k.H[i] + ((i % 4) == 0 ? 1.0 : 0.0);
-            const double detF = adj_det(F, Fa);   // F^-1 = Fa / detF
-            const double rdF = 1.0 / detF;
-            double P[9], Sg[9];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int J = 0; J < 3; ++J) {
-                    const double FiT = Fa[J * 3 + i] * rdF;   // F^-T_iJ
-                    P[i * 3 + J] = mu_ * (F[i * 3 + J] - FiT) + lam_ * lnJ * FiT;
-                }
-#pragma unroll
-            for (int mm = 0; mm < 3; ++mm)
-#pragma unroll
-                for (int L = 0; L < 3; ++L)
-                    Sg[mm * 3 + L] = (mm == L ? psi : 0.0) - (k.H[0 * 3 + mm] * P[0 * 3 + L]
-                                     + k.H[1 * 3 + mm] * P[1 * 3 + L] + k.H[2 * 3 + mm] * P[2 * 3 + L]);
-            // Q = w det Jx Sg Jx^-T = w Sg Ae^T
-            adj_det(Jx, Ae);
-            const double w = E::template weight<double>();
-            double Q[9];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int J = 0; J < 3; ++J)
-                    Q[i * 3 + J] = w * (Sg[i * 3 + 0] * Ae[J * 3 + 0] + Sg[i * 3 + 1] * Ae[J * 3 + 1]
-                                        + Sg[i * 3 + 2] * Ae[J * 3 + 2]);
-            E::template add_forces<false>(Q, q, A);
+            for (int i = 0; i < 9; ++i) Q[i] = 0.0;
+            return false;
         }
-        E::finish(A, f);
-        return ok;
+        const double lnJ = log1p_(k.Jm1);
+        const double psi = 0.5 * mu * k.I1m3 - mu * lnJ + 0.5 * lam * lnJ * lnJ;
+        double F[9], Fa[9], Ae[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) F[i] = k.H[i] + ((i % 4) == 0 ? 1.0 : 0.0);
+        const double detF = adj_det(F, Fa);   // F^-1 = Fa / detF
+        const double rdF = 1.0 / detF;
+        double P[9], Sg[9];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int J = 0; J < 3; ++J) {
+                const double FiT = Fa[J * 3 + i] * rdF;   // F^-T_iJ
+                P[i * 3 + J] = mu * (F[i * 3 + J] - FiT) + lam * lnJ * FiT;
+            }
+#pragma unroll
+        for (int mm = 0; mm < 3; ++mm)
+#pragma unroll
+            for (int L = 0; L < 3; ++L)
+                Sg[mm * 3 + L] = (mm == L ? psi : 0.0) - (k.H[0 * 3 + mm] * P[0 * 3 + L]
+                                 + k.H[1 * 3 + mm] * P[1 * 3 + L] + k.H[2 * 3 + mm] * P[2 * 3 + L]);
+        // Q = w det Jx Sg Jx^-T = w Sg Ae^T
+        adj_det(Jx, Ae);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int J = 0; J < 3; ++J)
+                Q[i * 3 + J] = w * (Sg[i * 3 + 0] * Ae[J * 3 + 0] + Sg[i * 3 + 1] * Ae[J * 3 + 1]
+                                    + Sg[i * 3 + 2] * Ae[J * 3 + 2]);
+        return true;
     }
 };
 
 // ---- operations of the linear model
 
-// X and a direction v: the linear model's tangent does not depend on u.
-template <class T> struct alignas(16) NodeXV {
-    T X[3], v[3];
-};
-
-template <class T> struct LinHvpOp {
+template <class T> struct LinHvpOp : ForceForm<LinHvpOp<T>, NodeXV<T>, T> {
     using Node = NodeXV<T>;
     const T *X, *v;
+    LinHvpOp(const T *X_, const T *v_) : X(X_), v(v_) {}
     __device__ void stage(const BlockMesh &m, Node &n, int64_t g) const
     {
         load3(X, g, n.X);
@@ -1350,138 +1335,75 @@ template <class T> struct LinHvpOp {
                 if ((b >> c) & 1) n.v[c] = T(0);
         }
     }
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const T *mu, const T *lam,
-                                            bool pair, T f[E::NEN][3]) const
+    template <bool>
+    __device__ static __forceinline__ bool point(T w, const T Jx[9], const T dJ[9], T mu, T lam, T Q[9])
     {
-        T Xe[E::NEN][3], ve[E::NEN][3];
-#pragma unroll
-        for (int a = 0; a < E::NEN; ++a)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                Xe[a][i] = sn[lc[a]].X[i];
-                ve[a][i] = sn[lc[a]].v[i];
-            }
-        typename E::template Field<T> FX, Fv;
-        E::prep(Xe, FX);
-        E::prep(ve, Fv);
-        typename E::template Acc<T> A;
-#pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            T Jx[9], dJ[9], Q[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fv, q, dJ);
-            qp_linear(E::template weight<T>(), Jx, dJ, mu[E::sub(q)], lam[E::sub(q)], Q);
-            E::template add_forces<true>(Q, q, A);
-        }
-        E::finish(A, f);
+        qp_linear(w, Jx, dJ, mu, lam, Q);
         return true;
     }
 };
 
-struct LinResidualOp : XUStage {
+struct LinResidualOp : XUStage, ForceForm<LinResidualOp, NodeXU, double> {
     using Node = NodeXU;
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+    template <bool>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double Hxi[9], double mu, double lam,
+                                                 double Q[9])
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        typename E::template Acc<double> A;
-#pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            double Jx[9], Hxi[9], Q[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            qp_linear(E::template weight<double>(), Jx, Hxi, mu[E::sub(q)], lam[E::sub(q)], Q);
-            E::template add_forces<true>(Q, q, A);
-        }
-        E::finish(A, f);
+        qp_linear(w, Jx, Hxi, mu, lam, Q);
         return true;
     }
 };
 
 // diag K of the linear model: w det Jx [mu |grad N_a|^2 + (mu + lam) (grad N_a)_i^2]
 // = w / De [mu |Ae^T n|^2 + (mu + lam) ((Ae^T n)_i)^2],  n = dN_a/dxi
-struct LinDiagOp : XUStage {
-    using Node = NodeXU;
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+struct LinDiagOp : NodeForm<LinDiagOp> {
+    struct Coef {
+        double c, mu, ml, Ae[9];
+    };
+    template <bool>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double *, double mu, double lam,
+                                                 Coef &c)
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-#pragma unroll
-        for (int a = 0; a < E::NEN; ++a) f[a][0] = f[a][1] = f[a][2] = 0.0;
-#pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            const double mq = mu[E::sub(q)], lq = lam[E::sub(q)];
-            double Jx[9], Ae[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            const double De = adj_det(Jx, Ae);
-            const double c = E::template weight<double>() / De;
-#pragma unroll
-            for (int n = 0; n < E::NEN; ++n) {
-                const double g0 = E::template dN<double>(q, n, 0);
-                const double g1 = E::template dN<double>(q, n, 1);
-                const double g2 = E::template dN<double>(q, n, 2);
-                const double t[3] = {Ae[0] * g0 + Ae[3] * g1 + Ae[6] * g2,
-                                     Ae[1] * g0 + Ae[4] * g1 + Ae[7] * g2,
-                                     Ae[2] * g0 + Ae[5] * g1 + Ae[8] * g2};
-                const double tt = t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) f[n][i] += c * (mq * tt + (mq + lq) * t[i] * t[i]);
-            }
-        }
+        const double De = adj_det(Jx, c.Ae);
+        c.c = w / De;
+        c.mu = mu;
+        c.ml = mu + lam;
         return true;
+    }
+    __device__ static __forceinline__ void node(const Coef &c, const double n[3], double f[3])
+    {
+        double t[3];
+        transposed(c.Ae, n, t);
+        const double tt = t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) f[i] += c.c * (c.mu * tt + c.ml * t[i] * t[i]);
     }
 };
 
 // dPsi/dX of the linear model at fixed nodal u: Q = w det Jx (psi I - H^T sigma) Jx^-T
-struct LinGradCoordsOp : XUStage {
+struct LinGradCoordsOp : XUStage, ForceForm<LinGradCoordsOp, NodeXU, double> {
     using Node = NodeXU;
-    template <class E>
-    __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
-                                            const double *lam, bool pair, double f[E::NEN][3]) const
+    template <bool>
+    __device__ static __forceinline__ bool point(double w, const double Jx[9], const double Hxi[9], double mu, double lam,
+                                                 double Q[9])
     {
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        typename E::template Acc<double> A;
+        double Ae[9], H[9], S[9], Sg[9], ee, tr;
+        lin_grad(Jx, Hxi, Ae, H);
+        lin_stress(H, mu, lam, S);
+        lin_invariants(H, ee, tr);
+        const double psi = mu * ee + 0.5 * lam * tr * tr;
 #pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            const double mq = mu[E::sub(q)], lq = lam[E::sub(q)];
-            double Jx[9], Hxi[9], Ae[9], H[9], S[9], Sg[9], Q[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            lin_grad(Jx, Hxi, Ae, H);
-            lin_stress(H, mq, lq, S);
-            double ee, tr;
-            lin_invariants(H, ee, tr);
-            const double psi = mq * ee + 0.5 * lq * tr * tr;
+        for (int mm = 0; mm < 3; ++mm)
 #pragma unroll
-            for (int mm = 0; mm < 3; ++mm)
+            for (int L = 0; L < 3; ++L)
+                Sg[mm * 3 + L] = (mm == L ? psi : 0.0) - (H[0 * 3 + mm] * S[0 * 3 + L]
+                                 + H[1 * 3 + mm] * S[1 * 3 + L] + H[2 * 3 + mm] * S[2 * 3 + L]);
 #pragma unroll
-                for (int L = 0; L < 3; ++L)
-                    Sg[mm * 3 + L] = (mm == L ? psi : 0.0) - (H[0 * 3 + mm] * S[0 * 3 + L]
-                                     + H[1 * 3 + mm] * S[1 * 3 + L] + H[2 * 3 + mm] * S[2 * 3 + L]);
-            const double w = E::template weight<double>();
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int J = 0; J < 3; ++J)
-                    Q[i * 3 + J] = w * (Sg[i * 3 + 0] * Ae[J * 3 + 0] + Sg[i * 3 + 1] * Ae[J * 3 + 1]
-                                        + Sg[i * 3 + 2] * Ae[J * 3 + 2]);
-            E::template add_forces<true>(Q, q, A);
-        }
-        E::finish(A, f);
+            for (int J = 0; J < 3; ++J)
+                Q[i * 3 + J] = w * (Sg[i * 3 + 0] * Ae[J * 3 + 0] + Sg[i * 3 + 1] * Ae[J * 3 + 1]
+                                    + Sg[i * 3 + 2] * Ae[J * 3 + 2]);
         return true;
     }
 };
@@ -1491,8 +1413,7 @@ struct LinGradCoordsOp : XUStage {
 //   r_{a,s} = sum_q w det J [ D grad c_s . grad N_a + (b(x_q) . grad c_s + k c_s) N_a ]
 // with b(x) = omega x x, D = mu_e, k = lam_e.  Linear in c: the residual of c
 // and the tangent action on v are the same map; the advection term makes the
-// tangent non-symmetric.  Gradients and forces in the node form (E::Lean),
-// which also interpolates values.
+// tangent non-symmetric.  The points also interpolate values.
 
 template <class T> struct TransportOp {
     using Node = NodeXV<T>;
@@ -1510,11 +1431,29 @@ template <class T> struct TransportOp {
                 if ((b >> i) & 1) n.v[i] = T(0);
         }
     }
+    // Q (diffusion) and g (advection and reaction) of a point
+    __device__ __forceinline__ void point(T w, const T Jx[9], const T Cxi[9], const T xq[3], const T cq[3], T D, T k,
+                                          T Q[9], T g[3]) const
+    {
+        T Ae[9], Gc[9];
+        const T De = lin_grad(Jx, Cxi, Ae, Gc);   // Gc[s][L] = d c_s / d x_L
+        const T b0 = om1 * xq[2] - om2 * xq[1], b1 = om2 * xq[0] - om0 * xq[2], b2 = om0 * xq[1] - om1 * xq[0];
+        // diffusion: w det Jx D grad c Jx^-T = w D Gc Ae^T
+#pragma unroll
+        for (int sp = 0; sp < 3; ++sp)
+#pragma unroll
+            for (int J = 0; J < 3; ++J)
+                Q[sp * 3 + J] = w * D * (Gc[sp * 3 + 0] * Ae[J * 3 + 0] + Gc[sp * 3 + 1] * Ae[J * 3 + 1]
+                                         + Gc[sp * 3 + 2] * Ae[J * 3 + 2]);
+        const T wDe = w * De;
+#pragma unroll
+        for (int sp = 0; sp < 3; ++sp)
+            g[sp] = wDe * (b0 * Gc[sp * 3 + 0] + b1 * Gc[sp * 3 + 1] + b2 * Gc[sp * 3 + 2] + k * cq[sp]);
+    }
     template <class E>
     __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const T *mu, const T *lam,
                                             bool pair, T f[E::NEN][3]) const
     {
-        using G = typename E::Lean;
         T Xe[E::NEN][3], ce[E::NEN][3];
 #pragma unroll
         for (int a = 0; a < E::NEN; ++a)
@@ -1524,49 +1463,52 @@ template <class T> struct TransportOp {
                 ce[a][i] = sn[lc[a]].v[i];
                 f[a][i] = T(0);
             }
-        typename G::template Field<T> FX, Fc;
-        G::prep(Xe, FX);
-        G::prep(ce, Fc);
+        typename E::template Field<T> FX, Fc;
+        E::prep(Xe, FX);
+        E::prep(ce, Fc);
 #pragma unroll
         for (int q = 0; q < E::NQ; ++q) {
             if (E::skip(q, pair)) continue;
-            T Jx[9], Cxi[9], Ae[9], Gc[9], Q[9];
-            G::grad(FX, q, Jx);
-            G::geom(Jx);
-            G::grad(Fc, q, Cxi);
-            const T De = lin_grad(Jx, Cxi, Ae, Gc);   // Gc[s][L] = d c_s / d x_L
+            T Jx[9], Cxi[9], Q[9], g[3];
+            E::grad(FX, q, Jx);
+            E::geom(Jx);
+            E::grad(Fc, q, Cxi);
             T xq[3] = {T(0), T(0), T(0)}, cq[3] = {T(0), T(0), T(0)};
 #pragma unroll
             for (int a = 0; a < E::NEN; ++a) {
-                const T Na = G::template N<T>(q, a);
+                const T Na = E::template N<T>(q, a);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     xq[i] += Na * Xe[a][i];
                     cq[i] += Na * ce[a][i];
                 }
             }
-            const T b0 = om1 * xq[2] - om2 * xq[1], b1 = om2 * xq[0] - om0 * xq[2], b2 = om0 * xq[1] - om1 * xq[0];
-            const T w = E::template weight<T>(), D = mu[E::sub(q)], k = lam[E::sub(q)];
-            // diffusion: w det Jx D grad c Jx^-T = w D Gc Ae^T
-#pragma unroll
-            for (int sp = 0; sp < 3; ++sp)
-#pragma unroll
-                for (int J = 0; J < 3; ++J)
-                    Q[sp * 3 + J] = w * D * (Gc[sp * 3 + 0] * Ae[J * 3 + 0] + Gc[sp * 3 + 1] * Ae[J * 3 + 1]
-                                             + Gc[sp * 3 + 2] * Ae[J * 3 + 2]);
-            G::template add_forces_to<false>(Q, q, f);
-            const T wDe = w * De;
-            T g[3];
-#pragma unroll
-            for (int sp = 0; sp < 3; ++sp)
-                g[sp] = wDe * (b0 * Gc[sp * 3 + 0] + b1 * Gc[sp * 3 + 1] + b2 * Gc[sp * 3 + 2] + k * cq[sp]);
+            point(E::template weight<T>(), Jx, Cxi, xq, cq, mu[E::sub(q)], lam[E::sub(q)], Q, g);
+            E::template add_forces_to<false>(Q, q, f);
 #pragma unroll
             for (int a = 0; a < E::NEN; ++a) {
-                const T Na = G::template N<T>(q, a);
+                const T Na = E::template N<T>(q, a);
 #pragma unroll
                 for (int sp = 0; sp < 3; ++sp) f[a][sp] += Na * g[sp];
             }
         }
+        return true;
+    }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, T mu, T lam, T f0[3], T f1[3]) const
+    {
+        Hex8Quad::Field<T> FX, Fc;
+        T xq[2][3], cq[2][3], Q[2][9], g[2][3];
+        Hex8Quad::prep<true>(n0.X, n1.X, FX, xq);
+        Hex8Quad::prep<true>(n0.v, n1.v, Fc, cq);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            T Jx[9], Cxi[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Hex8Quad::grad(Fc, q, Cxi);
+            point(Hex8Quad::weight<T>(l), Jx, Cxi, xq[q], cq[q], mu, lam, Q[q], g[q]);
+        }
+        Hex8Quad::forces(Q[0], Q[1], f0, f1);
+        Hex8Quad::add_values(g[0], g[1], f0, f1);
         return true;
     }
 };
@@ -1576,11 +1518,30 @@ template <class T> struct TransportOp {
 struct TransportDiagOp : XUStage {
     using Node = NodeXU;
     double om0, om1, om2;
+    struct Coef {
+        double cD, b[3], wk, Ae[9];
+    };
+    __device__ __forceinline__ void point(double w, const double Jx[9], const double xq[3], double D, double k,
+                                          Coef &c) const
+    {
+        const double De = adj_det(Jx, c.Ae);
+        c.cD = w * D / De;
+        c.b[0] = w * (om1 * xq[2] - om2 * xq[1]);
+        c.b[1] = w * (om2 * xq[0] - om0 * xq[2]);
+        c.b[2] = w * (om0 * xq[1] - om1 * xq[0]);
+        c.wk = w * De * k;
+    }
+    __device__ static __forceinline__ double node(const Coef &c, const double n[3], double N)
+    {
+        double t[3];
+        transposed(c.Ae, n, t);
+        return c.cD * (t[0] * t[0] + t[1] * t[1] + t[2] * t[2]) + (c.b[0] * t[0] + c.b[1] * t[1] + c.b[2] * t[2]) * N
+             + c.wk * N * N;
+    }
     template <class E>
     __device__ __forceinline__ bool element(const Node *sn, const uint16_t *lc, const double *mu,
                                             const double *lam, bool pair, double f[E::NEN][3]) const
     {
-        using G = typename E::Lean;
         double Xe[E::NEN][3];
 #pragma unroll
         for (int a = 0; a < E::NEN; ++a)
@@ -1589,38 +1550,64 @@ struct TransportDiagOp : XUStage {
                 Xe[a][i] = sn[lc[a]].X[i];
                 f[a][i] = 0.0;
             }
-        typename G::template Field<double> FX;
-        G::prep(Xe, FX);
+        typename E::template Field<double> FX;
+        E::prep(Xe, FX);
 #pragma unroll
         for (int q = 0; q < E::NQ; ++q) {
             if (E::skip(q, pair)) continue;
-            double Jx[9], Ae[9];
-            G::grad(FX, q, Jx);
-            G::geom(Jx);
-            const double De = adj_det(Jx, Ae);
+            double Jx[9];
+            E::grad(FX, q, Jx);
+            E::geom(Jx);
             double xq[3] = {0.0, 0.0, 0.0};
 #pragma unroll
             for (int a = 0; a < E::NEN; ++a)
 #pragma unroll
-                for (int i = 0; i < 3; ++i) xq[i] += G::template N<double>(q, a) * Xe[a][i];
-            const double b0 = om1 * xq[2] - om2 * xq[1], b1 = om2 * xq[0] - om0 * xq[2],
-                         b2 = om0 * xq[1] - om1 * xq[0];
-            const double w = E::template weight<double>(), D = mu[E::sub(q)], k = lam[E::sub(q)];
+                for (int i = 0; i < 3; ++i) xq[i] += E::template N<double>(q, a) * Xe[a][i];
+            Coef c;
+            point(E::template weight<double>(), Jx, xq, mu[E::sub(q)], lam[E::sub(q)], c);
 #pragma unroll
-            for (int n = 0; n < E::NEN; ++n) {
-                const double g0 = G::template dN<double>(q, n, 0);
-                const double g1 = G::template dN<double>(q, n, 1);
-                const double g2 = G::template dN<double>(q, n, 2);
-                const double t0 = Ae[0] * g0 + Ae[3] * g1 + Ae[6] * g2;
-                const double t1 = Ae[1] * g0 + Ae[4] * g1 + Ae[7] * g2;
-                const double t2 = Ae[2] * g0 + Ae[5] * g1 + Ae[8] * g2;
-                const double Nn = G::template N<double>(q, n);
-                const double d = w * (D * (t0 * t0 + t1 * t1 + t2 * t2) / De + (b0 * t0 + b1 * t1 + b2 * t2) * Nn
-                                      + De * k * Nn * Nn);
-                f[n][0] += d;
-                f[n][1] += d;
-                f[n][2] += d;
+            for (int a = 0; a < E::NEN; ++a) {
+                const double n[3] = {E::template dN<double>(q, a, 0), E::template dN<double>(q, a, 1),
+                                     E::template dN<double>(q, a, 2)};
+                const double d = node(c, n, E::template N<double>(q, a));
+                f[a][0] += d;
+                f[a][1] += d;
+                f[a][2] += d;
             }
+        }
+        return true;
+    }
+    __device__ __forceinline__ bool quad(const Node &n0, const Node &n1, int l, double mu, double lam, double f0[3],
+                                         double f1[3]) const
+    {
+        Hex8Quad::Field<double> FX;
+        double xq[2][3], d[2][2][2][3] = {};
+        Hex8Quad::prep<true>(n0.X, n1.X, FX, xq);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            double Jx[9];
+            Hex8Quad::grad(FX, q, Jx);
+            Coef c;
+            point(Hex8Quad::weight<double>(l), Jx, xq[q], mu, lam, c);
+#pragma unroll
+            for (int ix = 0; ix < 2; ++ix)
+#pragma unroll
+                for (int jy = 0; jy < 2; ++jy)
+#pragma unroll
+                    for (int jz = 0; jz < 2; ++jz) {
+                        const double n[3] = {Hex8Quad::dN(q, ix, jy, jz, 0), Hex8Quad::dN(q, ix, jy, jz, 1),
+                                             Hex8Quad::dN(q, ix, jy, jz, 2)};
+                        d[ix][jy][jz][0] += node(c, n, Hex8Quad::N(q, ix, jy, jz));
+                    }
+        }
+        // the three species share the sum: component 0 through the lanes
+#pragma unroll
+        for (int ix = 0; ix < 2; ++ix) {
+            const double e0 = d[ix][0][0][0] + Hex8Quad::peer<1>(d[ix][1][0][0]);
+            const double e1 = d[ix][0][1][0] + Hex8Quad::peer<1>(d[ix][1][1][0]);
+            const double s = e0 + Hex8Quad::peer<2>(e1);
+            double *f = ix ? f1 : f0;
+            f[0] = f[1] = f[2] = s;
         }
         return true;
     }
@@ -1650,7 +1637,7 @@ __device__ __forceinline__ ItemRange item_range(const BlockMesh &m, int b)
 // overlaps the previous item's arithmetic.
 template <class E> struct ItemWord;
 template <> struct ItemWord<Tet4Pair> { uint2 w; };
-template <> struct ItemWord<Hex8> { uint4 w; };
+template <> struct ItemWord<Hex8> {};   // read by lanes (quad_word)
 template <> struct ItemWord<Tri3> { uint32_t w; };
 
 template <class E> struct IData {
@@ -1664,8 +1651,7 @@ __device__ __forceinline__ IData<E> fetch_item(const BlockMesh &m, const ItemRan
     IData<E> d;
     const int64_t i = r.i0 + k;
     if constexpr (E::NEN == 5) d.lc.w = *reinterpret_cast<const uint2 *>(m.items + 2 * i);
-    else if constexpr (E::NEN == 3) d.lc.w = m.items[i];
-    else d.lc.w = *reinterpret_cast<const uint4 *>(m.items + 4 * i);
+    else d.lc.w = m.items[i];
 #pragma unroll
     for (int s = 0; s < E::NSUB; ++s) {
         if (m.mu) {
@@ -1688,8 +1674,7 @@ __device__ __forceinline__ ItemWord<E> fetch_lc(const BlockMesh &m, const ItemRa
     ItemWord<E> w;
     const int64_t i = r.i0 + k;
     if constexpr (E::NEN == 5) w.w = *reinterpret_cast<const uint2 *>(m.items + 2 * i);
-    else if constexpr (E::NEN == 3) w.w = m.items[i];
-    else w.w = *reinterpret_cast<const uint4 *>(m.items + 4 * i);
+    else w.w = m.items[i];
     return w;
 }
 
@@ -1718,11 +1703,8 @@ __device__ __forceinline__ void unpack_lc(const ItemWord<E> &l, uint16_t lc[E::N
     if constexpr (E::NEN == 5) {
         lc[0] = l.w.x & 1023u, lc[1] = (l.w.x >> 10) & 1023u, lc[2] = (l.w.x >> 20) & 1023u;
         lc[3] = l.w.y & 1023u, lc[4] = (l.w.y >> 10) & 1023u;
-    } else if constexpr (E::NEN == 3) {
-        lc[0] = l.w & 1023u, lc[1] = (l.w >> 10) & 1023u, lc[2] = (l.w >> 20) & 1023u;
     } else {
-        lc[0] = l.w.x & 0xffff, lc[1] = l.w.x >> 16, lc[2] = l.w.y & 0xffff, lc[3] = l.w.y >> 16;
-        lc[4] = l.w.z & 0xffff, lc[5] = l.w.z >> 16, lc[6] = l.w.w & 0xffff, lc[7] = l.w.w >> 16;
+        lc[0] = l.w & 1023u, lc[1] = (l.w >> 10) & 1023u, lc[2] = (l.w >> 20) & 1023u;
     }
 }
 
@@ -1734,6 +1716,20 @@ __device__ __forceinline__ void materials(const IData<E> &d, T mu[E::NSUB], T la
         mu[s] = T(d.mu[s]);
         lam[s] = T(d.lam[s]);
     }
+}
+
+// Hex8 on four lanes: the item's word of this lane, its x-edge's two nodes, as
+// (x-, x+) local ids.  The edges of a hexahedron are (0, 1), (3, 2), (4, 5),
+// (7, 6), so the odd lanes' words hold the x+ node first.
+__device__ __forceinline__ uint32_t quad_word(const BlockMesh &m, const ItemRange &r, int k, int lane)
+{
+    return m.items[4 * (int64_t)(r.i0 + k) + (lane & 3)];
+}
+__device__ __forceinline__ void quad_nodes(uint32_t w, int lane, int &l0, int &l1)
+{
+    const int a = (int)(w & 0xffffu), b = (int)(w >> 16);
+    l0 = (lane & 1) ? b : a;
+    l1 = (lane & 1) ? a : b;
 }
 
 // Stage a block's node records into LDS.  A thread issues all its global
@@ -1781,7 +1777,6 @@ template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
     static constexpr int value = EFEM_TET64_MIN_WAVES;
 };
 
-
 template <class E, class Op, class T, bool ACC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MinWaves<E, Op>::value, 8)))
 k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
@@ -1804,15 +1799,20 @@ k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
     // The 64 lanes of a wave take items S apart in the block's Morton order
     // (lane * S + j), so that the lanes of one LDS atomic rarely hit the same
     // node; wave w takes columns j = w, w + W, ...
+    constexpr bool QUAD = std::is_same<E, Hex8>::value;   // an item on four lanes: 16 items a wave step
     const int W = nt >> 6, lane = threadIdx.x & 63;
-    const int S = (r.ni + 63) >> 6;
+    const int S = QUAD ? (r.ni + 15) >> 4 : (r.ni + 63) >> 6;
     int j = threadIdx.x >> 6;
-    auto item_of = [&](int jj) { return lane * S + jj; };
+    auto item_of = [&](int jj) { return (QUAD ? lane >> 2 : lane) * S + jj; };
     // the next item's connectivity is in flight while this one computes; its
     // materials are read at use (two scalars when uniform), which keeps four
     // doubles per item out of the registers
     ItemWord<E> nxt{};
-    if (j < S && item_of(j) < r.ni) nxt = fetch_lc<E>(m, r, item_of(j));   // in flight during staging
+    uint32_t nxt1 = 0u;   // QUAD: the lane's own word, its edge's two nodes
+    if (j < S && item_of(j) < r.ni) {   // in flight during staging
+        if constexpr (QUAD) nxt1 = quad_word(m, r, item_of(j), lane);
+        else nxt = fetch_lc<E>(m, r, item_of(j));
+    }
     // the block-node words stay in LDS for write_out
     uint32_t *sbn = reinterpret_cast<uint32_t *>(acc + 3 * nn);
     stage_nodes(m, op, sn, bnode, nn, [&](int l, uint32_t ent) {
@@ -1826,18 +1826,33 @@ k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
     for (; j < S; j += W) {
         const int k = item_of(j);
         if (k >= r.ni) break;
-        const ItemWord<E> cur = nxt;
-        if (j + W < S && item_of(j + W) < r.ni) nxt = fetch_lc<E>(m, r, item_of(j + W));
-        uint16_t lc[E::NEN];
-        unpack_lc<E>(cur, lc);
         T mu[E::NSUB], lam[E::NSUB];
-        item_materials<E>(m, r, k, mu, lam);
-        T f[E::NEN][3];   // written in full by element()
-        bad |= !op.template element<E>(sn, lc, mu, lam, k < r.np, f);
+        if constexpr (QUAD) {
+            const uint32_t cur = nxt1;
+            if (j + W < S && item_of(j + W) < r.ni) nxt1 = quad_word(m, r, item_of(j + W), lane);
+            int l0, l1;
+            quad_nodes(cur, lane, l0, l1);
+            item_materials<E>(m, r, k, mu, lam);
+            T f0[3], f1[3];
+            bad |= !op.quad(sn[l0], sn[l1], lane & 3, mu[0], lam[0], f0, f1);
 #pragma unroll
-        for (int a = 0; a < E::NEN; ++a)
+            for (int i = 0; i < 3; ++i) {
+                atomicAdd(&acc[3 * l0 + i], (double)f0[i]);
+                atomicAdd(&acc[3 * l1 + i], (double)f1[i]);
+            }
+        } else {
+            const ItemWord<E> cur = nxt;
+            if (j + W < S && item_of(j + W) < r.ni) nxt = fetch_lc<E>(m, r, item_of(j + W));
+            uint16_t lc[E::NEN];
+            unpack_lc<E>(cur, lc);
+            item_materials<E>(m, r, k, mu, lam);
+            T f[E::NEN][3];   // written in full by element()
+            bad |= !op.template element<E>(sn, lc, mu, lam, k < r.np, f);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) atomicAdd(&acc[3 * lc[a] + i], (double)f[a][i]);
+            for (int a = 0; a < E::NEN; ++a)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) atomicAdd(&acc[3 * lc[a] + i], (double)f[a][i]);
+        }
     }
     if (bad) flag_inverted(m.flags);
     __syncthreads();
@@ -2207,6 +2222,41 @@ k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const 
 
 // ------------------------------------------------------------------- energy
 
+// The Hex8 items of a workgroup, four lanes each: f(item, the local ids of this
+// lane's edge), wave w taking columns w, w + W, ...
+template <class F> __device__ __forceinline__ void for_quads(const BlockMesh &m, const ItemRange &r, F f)
+{
+    const int W = blockDim.x >> 6, lane = threadIdx.x & 63, S = (r.ni + 15) >> 4;
+    for (int j = threadIdx.x >> 6; j < S; j += W) {
+        const int k = (lane >> 2) * S + j;
+        if (k >= r.ni) break;
+        int l0, l1;
+        quad_nodes(quad_word(m, r, k, lane), lane, l0, l1);
+        f(k, l0, l1);
+    }
+}
+
+// psi w det Jx of one point; inverted points set bad and give 0
+template <bool LIN>
+__device__ __forceinline__ double energy_point(double w, const double Jx[9], const double Hxi[9], double mu, double lam,
+                                               bool &bad)
+{
+    if (LIN) {
+        double Ae[9], H[9], ee, tr;
+        const double De = lin_grad(Jx, Hxi, Ae, H);
+        lin_invariants(H, ee, tr);
+        return w * De * (mu * ee + 0.5 * lam * tr * tr);
+    }
+    Kin kk;
+    kinematics(w, Jx, Hxi, kk);
+    if (!(1.0 + kk.Jm1 > 0.0)) {
+        bad = true;
+        return 0.0;
+    }
+    const double lnJ = log1p_(kk.Jm1);
+    return kk.wDe * (0.5 * mu * kk.I1m3 - mu * lnJ + 0.5 * lam * lnJ * lnJ);
+}
+
 template <class E, bool LIN>
 __global__ void __launch_bounds__(256) k_energy(BlockMesh m, const double *__restrict__ X,
                                                 const double *__restrict__ u,
@@ -2220,48 +2270,52 @@ __global__ void __launch_bounds__(256) k_energy(BlockMesh m, const double *__res
     const ItemRange r = item_range(m, b);
     NodeXU *sn = reinterpret_cast<NodeXU *>(smem);
     XUStage st{X, u};
-    const int nt = blockDim.x;
-    int k = threadIdx.x;
-    IData<E> nxt{};
-    if (k < r.ni) nxt = fetch_item<E>(m, r, k);
-    stage_nodes(m, st, sn, m.bnode + n0, nn, [](int, uint32_t) {});
-    __syncthreads();
     double acc = 0.0;
     bool bad = false;
-    for (; k < r.ni; k += nt) {
-        const IData<E> cur = nxt;
-        if (k + nt < r.ni) nxt = fetch_item<E>(m, r, k + nt);
-        uint16_t lc[E::NEN];
-        unpack_lc<E>(cur.lc, lc);
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        const bool pair = k < r.np;
-        double pe = 0.0;
+    if constexpr (std::is_same<E, Hex8>::value) {
+        stage_nodes(m, st, sn, m.bnode + n0, nn, [](int, uint32_t) {});
+        __syncthreads();
+        for_quads(m, r, [&](int k, int l0, int l1) {
+            Hex8Quad::Field<double> FX, Fu;
+            Hex8Quad::prep(sn[l0].X, sn[l1].X, FX);
+            Hex8Quad::prep(sn[l0].u, sn[l1].u, Fu);
+            double mu[1], lam[1];
+            item_materials<E>(m, r, k, mu, lam);
 #pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            const double mu = cur.mu[E::sub(q)], lam = cur.lam[E::sub(q)];
-            double Jx[9], Hxi[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            if (LIN) {
-                double Ae[9], H[9], ee, tr;
-                const double De = lin_grad(Jx, Hxi, Ae, H);
-                lin_invariants(H, ee, tr);
-                pe += E::template weight<double>() * De * (mu * ee + 0.5 * lam * tr * tr);
-                continue;
+            for (int q = 0; q < 2; ++q) {
+                double Jx[9], Hxi[9];
+                Hex8Quad::grad(FX, q, Jx);
+                Hex8Quad::grad(Fu, q, Hxi);
+                acc += energy_point<LIN>(Hex8Quad::weight<double>(threadIdx.x & 3), Jx, Hxi, mu[0], lam[0], bad);
             }
-            Kin kk;
-            kinematics(E::template weight<double>(), Jx, Hxi, kk);
-            if (!(1.0 + kk.Jm1 > 0.0)) {
-                bad = true;
-                continue;
+        });
+    } else {
+        const int nt = blockDim.x;
+        int k = threadIdx.x;
+        IData<E> nxt{};
+        if (k < r.ni) nxt = fetch_item<E>(m, r, k);
+        stage_nodes(m, st, sn, m.bnode + n0, nn, [](int, uint32_t) {});
+        __syncthreads();
+        for (; k < r.ni; k += nt) {
+            const IData<E> cur = nxt;
+            if (k + nt < r.ni) nxt = fetch_item<E>(m, r, k + nt);
+            uint16_t lc[E::NEN];
+            unpack_lc<E>(cur.lc, lc);
+            typename E::template Field<double> FX, Fu;
+            gather_xu<E>(sn, lc, FX, Fu);
+            const bool pair = k < r.np;
+            double pe = 0.0;
+#pragma unroll
+            for (int q = 0; q < E::NQ; ++q) {
+                if (E::skip(q, pair)) continue;
+                double Jx[9], Hxi[9];
+                E::grad(FX, q, Jx);
+                E::geom(Jx);
+                E::grad(Fu, q, Hxi);
+                pe += energy_point<LIN>(E::template weight<double>(), Jx, Hxi, cur.mu[E::sub(q)], cur.lam[E::sub(q)], bad);
             }
-            const double lnJ = log1p_(kk.Jm1);
-            pe += kk.wDe * (0.5 * mu * kk.I1m3 - mu * lnJ + 0.5 * lam * lnJ * lnJ);
+            acc += pe;
         }
-        acc += pe;
     }
     if (bad) {
         flag_inverted(m.flags);
@@ -2302,7 +2356,30 @@ __global__ void __launch_bounds__(256) k_sum_partials(const double *__restrict__
 
 // ---------------------------------------------------- per-element adjoint kernels
 
-// dPsi/dmu_e, dPsi/dlam_e at fixed u.
+// dPsi/dmu_e, dPsi/dlam_e at fixed u: one point's share added to gm, gl
+template <bool LIN>
+__device__ __forceinline__ void material_point(double w, const double Jx[9], const double Hxi[9], double &gm, double &gl,
+                                               bool &bad)
+{
+    if (LIN) {
+        double Ae[9], H[9], ee, tr;
+        const double wDe = w * lin_grad(Jx, Hxi, Ae, H);
+        lin_invariants(H, ee, tr);
+        gm += wDe * ee;
+        gl += wDe * 0.5 * tr * tr;
+        return;
+    }
+    Kin kk;
+    kinematics(w, Jx, Hxi, kk);
+    if (!(1.0 + kk.Jm1 > 0.0)) {
+        bad = true;
+        return;
+    }
+    const double lnJ = log1p_(kk.Jm1);
+    gm += kk.wDe * (0.5 * kk.I1m3 - lnJ);
+    gl += kk.wDe * 0.5 * lnJ * lnJ;
+}
+
 template <class E, bool LIN>
 __global__ void __launch_bounds__(256) k_grad_material(BlockMesh m, const double *__restrict__ X,
                                                        const double *__restrict__ u,
@@ -2318,45 +2395,52 @@ __global__ void __launch_bounds__(256) k_grad_material(BlockMesh m, const double
     stage_nodes(m, st, sn, m.bnode + n0, nn, [](int, uint32_t) {});
     __syncthreads();
     bool bad = false;
-    for (int k = threadIdx.x; k < r.ni; k += blockDim.x) {
-        const IData<E> d = fetch_item<E>(m, r, k);
-        uint16_t lc[E::NEN];
-        unpack_lc<E>(d.lc, lc);
-        typename E::template Field<double> FX, Fu;
-        gather_xu<E>(sn, lc, FX, Fu);
-        const bool pair = k < r.np;
-        double gm[E::NSUB] = {}, gl[E::NSUB] = {};
+    if constexpr (std::is_same<E, Hex8>::value) {
+        for_quads(m, r, [&](int k, int l0, int l1) {
+            Hex8Quad::Field<double> FX, Fu;
+            Hex8Quad::prep(sn[l0].X, sn[l1].X, FX);
+            Hex8Quad::prep(sn[l0].u, sn[l1].u, Fu);
+            double gm = 0.0, gl = 0.0;
 #pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            double Jx[9], Hxi[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            if (LIN) {
-                double Ae[9], H[9], ee, tr;
-                const double wDe = E::template weight<double>() * lin_grad(Jx, Hxi, Ae, H);
-                lin_invariants(H, ee, tr);
-                gm[E::sub(q)] += wDe * ee;
-                gl[E::sub(q)] += wDe * 0.5 * tr * tr;
-                continue;
+            for (int q = 0; q < 2; ++q) {
+                double Jx[9], Hxi[9];
+                Hex8Quad::grad(FX, q, Jx);
+                Hex8Quad::grad(Fu, q, Hxi);
+                material_point<LIN>(Hex8Quad::weight<double>(threadIdx.x & 3), Jx, Hxi, gm, gl, bad);
             }
-            Kin kk;
-            kinematics(E::template weight<double>(), Jx, Hxi, kk);
-            if (!(1.0 + kk.Jm1 > 0.0)) {
-                bad = true;
-                continue;
+            gm = Hex8Quad::sum(gm);
+            gl = Hex8Quad::sum(gl);
+            if ((threadIdx.x & 3) == 0) {
+                const int eo = m.eorig[r.elem(k, 0)];
+                dmu[eo] = gm;
+                dlam[eo] = gl;
             }
-            const double lnJ = log1p_(kk.Jm1);
-            gm[E::sub(q)] += kk.wDe * (0.5 * kk.I1m3 - lnJ);
-            gl[E::sub(q)] += kk.wDe * 0.5 * lnJ * lnJ;
-        }
+        });
+    } else {
+        for (int k = threadIdx.x; k < r.ni; k += blockDim.x) {
+            const IData<E> d = fetch_item<E>(m, r, k);
+            uint16_t lc[E::NEN];
+            unpack_lc<E>(d.lc, lc);
+            typename E::template Field<double> FX, Fu;
+            gather_xu<E>(sn, lc, FX, Fu);
+            const bool pair = k < r.np;
+            double gm[E::NSUB] = {}, gl[E::NSUB] = {};
 #pragma unroll
-        for (int s = 0; s < E::NSUB; ++s) {
-            if (s > 0 && !pair) break;
-            const int eo = m.eorig[r.elem(k, s)];
-            dmu[eo] = gm[s];
-            dlam[eo] = gl[s];
+            for (int q = 0; q < E::NQ; ++q) {
+                if (E::skip(q, pair)) continue;
+                double Jx[9], Hxi[9];
+                E::grad(FX, q, Jx);
+                E::geom(Jx);
+                E::grad(Fu, q, Hxi);
+                material_point<LIN>(E::template weight<double>(), Jx, Hxi, gm[E::sub(q)], gl[E::sub(q)], bad);
+            }
+#pragma unroll
+            for (int s = 0; s < E::NSUB; ++s) {
+                if (s > 0 && !pair) break;
+                const int eo = m.eorig[r.elem(k, s)];
+                dmu[eo] = gm[s];
+                dlam[eo] = gl[s];
+            }
         }
     }
     if (bad) flag_inverted(m.flags);
@@ -2364,6 +2448,51 @@ __global__ void __launch_bounds__(256) k_grad_material(BlockMesh m, const double
 
 // w . dr/dmu_e = sum_q w detJ (F - F^-T) : grad w,  w . dr/dlam_e = sum_q w detJ lnJ F^-T : grad w
 // linear model: w . dr/dmu_e = sum_q w detJ 2 eps(u) : grad w,  w . dr/dlam_e = sum_q w detJ tr eps(u) div w
+template <bool LIN>
+__device__ __forceinline__ void vjp_point(double w, const double Jx[9], const double Hxi[9], const double Wxi[9],
+                                          double &gm, double &gl, bool &bad)
+{
+    double Ae[9];
+    if (LIN) {
+        double H[9], Gw[9];
+        const double wDe = w * lin_grad(Jx, Hxi, Ae, H);
+        lin_grad(Jx, Wxi, Ae, Gw);
+        double sm = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int J = 0; J < 3; ++J) sm += (H[i * 3 + J] + H[J * 3 + i]) * Gw[i * 3 + J];
+        gm += wDe * sm;
+        gl += wDe * (H[0] + H[4] + H[8]) * (Gw[0] + Gw[4] + Gw[8]);
+        return;
+    }
+    Kin kk;
+    kinematics(w, Jx, Hxi, kk);
+    if (!(1.0 + kk.Jm1 > 0.0)) {
+        bad = true;
+        return;
+    }
+    const double lnJ = log1p_(kk.Jm1);
+    const double De = adj_det(Jx, Ae);
+    double F[9], Fa[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) F[i] = kk.H[i] + ((i % 4) == 0 ? 1.0 : 0.0);
+    const double rdF = 1.0 / adj_det(F, Fa);
+    double sm = 0.0, sl = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int J = 0; J < 3; ++J) {
+            const double gw = (Wxi[i * 3 + 0] * Ae[0 * 3 + J] + Wxi[i * 3 + 1] * Ae[1 * 3 + J]
+                               + Wxi[i * 3 + 2] * Ae[2 * 3 + J]) / De;
+            const double FiT = Fa[J * 3 + i] * rdF;
+            sm += (F[i * 3 + J] - FiT) * gw;
+            sl += lnJ * FiT * gw;
+        }
+    gm += kk.wDe * sm;
+    gl += kk.wDe * sl;
+}
+
 template <class E, bool LIN>
 __global__ void __launch_bounds__(256) k_vjp_material(BlockMesh m, const double *__restrict__ X,
                                                       const double *__restrict__ u,
@@ -2380,80 +2509,68 @@ __global__ void __launch_bounds__(256) k_vjp_material(BlockMesh m, const double 
     stage_nodes(m, st, sn, m.bnode + n0, nn, [](int, uint32_t) {});
     __syncthreads();
     bool bad = false;
-    for (int k = threadIdx.x; k < r.ni; k += blockDim.x) {
-        const IData<E> d = fetch_item<E>(m, r, k);
-        uint16_t lc[E::NEN];
-        unpack_lc<E>(d.lc, lc);
-        typename E::template Field<double> FX, Fu, Fw;
-        {
-            double Xe[E::NEN][3], ue[E::NEN][3], we[E::NEN][3];
+    if constexpr (std::is_same<E, Hex8>::value) {
+        for_quads(m, r, [&](int k, int l0, int l1) {
+            Hex8Quad::Field<double> FX, Fu, Fw;
+            Hex8Quad::prep(sn[l0].X, sn[l1].X, FX);
+            Hex8Quad::prep(sn[l0].u, sn[l1].u, Fu);
+            Hex8Quad::prep(sn[l0].w, sn[l1].w, Fw);
+            double gm = 0.0, gl = 0.0;
 #pragma unroll
-            for (int a = 0; a < E::NEN; ++a)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    Xe[a][i] = sn[lc[a]].X[i];
-                    ue[a][i] = sn[lc[a]].u[i];
-                    we[a][i] = sn[lc[a]].w[i];
-                }
-            E::prep(Xe, FX);
-            E::prep(ue, Fu);
-            E::prep(we, Fw);
-        }
-        const bool pair = k < r.np;
-        double gm[E::NSUB] = {}, gl[E::NSUB] = {};
-#pragma unroll
-        for (int q = 0; q < E::NQ; ++q) {
-            if (E::skip(q, pair)) continue;
-            double Jx[9], Hxi[9], Wxi[9], Ae[9];
-            E::grad(FX, q, Jx);
-            E::geom(Jx);
-            E::grad(Fu, q, Hxi);
-            E::grad(Fw, q, Wxi);
-            if (LIN) {
-                double H[9], Gw[9];
-                const double wDe = E::template weight<double>() * lin_grad(Jx, Hxi, Ae, H);
-                lin_grad(Jx, Wxi, Ae, Gw);
-                double sm = 0.0;
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int J = 0; J < 3; ++J) sm += (H[i * 3 + J] + H[J * 3 + i]) * Gw[i * 3 + J];
-                gm[E::sub(q)] += wDe * sm;
-                gl[E::sub(q)] += wDe * (H[0] + H[4] + H[8]) * (Gw[0] + Gw[4] + Gw[8]);
-                continue;
+            for (int q = 0; q < 2; ++q) {
+                double Jx[9], Hxi[9], Wxi[9];
+                Hex8Quad::grad(FX, q, Jx);
+                Hex8Quad::grad(Fu, q, Hxi);
+                Hex8Quad::grad(Fw, q, Wxi);
+                vjp_point<LIN>(Hex8Quad::weight<double>(threadIdx.x & 3), Jx, Hxi, Wxi, gm, gl, bad);
             }
-            Kin kk;
-            kinematics(E::template weight<double>(), Jx, Hxi, kk);
-            if (!(1.0 + kk.Jm1 > 0.0)) {
-                bad = true;
-                continue;
+            gm = Hex8Quad::sum(gm);
+            gl = Hex8Quad::sum(gl);
+            if ((threadIdx.x & 3) == 0) {
+                const int eo = m.eorig[r.elem(k, 0)];
+                dmu[eo] = gm;
+                dlam[eo] = gl;
             }
-            const double lnJ = log1p_(kk.Jm1);
-            const double De = adj_det(Jx, Ae);
-            double F[9], Fa[9];
+        });
+    } else {
+        for (int k = threadIdx.x; k < r.ni; k += blockDim.x) {
+            const IData<E> d = fetch_item<E>(m, r, k);
+            uint16_t lc[E::NEN];
+            unpack_lc<E>(d.lc, lc);
+            typename E::template Field<double> FX, Fu, Fw;
+            {
+                double Xe[E::NEN][3], ue[E::NEN][3], we[E::NEN][3];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) F[i] = kk.H[i] + ((i % 4) == 0 ? 1.0 : 0.0);
-            const double rdF = 1.0 / adj_det(F, Fa);
-            double sm = 0.0, sl = 0.0;
+                for (int a = 0; a < E::NEN; ++a)
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
+                    for (int i = 0; i < 3; ++i) {
+                        Xe[a][i] = sn[lc[a]].X[i];
+                        ue[a][i] = sn[lc[a]].u[i];
+                        we[a][i] = sn[lc[a]].w[i];
+                    }
+                E::prep(Xe, FX);
+                E::prep(ue, Fu);
+                E::prep(we, Fw);
+            }
+            const bool pair = k < r.np;
+            double gm[E::NSUB] = {}, gl[E::NSUB] = {};
 #pragma unroll
-                for (int J = 0; J < 3; ++J) {
-                    const double gw = (Wxi[i * 3 + 0] * Ae[0 * 3 + J] + Wxi[i * 3 + 1] * Ae[1 * 3 + J]
-                                       + Wxi[i * 3 + 2] * Ae[2 * 3 + J]) / De;
-                    const double FiT = Fa[J * 3 + i] * rdF;
-                    sm += (F[i * 3 + J] - FiT) * gw;
-                    sl += lnJ * FiT * gw;
-                }
-            gm[E::sub(q)] += kk.wDe * sm;
-            gl[E::sub(q)] += kk.wDe * sl;
-        }
+            for (int q = 0; q < E::NQ; ++q) {
+                if (E::skip(q, pair)) continue;
+                double Jx[9], Hxi[9], Wxi[9];
+                E::grad(FX, q, Jx);
+                E::geom(Jx);
+                E::grad(Fu, q, Hxi);
+                E::grad(Fw, q, Wxi);
+                vjp_point<LIN>(E::template weight<double>(), Jx, Hxi, Wxi, gm[E::sub(q)], gl[E::sub(q)], bad);
+            }
 #pragma unroll
-        for (int s = 0; s < E::NSUB; ++s) {
-            if (s > 0 && !pair) break;
-            const int eo = m.eorig[r.elem(k, s)];
-            dmu[eo] = gm[s];
-            dlam[eo] = gl[s];
+            for (int s = 0; s < E::NSUB; ++s) {
+                if (s > 0 && !pair) break;
+                const int eo = m.eorig[r.elem(k, s)];
+                dmu[eo] = gm[s];
+                dlam[eo] = gl[s];
+            }
         }
     }
     if (bad) flag_inverted(m.flags);
@@ -2617,7 +2734,7 @@ hipError_t launch_hvp_f64(const Ctx &c, const double *xlin, const double *v, dou
         return dispatch(c, op, y, true, 0.0, skip, mode);
     }
     if (c.model == EFEM_MODEL_LINEAR) {
-        LinHvpOp<double> op{c.m.X, v};
+        LinHvpOp<double> op(c.m.X, v);
         return dispatch(c, op, y, true, 0.0, skip, mode);
     }
     HvpOp<double> op{xlin, v, y};
@@ -2632,7 +2749,7 @@ hipError_t launch_hvp_f32(const Ctx &c, const float *ulin, const float *v, float
         return dispatch(c, op, y, true, 0.0f, skip, mode);
     }
     if (c.model == EFEM_MODEL_LINEAR) {
-        LinHvpOp<float> op{c.m.Xf, v};
+        LinHvpOp<float> op(c.m.Xf, v);
         return dispatch(c, op, y, true, 0.0f, skip, mode);
     }
     HvpOp<float> op{c.m.Xf, ulin, v, y};

@@ -133,3 +133,42 @@ def test_assembly_by_rows_and_by_colours(mesh, model):
     C = C.tocsr()
     C.sort_indices()
     assert np.abs(got - C.data).max() <= 1e-10 * np.abs(K.data).max()
+
+
+@pytest.mark.parametrize("model", ["neo_hookean", "linear"])
+@pytest.mark.parametrize("n,block", [(1, 0), (2, 3), (3, 0), (3, 17), (4, 63), (5, 0), (5, 65)])
+def test_hexahedra_at_lane_remainders(n, block, model):
+    """Hex8 passes with blocks that end inside a wave's 16 elements, with a
+    varying material (every element finds its own), a mask and the adjoints:
+    FP64 1e-10 and FP32 5e-5 of the largest entry."""
+    from paper_2602_12365_amd import Operator
+    m = I.scrambled_mesh(I.hex_mesh(n), 3) if n > 1 else I.hex_mesh(1)
+    g = np.random.default_rng(n)
+    mu = np.exp(0.4 * g.standard_normal(m.n_elems))
+    lam = np.exp(0.4 * g.standard_normal(m.n_elems))
+    u, v = 0.03 / n * g.standard_normal((2, m.n_nodes, 3))
+    op = Operator(I.HEX8, m.X, m.conn, model=model, block_elems=block)
+    op.set_material(dev(mu), dev(lam))
+    orc = F.FEM(I.HEX8, m.X, m.conn, mu, lam, model=model)
+    for mask in (None, (g.random(3 * m.n_nodes) < 0.3).astype(np.uint8)):
+        op.set_dirichlet(None if mask is None else dev(mask))
+        free = np.ones((m.n_nodes, 3)) if mask is None else 1.0 - mask.reshape(-1, 3)
+        want = orc.hvp(u, v * free) * free
+        op.linearize(dev(u), "f64")
+        assert np.abs(op.hvp(dev(v)).cpu().numpy() - want).max() <= 1e-10 * np.abs(want).max()
+        op.linearize(dev(u), "f32")
+        got = op.hvp(dev(v, torch.float32)).cpu().numpy()
+        assert np.abs(got - want).max() <= 5e-5 * np.abs(want).max()
+        res = orc.residual(u) * free
+        assert np.abs(op.residual(dev(u)).cpu().numpy() - res).max() <= 1e-10 * np.abs(res).max()
+        d = np.where(free > 0, orc.jacobi_diag(u).reshape(-1, 3), 1.0)
+        assert rel(op.jacobi_diag(dev(u)).cpu(), d) <= 1e-10
+    op.set_dirichlet(None)
+    psi = orc.energy(u)
+    assert abs(float(op.energy(dev(u))) - psi) <= 1e-12 * abs(psi)
+    assert rel(op.jacobi_offdiag(dev(u)).cpu(), orc.jacobi_offdiag(u).reshape(-1, 3)) <= 1e-10
+    for got, want in zip(op.grad_material(dev(u)), orc.grad_material(u)):
+        assert rel(got.cpu(), want) <= 1e-10
+    for got, want in zip(op.residual_vjp_material(dev(u), dev(v)), orc.residual_vjp_material(u, v)):
+        assert rel(got.cpu(), want) <= 1e-10
+    assert rel(op.grad_coords(dev(u)).cpu(), orc.grad_coords(u).reshape(-1, 3)) <= 1e-10
