@@ -887,7 +887,7 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device);
     HostChunks hc;
     const bool use_chunks = elem == EFEM_TET4 && ctx->scatter == Scatter::Halo && !(opts && opts->no_chunks)
-                            && n_nodes <= (int64_t)kStageGid && lds_max >= kChunkLds
+                            && n_nodes <= (int64_t)kStageGid && lds_max >= kChunkLds + kChunkPqLds
                             && build_chunks(hb, n_nodes, n_cu, hc);
     if (use_chunks) spread_items_chunks(hb, hc);
     else spread_items_blocks(hb, elem);

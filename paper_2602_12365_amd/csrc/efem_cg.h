@@ -20,9 +20,10 @@ struct CgScalars {
     int32_t done, breakdown, iter, fallback, stall[2];
 };
 
-// Reduction scratch: four arrays of per-workgroup partials.
+// Reduction scratch: four arrays of per-workgroup partials and the buckets of p.q.
 struct CgWorkspace {
-    double *partials = nullptr;   // [4 * kMaxRedBlocks]
+    double *partials = nullptr;   // [4 * kMaxRedBlocks + kPqBuckets]
+    double *buckets() const { return partials + 4 * kMaxRedBlocks; }
 };
 
 int red_grid(int64_t n);
@@ -35,16 +36,23 @@ struct CgLaunch {
     // the update kernel clears q for the next tangent action (only the
     // atomic scatter's single-launch form needs q = 0 on entry)
     bool clear_q = true;
+    // where the nodes shared between blocks find their sums (launch_halo_index),
+    // null when the tangent action stores every node, and the slots
+    const int2 *shared = nullptr;
+    const T *halo = nullptr;
+    const uint8_t *nmask = nullptr;
     // 3x3 block Jacobi: [n_nodes][6] inverse blocks in bfloat16
-    // (k_block_inv); when set, init / update / dir / scaled apply them and
+    // (k_block_inv); when set, init / step / next / scaled apply them and
     // ignore dinv
     const uint16_t *binv = nullptr;
 
     hipError_t init(const double *b, double sign, const T *dinv, const uint8_t *nmask, T *x, T *r,
                     T *p, T *q, CgScalars *sc, double eta2) const;
     hipError_t pq(const T *p, const T *q, CgScalars *sc) const;
-    hipError_t update(T *x, T *r, const T *p, T *q, const T *dinv, CgScalars *sc, int j) const;
-    hipError_t dir(T *p, const T *r, const T *dinv, CgScalars *sc, int j) const;
+    // the two vector kernels of an iteration, after a tangent action that left
+    // p.q in the buckets (WriteMode::Krylov)
+    hipError_t step(T *r, T *q, const T *dinv, CgScalars *sc, int j) const;
+    hipError_t next(T *x, T *p, const T *r, const T *dinv, CgScalars *sc, int j) const;
     hipError_t dinv_from_diag(const double *diag, const uint8_t *nmask, T *dinv) const;
     hipError_t axpy_state(const double *u, double alpha, const T *d, double *out) const;
     hipError_t scaled(const T *dinv, const double *b, double sign, T *x) const;
@@ -77,6 +85,8 @@ struct FcgLaunch {
 // [n_nodes][3] of the nodes' 3x3 blocks of K (prescribed components removed)
 hipError_t launch_block_inv(hipStream_t s, int64_t n_nodes, const double *d, const double *o,
                             const uint8_t *nmask, uint16_t *binv);
+// shared [n_nodes]: the halo map by node (k_halo_index)
+hipError_t launch_halo_index(hipStream_t s, int64_t n_nodes, const HaloMap &hm, int2 *shared);
 hipError_t launch_bc_increment(hipStream_t s, int64_t n, const double *u, const double *u_bc,
                                double frac, const uint8_t *nmask, double *dc, double *u_old);
 hipError_t launch_dot64(hipStream_t s, const CgWorkspace &ws, int64_t n, const double *a,

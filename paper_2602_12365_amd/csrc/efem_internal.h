@@ -56,6 +56,8 @@ constexpr int kChunkThreads = 768;   // 12 waves per workgroup: 3 per SIMD
 constexpr int kPieceBytes = kChunkCap * 16;
 constexpr int kChunkSteps = 32;      // blocks per chunk at most
 constexpr int kChunkLds = 5 * kPieceBytes + kChunkCap * 24 + kChunkThreads * 4 + (4 * kChunkSteps + 3) * 4;
+// and, where it also takes v.K v, one double per thread
+constexpr int kChunkPqLds = kChunkThreads * 8;
 // staging word of a chunk slot: global id | Dirichlet bits << 28
 constexpr uint32_t kStageGid = 0x0fffffffu;
 struct ChunkMesh {
@@ -138,12 +140,17 @@ hipError_t launch_residual(const Ctx &c, const double *u, double *r);
 //               components to their value, before the block pass adds into
 //               shared nodes);
 //   Accumulate: y += K v (plain read-modify-write on block-private nodes);
-//   Zeroed:     y = K v for a y that holds zeros on entry (no fill pre-pass).
-enum class WriteMode { Overwrite = 0, Accumulate = 1, Zeroed = 2 };
+//   Zeroed:     y = K v for a y that holds zeros on entry (no fill pre-pass);
+//   Krylov:     Zeroed for a caller that sums the halo slots itself (no gather)
+//               and also takes v.K v, which the blocks add into pq.
+enum class WriteMode { Overwrite = 0, Accumulate = 1, Zeroed = 2, Krylov = 3 };
+// v.K v of a Krylov action: block b adds into bucket b % kPqBuckets, so that the
+// next kernel reads 2 KB whatever the mesh (cleared by the caller)
+constexpr int kPqBuckets = 256;
 hipError_t launch_hvp_f64(const Ctx &c, const double *xlin, const double *v, double *y,
-                          const int32_t *skip, WriteMode mode);
+                          const int32_t *skip, WriteMode mode, double *pq = nullptr);
 hipError_t launch_hvp_f32(const Ctx &c, const float *ulin, const float *v, float *y,
-                          const int32_t *skip, WriteMode mode);
+                          const int32_t *skip, WriteMode mode, double *pq = nullptr);
 hipError_t launch_diag(const Ctx &c, const double *u, double *d);
 // (K01, K02, K12) of every node's 3x3 diagonal block of K(u), unmasked
 hipError_t launch_offdiag(const Ctx &c, const double *u, double *o);
@@ -225,6 +232,18 @@ struct Ctx {
 void mlp_release(Ctx &c);
 // sparse-tangent resources of a context (sparse.cpp)
 void sparse_release(Ctx &c);
+
+// The halo map and slots that the tangent action of this precision uses, or
+// null when it stores every node itself.
+inline const HaloMap *hvp_halo(const Ctx &c, bool f64, const void **slots)
+{
+    *slots = nullptr;
+    if (c.scatter != Scatter::Halo) return nullptr;
+    const bool chunks = f64 && c.model == EFEM_MODEL_NEO_HOOKE && c.ch.n_chunks > 0;
+    if ((chunks ? c.n_ch_shared : c.n_shared) == 0) return nullptr;
+    *slots = chunks ? c.ch.halo : c.m.halo;
+    return chunks ? &c.ch_halo : &c.halo;
+}
 
 // error helpers (api.cpp)
 void set_error(const std::string &msg);

@@ -782,14 +782,19 @@ __device__ __forceinline__ bool comp_fixed(const uint8_t *nmask, int64_t g, int 
 // `fixed_val`.  Under the halo scatter a node shared with other blocks is not
 // written here: its sum goes to its halo slot (hslot[l]), and k_halo_gather
 // adds each node's slots up afterwards.
-template <bool ACC, class T>
-__device__ __forceinline__ void write_out(const BlockMesh &m, const uint32_t *bnode, int nn,
-                                          const double *acc, T *__restrict__ y, Scatter mode,
-                                          bool use_mask, T fixed_val, T *__restrict__ halo,
-                                          const int32_t *__restrict__ hslot)
+// PQ: returns the thread's share of v.K v, from the staged records sn.
+template <bool ACC, bool PQ, class T, class Node>
+__device__ __forceinline__ double write_out(const BlockMesh &m, const uint32_t *bnode, int nn,
+                                            const double *acc, T *__restrict__ y, Scatter mode,
+                                            bool use_mask, T fixed_val, T *__restrict__ halo,
+                                            const int32_t *__restrict__ hslot, const Node *sn)
 {
+    double vf = 0.0;
     for (int l = threadIdx.x; l < nn; l += blockDim.x) {
         const uint32_t ent = bnode[l];
+        if constexpr (PQ)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vf += (double)sn[l].v[c] * acc[l * 3 + c];
         const int64_t g = ent & kGidMask;
         if ((ent & kShared) && mode == Scatter::Halo) {
             T *h = halo + 3 * (int64_t)hslot[l];
@@ -819,6 +824,7 @@ __device__ __forceinline__ void write_out(const BlockMesh &m, const uint32_t *bn
             }
         }
     }
+    return vf;
 }
 
 // --------------------------------------------------------------- operations
@@ -1777,12 +1783,27 @@ template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
     static constexpr int value = EFEM_TET64_MIN_WAVES;
 };
 
-template <class E, class Op, class T, bool ACC>
+// Sum over the workgroup's waves into bucket `b`: one add per workgroup.
+__device__ __forceinline__ void add_bucket(double v, double *red, double *bucket)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
+        unsafeAtomicAdd(bucket, s);
+    }
+}
+
+// PQ (Krylov actions): v.K v, from the block's nodal sums and the v it staged.
+template <class E, class Op, class T, bool ACC, bool PQ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MinWaves<E, Op>::value, 8)))
 k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
                                                     const int32_t *__restrict__ list, int count,
                                                     Scatter mode, int use_mask, T fixed_val,
-                                                    const int32_t *__restrict__ skip)
+                                                    const int32_t *__restrict__ skip, double *__restrict__ pq)
 {
     using Node = typename Op::Node;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1856,8 +1877,12 @@ k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
     }
     if (bad) flag_inverted(m.flags);
     __syncthreads();
-    write_out<ACC>(m, sbn, nn, acc, y, mode, use_mask != 0, fixed_val,
-                   reinterpret_cast<T *>(m.halo), m.hslot ? m.hslot + n0 : nullptr);
+    const double vf = write_out<ACC, PQ>(m, sbn, nn, acc, y, mode, use_mask != 0, fixed_val,
+                                         reinterpret_cast<T *>(m.halo), m.hslot ? m.hslot + n0 : nullptr, sn);
+    if constexpr (PQ) {
+        __shared__ double wred[4];
+        add_bucket(vf, wred, pq + (b & (kPqBuckets - 1)));
+    }
 }
 
 // Second half of the halo scatter: shared node i = node[i] sums its halo
@@ -2039,11 +2064,18 @@ __device__ __forceinline__ void chunk_stage_mask(const BlockMesh &m, unsigned ch
 // Write-out of one chunk slot whose sum is final: to its halo entry (dst =
 // kShared | entry) or to y (dst = global id | Dirichlet bits << 28; ACC:
 // y += sum), prescribed components fixed_val while a mask is in force.
-template <bool ACC>
+// PQ: the slot's share of v.K v, from the v it staged (smem), is added to *vf.
+template <bool ACC, bool PQ>
 __device__ __forceinline__ void chunk_fin_store(const double *acc, int slot, uint32_t dst, double *__restrict__ y,
-                                                double *__restrict__ halo, bool masked, double fixed_val)
+                                                double *__restrict__ halo, bool masked, double fixed_val,
+                                                const unsigned char *smem, double *vf)
 {
     const double s0 = acc[3 * slot], s1 = acc[3 * slot + 1], s2 = acc[3 * slot + 2];
+    if constexpr (PQ) {
+        const double2 *P = reinterpret_cast<const double2 *>(smem);
+        const double2 p3 = P[3 * kChunkCap + slot], p4 = P[4 * kChunkCap + slot];
+        *vf += p3.x * s0 + p3.y * s1 + p4.y * s2;
+    }
     if (dst & kShared) {
         double *h = halo + 3 * (int64_t)(dst & ~kShared);
         h[0] = s0, h[1] = s1, h[2] = s2;
@@ -2066,12 +2098,13 @@ __device__ __forceinline__ void chunk_fin_store(const double *acc, int slot, uin
 __device__ __forceinline__ void wait_vm_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // UNI: a uniform material (the two kernel-argument scalars); otherwise per element.
-template <bool ACC, bool UNI>
+template <bool ACC, bool UNI, bool PQ>
 __global__ void __launch_bounds__(kChunkThreads)
 k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const double *__restrict__ v,
-              double *__restrict__ y, int use_mask, double fixed_val, const int32_t *__restrict__ skip)
+              double *__restrict__ y, int use_mask, double fixed_val, const int32_t *__restrict__ skip,
+              double *__restrict__ pq)
 {
-    __shared__ __align__(16) unsigned char smem[kChunkLds];
+    __shared__ __align__(16) unsigned char smem[kChunkLds + (PQ ? kChunkPqLds : 0)];
     if (skip && *skip) return;
     constexpr int W = kChunkThreads / 64;
     const int c = xcd_remap(blockIdx.x, ch.n_chunks);
@@ -2127,6 +2160,10 @@ k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const 
     __syncthreads();
 
     bool bad = false;
+    // the thread's share of v.K v stays in LDS between steps (two registers held
+    // through the element would spill)
+    double *vf = reinterpret_cast<double *>(smem + kChunkLds) + threadIdx.x;
+    if constexpr (PQ) *vf = 0.0;
     const bool masked = use_mask != 0 && m.nmask;
     // Progressive write-out: a slot's sum is final at the barrier after the
     // last block that touches it.  Its store goes out at the start of the
@@ -2138,10 +2175,10 @@ k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const 
     uint32_t fdst = 0u;
     for (int t = 0; t < nsteps; ++t) {
         if (fj >= 0) {
-            chunk_fin_store<ACC>(acc, fslot, fdst, y, ch.halo, masked, fixed_val);
+            chunk_fin_store<ACC, PQ>(acc, fslot, fdst, y, ch.halo, masked, fixed_val, smem, vf);
             // more final slots than threads (not met at the default sizes)
             for (int j = fj + kChunkThreads; j < t_fin[t]; j += kChunkThreads)
-                chunk_fin_store<ACC>(acc, ch.fin_slot[j], ch.fin_dst[j], y, ch.halo, masked, fixed_val);
+                chunk_fin_store<ACC, PQ>(acc, ch.fin_slot[j], ch.fin_dst[j], y, ch.halo, masked, fixed_val, smem, vf);
         }
         // records of step t+1 on their way, then the words of step t+2
         uint32_t word1 = 0u;
@@ -2217,7 +2254,11 @@ k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const 
     if (bad) flag_inverted(m.flags);
     // the slots final after the last step
     for (int j = t_fin[nsteps - 1] + (int)threadIdx.x; j < t_fin[nsteps]; j += kChunkThreads)
-        chunk_fin_store<ACC>(acc, ch.fin_slot[j], ch.fin_dst[j], y, ch.halo, masked, fixed_val);
+        chunk_fin_store<ACC, PQ>(acc, ch.fin_slot[j], ch.fin_dst[j], y, ch.halo, masked, fixed_val, smem, vf);
+    // the staging words' space is free after the last step
+    if constexpr (PQ)
+        add_bucket(*vf, reinterpret_cast<double *>(smem + 5 * kPieceBytes + kChunkCap * 24),
+                   pq + (c & (kPqBuckets - 1)));
 }
 
 // ------------------------------------------------------------------- energy
@@ -2599,34 +2640,47 @@ static void launch_gather(const Ctx &c, bool acc, const HaloMap &hm, const T *ha
 // The chunk pass of the FP64 Tet4 tangent action, then the gather of the
 // nodes that several chunks share.
 static hipError_t run_chunks(const Ctx &c, const HvpOp<double> &op, double *y, bool use_mask,
-                             const int32_t *skip, WriteMode mode)
+                             const int32_t *skip, WriteMode mode, double *pq)
 {
     const bool acc = mode == WriteMode::Accumulate, uni = c.m.mu == nullptr;
     const uint8_t *gmask = use_mask ? c.m.nmask : nullptr;
-    auto kern = acc ? (uni ? k_chunk_hvp64<true, true> : k_chunk_hvp64<true, false>)
-                    : (uni ? k_chunk_hvp64<false, true> : k_chunk_hvp64<false, false>);
+    const bool krylov = mode == WriteMode::Krylov;
+    auto kern = krylov ? (uni ? k_chunk_hvp64<false, true, true> : k_chunk_hvp64<false, false, true>)
+                : acc  ? (uni ? k_chunk_hvp64<true, true, false> : k_chunk_hvp64<true, false, false>)
+                       : (uni ? k_chunk_hvp64<false, true, false> : k_chunk_hvp64<false, false, false>);
     hipLaunchKernelGGL(kern, dim3(c.ch.n_chunks), dim3(kChunkThreads), 0, c.stream, c.m, c.ch, op.xrec, op.v, y,
-                       use_mask ? 1 : 0, 0.0, skip);
-    if (c.n_ch_shared > 0)
+                       use_mask ? 1 : 0, 0.0, skip, pq);
+    if (c.n_ch_shared > 0 && !krylov)
         launch_gather<double>(c, acc, c.ch_halo, c.ch.halo, y, gmask, 0.0, skip);
     return hipGetLastError();
 }
 
+// the symmetric tangent actions, which CG takes in mode Krylov
+template <class Op> struct TakesPq {
+    static constexpr bool value = false;
+};
+template <class T> struct TakesPq<HvpOp<T>> {
+    static constexpr bool value = true;
+};
+template <class T> struct TakesPq<LinHvpOp<T>> {
+    static constexpr bool value = true;
+};
+
 template <class E, class Op, class T>
 static hipError_t run_accumulate(const Ctx &c, const Op &op, T *y, bool use_mask, T fixed_val,
-                                 const int32_t *skip, WriteMode mode)
+                                 const int32_t *skip, WriteMode mode, double *pq)
 {
     if constexpr (std::is_same<E, Tet4Pair>::value && std::is_same<Op, HvpOp<double>>::value)
-        if (c.ch.n_chunks > 0 && c.scatter == Scatter::Halo) return run_chunks(c, op, y, use_mask, skip, mode);
+        if (c.ch.n_chunks > 0 && c.scatter == Scatter::Halo) return run_chunks(c, op, y, use_mask, skip, mode, pq);
     const size_t lds = lds_bytes<Op>(c, sizeof(double));
     const bool halo = c.scatter == Scatter::Halo && c.n_shared > 0;
     const uint8_t *gmask = use_mask ? c.m.nmask : nullptr;
     if (mode == WriteMode::Accumulate) {
         for (const Pass &p : c.passes) {
             if (p.count == 0) continue;
-            hipLaunchKernelGGL((k_accumulate<E, Op, T, true>), dim3(p.count), dim3(c.threads), lds,
+            hipLaunchKernelGGL((k_accumulate<E, Op, T, true, false>), dim3(p.count), dim3(c.threads), lds,
                                c.stream, c.m, op, y, p.list, p.count, c.scatter, use_mask ? 1 : 0,
-                               fixed_val, skip);
+                               fixed_val, skip, nullptr);
         }
         if (halo)
             launch_gather<T>(c, true, c.halo, reinterpret_cast<const T *>(c.m.halo), y, gmask, fixed_val, skip);
@@ -2639,22 +2693,24 @@ static hipError_t run_accumulate(const Ctx &c, const Op &op, T *y, bool use_mask
     }
     for (const Pass &p : c.passes) {
         if (p.count == 0) continue;
-        hipLaunchKernelGGL((k_accumulate<E, Op, T, false>), dim3(p.count), dim3(c.threads), lds, c.stream,
-                           c.m, op, y, p.list, p.count, c.scatter, use_mask ? 1 : 0, fixed_val,
-                           skip);
+        auto kern = k_accumulate<E, Op, T, false, false>;
+        if constexpr (TakesPq<Op>::value)
+            if (mode == WriteMode::Krylov) kern = k_accumulate<E, Op, T, false, true>;
+        hipLaunchKernelGGL(kern, dim3(p.count), dim3(c.threads), lds, c.stream, c.m, op, y, p.list, p.count, c.scatter,
+                           use_mask ? 1 : 0, fixed_val, skip, pq);
     }
-    if (halo)
+    if (halo && mode != WriteMode::Krylov)
         launch_gather<T>(c, false, c.halo, reinterpret_cast<const T *>(c.m.halo), y, gmask, fixed_val, skip);
     return hipGetLastError();
 }
 
 template <class Op, class T>
 static hipError_t dispatch(const Ctx &c, const Op &op, T *y, bool use_mask, T fixed_val,
-                           const int32_t *skip = nullptr, WriteMode mode = WriteMode::Overwrite)
+                           const int32_t *skip = nullptr, WriteMode mode = WriteMode::Overwrite, double *pq = nullptr)
 {
-    if (c.elem == EFEM_TRI3) return run_accumulate<Tri3>(c, op, y, use_mask, fixed_val, skip, mode);
-    return c.elem == EFEM_TET4 ? run_accumulate<Tet4Pair>(c, op, y, use_mask, fixed_val, skip, mode)
-                               : run_accumulate<Hex8>(c, op, y, use_mask, fixed_val, skip, mode);
+    if (c.elem == EFEM_TRI3) return run_accumulate<Tri3>(c, op, y, use_mask, fixed_val, skip, mode, pq);
+    return c.elem == EFEM_TET4 ? run_accumulate<Tet4Pair>(c, op, y, use_mask, fixed_val, skip, mode, pq)
+                               : run_accumulate<Hex8>(c, op, y, use_mask, fixed_val, skip, mode, pq);
 }
 
 hipError_t launch_residual(const Ctx &c, const double *u, double *r)
@@ -2727,33 +2783,33 @@ hipError_t launch_grad_coords(const Ctx &c, const double *u, double *g)
 }
 
 hipError_t launch_hvp_f64(const Ctx &c, const double *xlin, const double *v, double *y,
-                          const int32_t *skip, WriteMode mode)
+                          const int32_t *skip, WriteMode mode, double *pq)
 {
     if (c.model == EFEM_MODEL_TRANSPORT) {
         TransportOp<double> op{c.m.X, v, c.omega[0], c.omega[1], c.omega[2], 1};
-        return dispatch(c, op, y, true, 0.0, skip, mode);
+        return dispatch(c, op, y, true, 0.0, skip, mode, pq);
     }
     if (c.model == EFEM_MODEL_LINEAR) {
         LinHvpOp<double> op(c.m.X, v);
-        return dispatch(c, op, y, true, 0.0, skip, mode);
+        return dispatch(c, op, y, true, 0.0, skip, mode, pq);
     }
     HvpOp<double> op{xlin, v, y};
-    return dispatch(c, op, y, true, 0.0, skip, mode);
+    return dispatch(c, op, y, true, 0.0, skip, mode, pq);
 }
 
 hipError_t launch_hvp_f32(const Ctx &c, const float *ulin, const float *v, float *y,
-                          const int32_t *skip, WriteMode mode)
+                          const int32_t *skip, WriteMode mode, double *pq)
 {
     if (c.model == EFEM_MODEL_TRANSPORT) {
         TransportOp<float> op{c.m.Xf, v, float(c.omega[0]), float(c.omega[1]), float(c.omega[2]), 1};
-        return dispatch(c, op, y, true, 0.0f, skip, mode);
+        return dispatch(c, op, y, true, 0.0f, skip, mode, pq);
     }
     if (c.model == EFEM_MODEL_LINEAR) {
         LinHvpOp<float> op(c.m.Xf, v);
-        return dispatch(c, op, y, true, 0.0f, skip, mode);
+        return dispatch(c, op, y, true, 0.0f, skip, mode, pq);
     }
     HvpOp<float> op{c.m.Xf, ulin, v, y};
-    return dispatch(c, op, y, true, 0.0f, skip, mode);
+    return dispatch(c, op, y, true, 0.0f, skip, mode, pq);
 }
 
 template <class E, bool LIN>

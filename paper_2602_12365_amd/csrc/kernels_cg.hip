@@ -22,17 +22,37 @@ __device__ __forceinline__ bool dof_fixed(const uint8_t *nmask, int64_t i)
 #define GRID_STRIDE(i, n) \
     for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < (n); i += (int64_t)gridDim.x * kThreads)
 
-// Workgroup tree sum of one value per thread; every thread gets the total.
+// Sum over the 64 lanes of a wave; every lane gets the total.
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Workgroup sums of one or two values per thread in a fixed order (the waves
+// by lane exchanges, then the four wave sums): one barrier where a tree in LDS
+// takes nine, which is most of a small vector's time.  red: kThreads doubles.
 __device__ __forceinline__ double block_sum(double v, double *red)
 {
+    v = wave_sum(v);
     __syncthreads();
-    red[threadIdx.x] = v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+__device__ __forceinline__ void block_sum2(double &a, double &b, double *red)
+{
+    a = wave_sum(a);
+    b = wave_sum(b);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = a;
+        red[4 + (threadIdx.x >> 6)] = b;
     }
-    return red[0];
+    __syncthreads();
+    a = (red[0] + red[1]) + (red[2] + red[3]);
+    b = (red[4] + red[5]) + (red[6] + red[7]);
 }
 
 // Sum of the `count` partials of the previous kernel (same order in every workgroup).
@@ -41,6 +61,16 @@ __device__ __forceinline__ double sum_partials(const double *part, int count, do
     double s = 0.0;
     for (int i = threadIdx.x; i < count; i += kThreads) s += part[i];
     return block_sum(s, red);
+}
+__device__ __forceinline__ void sum_partials2(const double *pa, const double *pb, int count, double *red, double &a,
+                                              double &b)
+{
+    a = b = 0.0;
+    for (int i = threadIdx.x; i < count; i += kThreads) {
+        a += pa[i];
+        b += pb[i];
+    }
+    block_sum2(a, b, red);
 }
 
 // r = sign * b (prescribed -> 0), z = dinv r, p = z, x = 0, q = 0; partials of r.r, r.z
@@ -65,21 +95,21 @@ __global__ void __launch_bounds__(kThreads) k_cg_init(int64_t n, const double *_
         rz += (double)ri * (double)zi;
         rr += (double)ri * (double)ri;
     }
-    const double srr = block_sum(rr, red);
-    const double srz = block_sum(rz, red);
+    block_sum2(rr, rz, red);
     if (threadIdx.x == 0) {
-        prr[blockIdx.x] = srr;
-        prz[blockIdx.x] = srz;
+        prr[blockIdx.x] = rr;
+        prz[blockIdx.x] = rz;
     }
 }
 
 __global__ void __launch_bounds__(kThreads) k_cg_init_fin(const double *__restrict__ prr,
                                                           const double *__restrict__ prz, int count,
-                                                          CgScalars *sc, double eta2)
+                                                          CgScalars *sc, double eta2, double *__restrict__ buckets)
 {
     __shared__ double red[kThreads];
-    const double rr = sum_partials(prr, count, red);
-    const double rz = sum_partials(prz, count, red);
+    double rr, rz;
+    sum_partials2(prr, prz, count, red, rr, rz);
+    buckets[threadIdx.x] = 0.0;   // of the first tangent action's p.q
     if (threadIdx.x == 0) {
         sc->rz[0] = rz;
         sc->rz[1] = 0.0;
@@ -108,85 +138,6 @@ __global__ void __launch_bounds__(kThreads) k_cg_pq(int64_t n, const T *__restri
     GRID_STRIDE(i, n) pq += (double)p[i] * (double)q[i];
     const double s = block_sum(pq, red);
     if (threadIdx.x == 0) ppq[blockIdx.x] = s;
-}
-
-// alpha = rz / pq (breakdown if pq <= 0 or not finite); x += alpha p,
-// r -= alpha q, q = 0 if CLEAR (for a next tangent action that adds into q);
-// partials of r.r and r.(dinv r).  `j` is the iteration index and `par` its
-// parity (which rz slot is current).
-template <class T, bool CLEAR>
-__global__ void __launch_bounds__(kThreads) k_cg_update(int64_t n, T *__restrict__ x,
-                                                        T *__restrict__ r, const T *__restrict__ p,
-                                                        T *__restrict__ q, const T *__restrict__ dinv,
-                                                        CgScalars *sc, const double *__restrict__ ppq,
-                                                        int count, double *__restrict__ prr,
-                                                        double *__restrict__ prz, int par, int j)
-{
-    __shared__ double red[kThreads];
-    if (sc->done) return;
-    const double pq = sum_partials(ppq, count, red);
-    if (!(pq > 0.0) || !isfinite(pq)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            sc->pq = pq;
-            sc->breakdown = 1;
-            sc->done = 1;
-        }
-        return;
-    }
-    const double alpha = sc->rz[par] / pq;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->pq = pq;
-        sc->alpha = alpha;
-        sc->iter = j + 1;
-    }
-    const T a = (T)alpha;
-    double rr = 0.0, rz = 0.0;
-    GRID_STRIDE(i, n)
-    {
-        x[i] += a * p[i];
-        const T ri = r[i] - a * q[i];
-        r[i] = ri;
-        if (CLEAR) q[i] = T(0);
-        const T zi = dinv[i] * ri;
-        rr += (double)ri * (double)ri;
-        rz += (double)ri * (double)zi;
-    }
-    const double srr = block_sum(rr, red);
-    const double srz = block_sum(rz, red);
-    if (threadIdx.x == 0) {
-        prr[blockIdx.x] = srr;
-        prz[blockIdx.x] = srz;
-    }
-}
-
-// convergence test rr <= tol2; beta = rz_new / rz; p = dinv r + beta p
-template <class T>
-__global__ void __launch_bounds__(kThreads) k_cg_dir(int64_t n, T *__restrict__ p,
-                                                     const T *__restrict__ r,
-                                                     const T *__restrict__ dinv, CgScalars *sc,
-                                                     const double *__restrict__ prr,
-                                                     const double *__restrict__ prz, int count,
-                                                     int par)
-{
-    __shared__ double red[kThreads];
-    if (sc->done) return;
-    const double rr = sum_partials(prr, count, red);
-    const double rz = sum_partials(prz, count, red);
-    if (rr <= sc->tol2 || !isfinite(rr)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            sc->rr = rr;
-            sc->done = 1;
-        }
-        return;
-    }
-    const double beta = rz / sc->rz[par];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->rz[par ^ 1] = rz;
-        sc->rr = rr;
-        sc->beta = beta;
-    }
-    const T bt = (T)beta;
-    GRID_STRIDE(i, n) p[i] = dinv[i] * r[i] + bt * p[i];
 }
 
 // ------------------------------------------------ 3x3 block Jacobi
@@ -240,19 +191,22 @@ __global__ void k_block_inv(int64_t nn, const double *__restrict__ d, const doub
 
 // z = B r for node i's block
 template <class T>
-__device__ __forceinline__ void block_apply(const uint16_t *__restrict__ binv, int64_t i, T r0, T r1, T r2, T &z0,
-                                            T &z1, T &z2)
+__device__ __forceinline__ void block_mul(const uint32_t w[3], T r0, T r1, T r2, T &z0, T &z1, T &z2)
 {
-    const T b00 = T(from_bf16(binv[6 * i])), b11 = T(from_bf16(binv[6 * i + 1])), b22 = T(from_bf16(binv[6 * i + 2]));
-    const T b01 = T(from_bf16(binv[6 * i + 3])), b02 = T(from_bf16(binv[6 * i + 4]));
-    const T b12 = T(from_bf16(binv[6 * i + 5]));
+    const T b00 = T(from_bf16((uint16_t)w[0])), b11 = T(from_bf16((uint16_t)(w[0] >> 16)));
+    const T b22 = T(from_bf16((uint16_t)w[1])), b01 = T(from_bf16((uint16_t)(w[1] >> 16)));
+    const T b02 = T(from_bf16((uint16_t)w[2])), b12 = T(from_bf16((uint16_t)(w[2] >> 16)));
     z0 = b00 * r0 + b01 * r1 + b02 * r2;
     z1 = b01 * r0 + b11 * r1 + b12 * r2;
     z2 = b02 * r0 + b12 * r1 + b22 * r2;
 }
+template <class T>
+__device__ __forceinline__ void block_apply(const uint16_t *__restrict__ binv, int64_t i, T r0, T r1, T r2, T &z0,
+                                            T &z1, T &z2)
+{
+    block_mul(reinterpret_cast<const uint32_t *>(binv + 6 * i), r0, r1, r2, z0, z1, z2);   // 12 bytes a node
+}
 
-// The PCG kernels with the block preconditioner, one node (three DOFs) per
-// thread; their reductions and scalar logic are those of the DOF-wise ones.
 template <class T>
 __global__ void __launch_bounds__(kThreads) k_cgb_init(int64_t nn, const double *__restrict__ b, double sign,
                                                        const uint16_t *__restrict__ binv,
@@ -278,25 +232,93 @@ __global__ void __launch_bounds__(kThreads) k_cgb_init(int64_t nn, const double 
             rr += (double)rv[c] * (double)rv[c];
         }
     }
-    const double srr = block_sum(rr, red);
-    const double srz = block_sum(rz, red);
+    block_sum2(rr, rz, red);
     if (threadIdx.x == 0) {
-        prr[blockIdx.x] = srr;
-        prz[blockIdx.x] = srz;
+        prr[blockIdx.x] = rr;
+        prz[blockIdx.x] = rz;
     }
 }
 
-template <class T, bool CLEAR>
-__global__ void __launch_bounds__(kThreads) k_cgb_update(int64_t nn, T *__restrict__ x, T *__restrict__ r,
-                                                         const T *__restrict__ p, T *__restrict__ q,
-                                                         const uint16_t *__restrict__ binv, CgScalars *sc,
-                                                         const double *__restrict__ ppq, int count,
-                                                         double *__restrict__ prr, double *__restrict__ prz,
-                                                         int par, int j)
+// The preconditioner of one node: its 3x3 block in bfloat16 (12 bytes) or its diagonal.
+template <bool BLOCK, class T> struct NodePrec;
+template <class T> struct NodePrec<true, T> {
+    uint32_t w[3];
+    __device__ __forceinline__ void load(const T *, const uint16_t *__restrict__ binv, int64_t i)
+    {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(binv + 6 * i);
+        w[0] = p[0], w[1] = p[1], w[2] = p[2];
+    }
+    __device__ __forceinline__ void apply(const T r[3], T z[3]) const { block_mul(w, r[0], r[1], r[2], z[0], z[1], z[2]); }
+};
+template <class T> struct NodePrec<false, T> {
+    T d[3];
+    __device__ __forceinline__ void load(const T *__restrict__ dinv, const uint16_t *, int64_t i)
+    {
+        d[0] = dinv[3 * i], d[1] = dinv[3 * i + 1], d[2] = dinv[3 * i + 2];
+    }
+    __device__ __forceinline__ void apply(const T r[3], T z[3]) const
+    {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) z[c] = d[c] * r[c];
+    }
+};
+template <class T> __device__ __forceinline__ void load3(const T *__restrict__ p, int64_t i, T v[3])
+{
+    v[0] = p[3 * i], v[1] = p[3 * i + 1], v[2] = p[3 * i + 2];
+}
+
+// One PCG iteration is three launches: the tangent action, which also leaves
+// p.q (from the blocks' nodal sums, in kPqBuckets parts) and, under the halo scatter,
+// leaves the nodes shared between blocks in their halo slots; k_cg_step; and
+// k_cg_next.  Bound by launches and one memory latency each on small meshes,
+// by the vectors (10 passes) on large ones.  Per iteration against the five
+// launches before (gather and p.q on their own, x advanced in the update): 8^3
+// hexahedra 36 and 19 us (four-lane elements included), 64^3 tetrahedra, FP64,
+// 54.6 and 45.8, FP32 48.4 and 38.2, 128^3 hexahedra FP32 242 and 221.
+//
+// k_cg_step: alpha = rz / pq (breakdown if pq <= 0 or not finite); r -= alpha q
+// with a shared node's q summed from its slots; CLEAR: q = 0 for a next action
+// that adds into it; partials of r.r and r.z.  `j` is the iteration index and
+// `par` its parity (which rz slot is current).  One node per thread, its loads
+// issued before the scalars are summed (and the next node's before this one is
+// stored): a small vector is one memory latency, not three.
+template <class T, bool BLOCK, bool CLEAR>
+__global__ void __launch_bounds__(kThreads) k_cg_step(int64_t nn, T *__restrict__ r, T *__restrict__ q,
+                                                      const T *__restrict__ dinv, const uint16_t *__restrict__ binv,
+                                                      const int2 *__restrict__ shared, const T *__restrict__ halo,
+                                                      const uint8_t *__restrict__ nmask, CgScalars *sc,
+                                                      const double *__restrict__ buckets, double *__restrict__ prr,
+                                                      double *__restrict__ prz, int par, int j)
 {
     __shared__ double red[kThreads];
-    if (sc->done) return;
-    const double pq = sum_partials(ppq, count, red);
+    T qi[3], ri[3];
+    NodePrec<BLOCK, T> prec;
+    auto load = [&](int64_t i) {
+        const int2 sh = shared ? shared[i] : make_int2(0, 0);
+        load3(r, i, ri);
+        prec.load(dinv, binv, i);
+        if (sh.y == 0) {
+            load3(q, i, qi);
+        } else {
+            // the slots in block order, in FP64, as k_halo_gather sums them
+            double s[3] = {0.0, 0.0, 0.0};
+            const T *h = halo + 3 * (int64_t)sh.x;
+#pragma unroll 4
+            for (int k = 0; k < sh.y; ++k)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s[c] += (double)h[3 * k + c];
+            const int m = nmask ? nmask[i] : 0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) qi[c] = (m >> c) & 1 ? T(0) : T(s[c]);
+        }
+    };
+    int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    const double rz0 = sc->rz[par], mine = buckets[threadIdx.x];
+    const int done = sc->done;
+    if (i < nn) load(i);
+    if (done) return;
+    const double pq = block_sum(mine, red);
     if (!(pq > 0.0) || !isfinite(pq)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pq = pq;
@@ -305,7 +327,7 @@ __global__ void __launch_bounds__(kThreads) k_cgb_update(int64_t nn, T *__restri
         }
         return;
     }
-    const double alpha = sc->rz[par] / pq;
+    const double alpha = rz0 / pq;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc->pq = pq;
         sc->alpha = alpha;
@@ -313,63 +335,115 @@ __global__ void __launch_bounds__(kThreads) k_cgb_update(int64_t nn, T *__restri
     }
     const T a = (T)alpha;
     double rr = 0.0, rz = 0.0;
-    GRID_STRIDE(i, nn)
-    {
-        T rv[3], z[3];
+    for (; i < nn; i += stride) {
+        T rn[3], z[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) rn[c] = ri[c] - a * qi[c];
+        prec.apply(rn, z);
+        if (i + stride < nn) load(i + stride);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const int64_t k = 3 * i + c;
-            x[k] += a * p[k];
-            rv[c] = r[k] - a * q[k];
-            r[k] = rv[c];
-            if (CLEAR) q[k] = T(0);
-        }
-        block_apply(binv, i, rv[0], rv[1], rv[2], z[0], z[1], z[2]);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            rr += (double)rv[c] * (double)rv[c];
-            rz += (double)rv[c] * (double)z[c];
+            r[3 * i + c] = rn[c];
+            if (CLEAR) q[3 * i + c] = T(0);
+            rr += (double)rn[c] * (double)rn[c];
+            rz += (double)rn[c] * (double)z[c];
         }
     }
-    const double srr = block_sum(rr, red);
-    const double srz = block_sum(rz, red);
+    block_sum2(rr, rz, red);
     if (threadIdx.x == 0) {
-        prr[blockIdx.x] = srr;
-        prz[blockIdx.x] = srz;
+        prr[blockIdx.x] = rr;
+        prz[blockIdx.x] = rz;
     }
 }
 
-template <class T>
-__global__ void __launch_bounds__(kThreads) k_cgb_dir(int64_t nn, T *__restrict__ p, const T *__restrict__ r,
+// x += alpha p; convergence test rr <= tol2; beta = rz_new / rz; p = z + beta p.
+// x is advanced here, where p is read anyway, and not in the step.  The launch
+// runs if this iteration's step did (sc->iter), not by `done`: workgroup 0 sets
+// that below, and a later workgroup must still advance its part of x.
+template <class T, bool BLOCK>
+__global__ void __launch_bounds__(kThreads) k_cg_next(int64_t nn, T *__restrict__ x, T *__restrict__ p,
+                                                      const T *__restrict__ r, const T *__restrict__ dinv,
                                                       const uint16_t *__restrict__ binv, CgScalars *sc,
-                                                      const double *__restrict__ prr,
-                                                      const double *__restrict__ prz, int count, int par)
+                                                      const double *__restrict__ prr, const double *__restrict__ prz,
+                                                      int count, double *__restrict__ buckets, int par, int j)
 {
     __shared__ double red[kThreads];
-    if (sc->done) return;
-    const double rr = sum_partials(prr, count, red);
-    const double rz = sum_partials(prz, count, red);
-    if (rr <= sc->tol2 || !isfinite(rr)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+    T pi[3], xi[3], ri[3];
+    NodePrec<BLOCK, T> prec;
+    auto load = [&](int64_t i) {
+        load3(p, i, pi);
+        load3(x, i, xi);
+        load3(r, i, ri);
+        prec.load(dinv, binv, i);
+    };
+    int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    const double rz0 = sc->rz[par], tol2 = sc->tol2, alpha = sc->alpha;
+    const int iter = sc->iter;
+    double rr = 0.0, rz = 0.0;
+    for (int k = threadIdx.x; k < count; k += kThreads) {
+        rr += prr[k];
+        rz += prz[k];
+    }
+    if (i < nn) load(i);
+    if (iter != j + 1) return;
+    block_sum2(rr, rz, red);
+    const bool stop = rr <= tol2 || !isfinite(rr);
+    const double beta = rz / rz0;
+    if (blockIdx.x == 0) {
+        buckets[threadIdx.x] = 0.0;   // of the next tangent action
+        if (threadIdx.x == 0) {
             sc->rr = rr;
-            sc->done = 1;
+            if (stop) {
+                sc->done = 1;
+            } else {
+                sc->rz[par ^ 1] = rz;
+                sc->beta = beta;
+            }
         }
-        return;
     }
-    const double beta = rz / sc->rz[par];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->rz[par ^ 1] = rz;
-        sc->rr = rr;
-        sc->beta = beta;
-    }
-    const T bt = (T)beta;
-    GRID_STRIDE(i, nn)
-    {
-        T z[3];
-        block_apply(binv, i, r[3 * i], r[3 * i + 1], r[3 * i + 2], z[0], z[1], z[2]);
+    const T a = (T)alpha, bt = (T)beta;
+    for (; i < nn; i += stride) {
+        T xn[3], pn[3], z[3];
+        prec.apply(ri, z);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) p[3 * i + c] = z[c] + bt * p[3 * i + c];
+        for (int c = 0; c < 3; ++c) {
+            xn[c] = xi[c] + a * pi[c];
+            pn[c] = z[c] + bt * pi[c];
+        }
+        if (i + stride < nn) load(i + stride);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[3 * i + c] = xn[c];
+            if (!stop) p[3 * i + c] = pn[c];
+        }
     }
+}
+
+// Where each node's sum lies under the halo scatter: (first slot, slots), or
+// slots = 0 for a node of one block, whose sum the block pass stores itself.
+__global__ void __launch_bounds__(kThreads) k_halo_index(HaloSegs seg, const int32_t *__restrict__ gptr,
+                                                         const int32_t *__restrict__ node, int2 *__restrict__ shared)
+{
+    GRID_STRIDE(i, seg.n)
+    {
+        int k0, cnt;
+        if (i < seg.start[kSegMax + 1]) {
+            cnt = 2;
+            for (int c = 3; c <= kSegMax; ++c)
+                if (i >= seg.start[c]) cnt = c;
+            k0 = seg.base[cnt] + cnt * (int)(i - seg.start[cnt]);
+        } else {
+            const int64_t k = i - seg.start[kSegMax + 1];
+            k0 = gptr[k];
+            cnt = gptr[k + 1] - k0;
+        }
+        shared[node[i]] = make_int2(k0, cnt);
+    }
+}
+__global__ void __launch_bounds__(kThreads) k_halo_index_clear(int64_t nn, int2 *__restrict__ shared)
+{
+    GRID_STRIDE(i, nn) shared[i] = make_int2(0, 0);
 }
 
 template <class T>
@@ -491,7 +565,7 @@ hipError_t CgLaunch<T>::init(const double *b, double sign, const T *dinv, const 
         hipLaunchKernelGGL(k_cg_init<T>, dim3(g), dim3(kThreads), 0, s, n, b, sign, dinv, nmask, x, r,
                            p, q, ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks);
     hipLaunchKernelGGL(k_cg_init_fin, dim3(1), dim3(kThreads), 0, s, ws.partials + kMaxRedBlocks,
-                       ws.partials + 2 * kMaxRedBlocks, g, sc, eta2);
+                       ws.partials + 2 * kMaxRedBlocks, g, sc, eta2, ws.buckets());
     return hipGetLastError();
 }
 
@@ -503,34 +577,24 @@ hipError_t CgLaunch<T>::pq(const T *p, const T *q, CgScalars *sc) const
 }
 
 template <class T>
-hipError_t CgLaunch<T>::update(T *x, T *r, const T *p, T *q, const T *dinv, CgScalars *sc, int j) const
+hipError_t CgLaunch<T>::step(T *r, T *q, const T *dinv, CgScalars *sc, int j) const
 {
-    const int gpq = red_grid(n);   // partials of k_cg_pq
-    if (binv) {
-        const int g = red_grid(n / 3);
-        auto kern = clear_q ? k_cgb_update<T, true> : k_cgb_update<T, false>;
-        hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, s, n / 3, x, r, p, q, binv, sc, ws.partials, gpq,
-                           ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks, j & 1, j);
-        return hipGetLastError();
-    }
-    auto kern = clear_q ? k_cg_update<T, true> : k_cg_update<T, false>;
-    hipLaunchKernelGGL(kern, dim3(gpq), dim3(kThreads), 0, s, n, x, r, p, q, dinv, sc, ws.partials, gpq,
-                       ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks, j & 1, j);
+    const int64_t nn = n / 3;
+    auto kern = binv ? (clear_q ? k_cg_step<T, true, true> : k_cg_step<T, true, false>)
+                     : (clear_q ? k_cg_step<T, false, true> : k_cg_step<T, false, false>);
+    hipLaunchKernelGGL(kern, dim3(red_grid(nn)), dim3(kThreads), 0, s, nn, r, q, dinv, binv, shared, halo, nmask, sc,
+                       ws.buckets(), ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks, j & 1, j);
     return hipGetLastError();
 }
 
 template <class T>
-hipError_t CgLaunch<T>::dir(T *p, const T *r, const T *dinv, CgScalars *sc, int j) const
+hipError_t CgLaunch<T>::next(T *x, T *p, const T *r, const T *dinv, CgScalars *sc, int j) const
 {
-    if (binv) {
-        const int g = red_grid(n / 3);
-        hipLaunchKernelGGL(k_cgb_dir<T>, dim3(g), dim3(kThreads), 0, s, n / 3, p, r, binv, sc,
-                           ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks, g, j & 1);
-        return hipGetLastError();
-    }
-    const int g = red_grid(n);
-    hipLaunchKernelGGL(k_cg_dir<T>, dim3(g), dim3(kThreads), 0, s, n, p, r, dinv, sc,
-                       ws.partials + kMaxRedBlocks, ws.partials + 2 * kMaxRedBlocks, g, j & 1);
+    const int64_t nn = n / 3;
+    const int g = red_grid(nn);
+    auto kern = binv ? k_cg_next<T, true> : k_cg_next<T, false>;
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, s, nn, x, p, r, dinv, binv, sc, ws.partials + kMaxRedBlocks,
+                       ws.partials + 2 * kMaxRedBlocks, g, ws.buckets(), j & 1, j);
     return hipGetLastError();
 }
 
@@ -590,6 +654,13 @@ hipError_t CgLaunch<T>::apply_predictor(const double *u_old, const double *dc, c
 {
     hipLaunchKernelGGL(k_apply_predictor<T>, dim3(red_grid(n)), dim3(kThreads), 0, s, n, u_old, dc,
                        df, nmask, use_df ? 1 : 0, u);
+    return hipGetLastError();
+}
+
+hipError_t launch_halo_index(hipStream_t s, int64_t n_nodes, const HaloMap &hm, int2 *shared)
+{
+    hipLaunchKernelGGL(k_halo_index_clear, dim3(red_grid(n_nodes)), dim3(kThreads), 0, s, n_nodes, shared);
+    hipLaunchKernelGGL(k_halo_index, dim3(red_grid(hm.seg.n)), dim3(kThreads), 0, s, hm.seg, hm.gptr, hm.node, shared);
     return hipGetLastError();
 }
 
@@ -695,11 +766,10 @@ __global__ void __launch_bounds__(kThreads) k_fcg_update(int64_t n, T *__restric
         rr += (double)ri * (double)ri;
         rzo += (double)ri * (double)zold[i];
     }
-    const double s0 = block_sum(rr, red);
-    const double s1 = block_sum(rzo, red);
+    block_sum2(rr, rzo, red);
     if (threadIdx.x == 0) {
-        prr[blockIdx.x] = s0;
-        prz[blockIdx.x] = s1;
+        prr[blockIdx.x] = rr;
+        prz[blockIdx.x] = rzo;
     }
 }
 
@@ -716,8 +786,8 @@ __global__ void __launch_bounds__(kThreads) k_fcg_dir(int64_t n, T *__restrict__
 {
     __shared__ double red[kThreads];
     if (sc->done) return;
-    const double rr = sum_partials(prr, count, red);
-    const double rzo = sum_partials(przo, count, red);
+    double rr, rzo;
+    sum_partials2(prr, przo, count, red, rr, rzo);
     const double rzn = sum_partials(przn, nz, red);
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     if (rr <= sc->tol2 || !isfinite(rr)) {

@@ -45,6 +45,7 @@ struct Solver {
     std::vector<void *> bufs;
     double *r = nullptr, *dc = nullptr, *u_old = nullptr, *u_trial = nullptr, *diag = nullptr,
            *kdc = nullptr, *dscal = nullptr;
+    int2 *shared = nullptr;   // the halo map by node
     T *x = nullptr, *rv = nullptr, *p = nullptr, *q = nullptr, *dinv = nullptr;
     double *off = nullptr;   // precond = 2: off-diagonals of the nodes' 3x3 blocks
     uint16_t *binv = nullptr;   // and their inverses [n_nodes][6], bfloat16
@@ -82,7 +83,7 @@ struct Solver {
             || (rc = alloc(&u_trial, n)) || (rc = alloc(&diag, n)) || (rc = alloc(&kdc, n))
             || (rc = alloc(&dscal, 4)) || (rc = alloc(&x, n)) || (rc = alloc(&rv, n))
             || (rc = alloc(&p, n)) || (rc = alloc(&q, n)) || (rc = alloc(&dinv, n))
-            || (rc = alloc(&sc, 1)) || (rc = alloc(&ws.partials, 4 * kMaxRedBlocks)))
+            || (rc = alloc(&sc, 1)) || (rc = alloc(&ws.partials, 4 * kMaxRedBlocks + kPqBuckets)))
             return rc;
         if (o.precond == 2 && ((rc = alloc(&off, n)) || (rc = alloc(&binv, 2 * n)))) return rc;   // 6 per node
         if (!c.xlin) {
@@ -101,6 +102,13 @@ struct Solver {
         TRY(hipHostMalloc((void **)&h_scal, 4 * sizeof(double), hipHostMallocDefault));
         L = CgLaunch<T>{n, c.stream, ws};
         L.clear_q = c.scatter == Scatter::Atomic;
+        const void *slots;
+        if (const HaloMap *hm = hvp_halo(c, std::is_same<T, double>::value, &slots)) {
+            if ((rc = alloc(&shared, (size_t)c.n_nodes))) return rc;
+            TRY(launch_halo_index(c.stream, c.n_nodes, *hm, shared));
+            L.shared = shared;
+            L.halo = static_cast<const T *>(slots);
+        }
         return EFEM_OK;
     }
 
@@ -148,15 +156,24 @@ struct Solver {
         return EFEM_OK;
     }
 
-    // The single-launch form: under the halo and colour scatters it writes
-    // every entry of q; under the atomic scatter it adds into a q that the
-    // CG init/update kernels have cleared (clear_q)
-    hipError_t hvp_acc(const T *v, T *y, const int32_t *skip)
+    // Under the atomic scatter the action adds into a q that the CG kernels
+    // have cleared (clear_q); mode Krylov leaves p.q in the buckets
+    hipError_t hvp(const T *v, T *y, const int32_t *skip, WriteMode mode)
     {
         if constexpr (std::is_same<T, double>::value)
-            return launch_hvp_f64(c, c.xlin, v, y, skip, WriteMode::Zeroed);
+            return launch_hvp_f64(c, c.xlin, v, y, skip, mode, ws.buckets());
         else
-            return launch_hvp_f32(c, c.ulin, v, y, skip, WriteMode::Zeroed);
+            return launch_hvp_f32(c, c.ulin, v, y, skip, mode, ws.buckets());
+    }
+
+    // one PCG iteration
+    int iterate(int j)
+    {
+        L.nmask = c.m.nmask;
+        TRY(hvp(p, q, &sc->done, WriteMode::Krylov));
+        TRY(L.step(rv, q, dinv, sc, j));
+        TRY(L.next(x, p, rv, dinv, sc, j));
+        return EFEM_OK;
     }
 
     // Jacobi-PCG for K_ff x = sign * b from x = 0; dinv must be set.
@@ -164,14 +181,10 @@ struct Solver {
     {
         TRY(L.init(b, sign, dinv, c.m.nmask, x, rv, p, q, sc, eta * eta));
         const int every = std::max(1, o.check_every);
-        int j = 0;
+        int j = 0, rc;
         for (;;) {
-            for (int k = 0; k < every; ++k, ++j) {
-                TRY(hvp_acc(p, q, &sc->done));
-                TRY(L.pq(p, q, sc));
-                TRY(L.update(x, rv, p, q, dinv, sc, j));
-                TRY(L.dir(p, rv, dinv, sc, j));
-            }
+            for (int k = 0; k < every; ++k, ++j)
+                if ((rc = iterate(j))) return rc;
             TRY(hipMemcpyAsync(h_sc, sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c.stream));
             TRY(hipStreamSynchronize(c.stream));
             if (h_sc->done || h_sc->iter >= max_it) break;
@@ -200,7 +213,7 @@ struct Solver {
         int j = 0;
         for (;;) {
             for (int k = 0; k < every; ++k, ++j) {
-                TRY(hvp_acc(p, q, &sc->done));
+                TRY(hvp(p, q, &sc->done, WriteMode::Zeroed));
                 TRY(L.pq(p, q, sc));
                 TRY(F.update(x, rv, p, q, M.z, sc, j));
                 TRY(mlp_precondition(c, M, rv, M.z));
@@ -285,10 +298,7 @@ struct Solver {
                 ++k;
             }
             if (k == nsnap) break;
-            TRY(hvp_acc(p, q, &sc->done));
-            TRY(L.pq(p, q, sc));
-            TRY(L.update(x, rv, p, q, dinv, sc, j));
-            TRY(L.dir(p, rv, dinv, sc, j));
+            if ((rc = iterate(j))) return rc;
         }
         TRY(hipMemcpyAsync(h_sc, sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c.stream));
         TRY(hipStreamSynchronize(c.stream));

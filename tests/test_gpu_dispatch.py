@@ -172,3 +172,39 @@ def test_hexahedra_at_lane_remainders(n, block, model):
     for got, want in zip(op.residual_vjp_material(dev(u), dev(v)), orc.residual_vjp_material(u, v)):
         assert rel(got.cpu(), want) <= 1e-10
     assert rel(op.grad_coords(dev(u)).cpu(), orc.grad_coords(u).reshape(-1, 3)) <= 1e-10
+
+
+@pytest.mark.parametrize("scatter", ["halo", "color", "atomic"])
+@pytest.mark.parametrize("elem,n,block", [(I.TET4, 1, 0), (I.TET4, 4, 0), (I.TET4, 4, 40), (I.HEX8, 2, 0),
+                                          (I.HEX8, 4, 7), (I.TRI3, 6, 9)])
+def test_krylov_iterations_by_scatter(elem, n, block, scatter):
+    """PCG whose step sums the shared nodes' halo slots (or reads every node,
+    on one block and under the other scatters), with both preconditioners and
+    models: the true residual meets the tolerance (rtol 1e-9, and the FP64
+    recursion's drift, 1e-10), an FP32 solve its own accuracy (1e-4), b = 0
+    gives 0, and a cap of one iteration returns after the first check."""
+    from paper_2602_12365_amd import Operator
+    m = I.make_mesh(elem, n)
+    m = I.scrambled_mesh(m, 8) if elem != I.TRI3 and n > 1 else m
+    g = np.random.default_rng(2)
+    mu = np.exp(0.3 * g.standard_normal(m.n_elems))
+    mask = I.clamp_planar(m.X, 0.1)[0] if elem == I.TRI3 else (m.X[:, 2:] < 1e-9).repeat(3, 1).astype(np.uint8).ravel()
+    free = 1.0 - mask.reshape(-1, 3)
+    u = 0.005 / n * g.standard_normal((m.n_nodes, 3)) * free
+    b = g.standard_normal((m.n_nodes, 3))
+    for model in ("neo_hookean", "linear"):
+        op = Operator(elem, m.X, m.conn, scatter=scatter, block_elems=block, model=model)
+        op.set_material(dev(mu), dev(1.5 * mu))
+        op.set_dirichlet(dev(mask))
+        orc = F.FEM(elem, m.X, m.conn, mu, 1.5 * mu, model=model)
+        bn = np.linalg.norm(b * free)
+        for precond in (0, 2):
+            x, it, _ = op.linear_solve(dev(u), dev(b), rtol=1e-9, precond=precond)
+            x = x.cpu().numpy()
+            assert it > 0 and np.all(x[mask.reshape(-1, 3) == 1] == 0.0)
+            assert np.linalg.norm((b - orc.hvp(u, x)) * free) <= (1e-9 + 1e-10) * bn
+            x32 = op.linear_solve(dev(u), dev(b), rtol=1e-6, hvp_prec="f32", precond=precond)[0].cpu().numpy()
+            assert np.abs(x32 - x).max() <= 1e-4 * np.abs(x).max()
+            assert float(op.linear_solve(dev(u), dev(0.0 * b), precond=precond)[0].abs().max()) == 0.0
+            assert op.linear_solve(dev(u), dev(b), rtol=1e-9, precond=precond, max_iter=1)[1] <= 8
+        op.close()
