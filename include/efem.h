@@ -93,7 +93,8 @@ typedef struct efem_ctx efem_ctx;
 
 typedef struct {
     int32_t block_elems;   /* max elements per workgroup block (the paper's batch
-                              size N_B, Alg. 1); 0 = default for the element type */
+                              size N_B, Alg. 1); 0 = default for the element type
+                              and the mesh size */
     int32_t block_nodes;   /* max distinct nodes per block (<= 768, so that two
                               blocks fit a CU's 160 KB of LDS); 0 = default */
     int32_t scatter;       /* EFEM_SCATTER_HALO (0, default), _COLOR or _ATOMIC */
@@ -103,7 +104,9 @@ typedef struct {
                               (5 nodes instead of 8), which results do not depend on
                               beyond rounding */
     int32_t no_chunks;     /* EFEM_TET4, halo scatter: nonzero = the FP64 tangent
-                              action runs block by block.  By default runs of
+                              action runs block by block.  Otherwise, on meshes
+                              of more than two default blocks per CU and wherever
+                              block_elems is given, runs of
                               consecutive blocks form chunks whose nodes stay
                               resident in one workgroup's LDS (the whole 160 KB of
                               a CU) while the blocks stream through, the next

@@ -230,9 +230,18 @@ static int pair_tets(const double *X, const int32_t *conn, std::vector<int32_t> 
     return np;
 }
 
-// Default elements per block.
-// Tetrahedra: 1536 (768 pairs) within 600 nodes; triangles: 768 within 600 nodes
-// (measured on 64^3 and 1024^2 cells).
+// Default elements per block, by mesh size.  Small meshes in large blocks leave
+// CUs idle and give each thread several elements in a row; small blocks stage
+// and gather more shared nodes.
+// Tetrahedra: two blocks per CU (512), of 384 to 1536 elements: FP64 tangent
+// action 24^3 13.4 us in 1536s, 8.9 in 384s; 32^3 11.6 and 9.4; 40^3 14.6 and 13.9
+// in 750s.  Larger meshes run in chunks (build_chunks), one per CU if they fit
+// its LDS, whose blocks are the steps: equal steps of at most 1536, so that a
+// block with unpaired tetrahedra stays within the pass's 768 items: 56^3 29 us
+// in 1536s (no chunks), 21 in 1372s; 80^3 59 and 46; 64^3 has exactly 1536.
+// Triangles: 256 up to 2^18 (256^2 cells 9.2 us in 768s, 7.4), then 512 (1024^2
+// 39.6 and 37.7); 768 for one block, and beyond 2^24 (the block count that
+// efem_energy_noalloc's 65,536 partials can hold).
 // Hexahedra (an element on four lanes, so 64 of them fill a workgroup's four
 // waves): the smallest of 64, 128 and 256 that leaves at most two blocks per
 // CU, else 256.  A mesh in few blocks leaves CUs idle, small blocks stage more
@@ -241,10 +250,14 @@ static int pair_tets(const double *X, const int32_t *conn, std::vector<int32_t> 
 // 10.0, 13.9, 21.3; 64^3 39.8, 37.8, 38.5; 96^3 102 in 256s, 159 in 512s.
 // Beyond 2^23 hexahedra 512 (even at 128^3: 231 and 234), which keeps the block
 // count of every mesh that efem_energy_noalloc's 65,536 partials can hold.
-static int default_block_elems(int elem, int64_t ne)
+static int default_block_elems(int elem, int64_t ne, int n_cu)
 {
-    if (elem == EFEM_TET4) return 1536;
-    if (elem == EFEM_TRI3) return 768;
+    if (elem == EFEM_TET4) {
+        if (ne <= 512 * 1536) return (int)std::max<int64_t>(384, (ne + 511) / 512);
+        const int64_t per = (ne + n_cu - 1) / n_cu, steps = (per + 1535) / 1536;
+        return steps > 8 ? 1536 : (int)((per + steps - 1) / steps);
+    }
+    if (elem == EFEM_TRI3) return ne <= 768 ? 768 : (ne <= (1 << 18) ? 256 : (ne <= (1 << 24) ? 512 : 768));
     for (int be : {64, 128})
         if (ne <= 512 * (int64_t)be) return be;
     return ne <= ((int64_t)1 << 23) ? 256 : 512;
@@ -504,6 +517,9 @@ static bool try_chunks(const HostBlocks &hb, int64_t nn, int n, HostChunks &hc)
     return true;
 }
 
+// Chunks are tried on default blocks when there are more than two per CU (with
+// fewer a chunk is one or two steps, its loads hidden by nothing: 8^3 to 32^3
+// took 0.4 to 3 us more than the block pass), and always on a caller's blocks.
 // Chunk count: a multiple of the CU count (one resident chunk per CU, all of
 // them in one round when it fits), the smallest whose chunks fit the LDS; one
 // block per chunk always fits.  False if the pass does not apply: blocks with
@@ -825,7 +841,11 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
         set_error("efem_create: reference element with det J <= 0");
         return EFEM_ERR_INVERTED;
     }
-    int be = default_block_elems(elem, n_elems);
+    int dev = 0, lds_max = 0, n_cu = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    int be = default_block_elems(elem, n_elems, std::max(n_cu, 1));
     int bn = elem == EFEM_HEX8 ? 768 : 600;
     int scatter = EFEM_SCATTER_HALO;
     int threads = 256;
@@ -882,12 +902,10 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
     };
     // chunks for the LDS-resident FP64 tangent action (Tet4 pairs, halo
     // scatter), built before the uploads: the item order follows them
-    int lds_max = 0, n_cu = 0;
-    (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device);
-    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device);
     HostChunks hc;
+    const bool sized = opts && opts->block_elems > 0;   // the caller's blocks: chunks whenever they fit
     const bool use_chunks = elem == EFEM_TET4 && ctx->scatter == Scatter::Halo && !(opts && opts->no_chunks)
-                            && n_nodes <= (int64_t)kStageGid && lds_max >= kChunkLds + kChunkPqLds
+                            && (sized || (int)hb.estart.size() - 1 > 2 * n_cu) && n_nodes <= (int64_t)kStageGid && lds_max >= kChunkLds + kChunkPqLds
                             && build_chunks(hb, n_nodes, n_cu, hc);
     if (use_chunks) spread_items_chunks(hb, hc);
     else spread_items_blocks(hb, elem);

@@ -208,3 +208,34 @@ def test_krylov_iterations_by_scatter(elem, n, block, scatter):
             assert float(op.linear_solve(dev(u), dev(0.0 * b), precond=precond)[0].abs().max()) == 0.0
             assert op.linear_solve(dev(u), dev(b), rtol=1e-9, precond=precond, max_iter=1)[1] <= 8
         op.close()
+
+
+@pytest.mark.parametrize("elem,n,chunks", [
+    (I.TRI3, 19, False), (I.TRI3, 20, False), (I.TRI3, 362, False), (I.TRI3, 363, False), (I.TET4, 3, False),
+    (I.TET4, 4, False), (I.TET4, 5, False), (I.TET4, 32, False), (I.TET4, 33, False), (I.TET4, 50, False),
+    (I.TET4, 51, True), (I.TET4, 57, True), (I.HEX8, 32, False), (I.HEX8, 33, False)])
+def test_default_blocks_by_mesh_size(elem, n, chunks):
+    """Default block sizes and the choice of the chunk pass at the edges of
+    their rules (722 and 800 triangles, 2^18 and above; tetrahedra below and
+    above 384 a block, 512 blocks and two blocks per CU; hexahedra at 512
+    blocks of 64), against a caller's blocks of 300: FP64 actions, residuals
+    and diagonals within 1e-11 (sums in another order), FP32 2e-5."""
+    from paper_2602_12365_amd import Operator
+    m = I.make_mesh(elem, n)
+    dim = m.X.shape[1]
+    g = np.random.default_rng(n)
+    u, v = (dev(s * g.standard_normal((m.n_nodes, dim))) for s in (0.01 / n, 1.0))
+    mu = dev(np.exp(0.3 * g.standard_normal(m.n_elems)))
+    a, b = (Operator(elem, m.X, m.conn, block_elems=be, chunks=be == 0) for be in (0, 300))
+    assert (a.info()["n_chunks"] > 0) == chunks
+    for op in (a, b):
+        op.set_material(mu, 1.5 * mu)
+    for what in (lambda op: op.residual(u), lambda op: op.jacobi_diag(u),
+                 lambda op: (op.linearize(u, "f64"), op.hvp(v))[1]):
+        assert rel(what(a).cpu(), what(b).cpu()) <= 1e-11
+    for op in (a, b):
+        op.linearize(u, "f32")
+    assert rel(a.hvp(v.float()).cpu(), b.hvp(v.float()).cpu()) <= 2e-5
+    assert abs(float(a.energy(u)) - float(b.energy(u))) <= 1e-12 * abs(float(b.energy(u)))
+    a.close()
+    b.close()
