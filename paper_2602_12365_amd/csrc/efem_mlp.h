@@ -44,10 +44,9 @@ constexpr int kEnergyBlocks = 512;
 
 hipError_t mlp_features_static(hipStream_t s, const MlpState &M, int64_t n, const double *diag,
                                const uint8_t *nmask, uint16_t *X);
-// dinv and g4 = (dinv r, |dinv r|^2) at once
-hipError_t mlp_dinv_g4(hipStream_t s, int64_t n, const double *diag, const uint8_t *nmask, const float *r,
-                       float *dinv, float4 *g4);
-// r = null: g4 is there already
+// M.dinv, M.g4 = (dinv r, |dinv r|^2), both kinds of features and M.scale at once
+hipError_t mlp_features(hipStream_t s, const MlpState &M, int64_t n, const double *diag, const uint8_t *nmask,
+                        const float *r, uint16_t *X);
 hipError_t mlp_features_dyn(hipStream_t s, const MlpState &M, int64_t n, const float *r,
                             const float *dinv, uint16_t *X, float *scale, float4 *g4);
 // H1, H2 (both or neither): the hidden layers' bf16 activations [n][64]

@@ -48,6 +48,40 @@ __device__ __forceinline__ float softplus(float x)
 
 // ------------------------------------------------------------------ features
 
+// Static features of node i into slots 6..15: its diagonal di, the sums sd over
+// its closed 1-ring, its own prescribed components and its neighbours' (sm).
+__device__ __forceinline__ void store_static(uint16_t *__restrict__ X, int64_t i, int deg, const double di[3],
+                                             const double sd[3], int mi, int sm)
+{
+    uint16_t x[10];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = f2bf((float)log(di[c] / (sd[c] / (deg + 1))));
+    x[3] = f2bf((float)mi / 3.f);
+    x[4] = f2bf((float)sm / (3.f * (float)max(deg, 1)));
+    x[5] = f2bf((float)deg / 26.f);
+    x[6] = x[7] = x[8] = x[9] = 0;
+    uint32_t *o = reinterpret_cast<uint32_t *>(X + i * kInPad + 6);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) o[k] = (uint32_t)x[2 * k] | (uint32_t)x[2 * k + 1] << 16;
+}
+
+// Dynamic features of node i into slots 0..5 and its scale: its g, the sums s of
+// its neighbours' g, and q = |g|^2 over its closed 1-ring.
+__device__ __forceinline__ void store_dynamic(uint16_t *__restrict__ X, float *__restrict__ s_out, int64_t i, int deg,
+                                              const float4 gi, float s0, float s1, float s2, float q)
+{
+    const float s = sqrtf(q / (3.f * (float)(deg + 1)));
+    uint16_t *x = X + i * kInPad;
+    if (s > 0.f) {
+        const float rs = 1.f / s, rd = rs / (float)max(deg, 1);
+        x[0] = f2bf(gi.x * rs), x[1] = f2bf(gi.y * rs), x[2] = f2bf(gi.z * rs);
+        x[3] = f2bf(s0 * rd), x[4] = f2bf(s1 * rd), x[5] = f2bf(s2 * rd);
+    } else {
+        x[0] = x[1] = x[2] = x[3] = x[4] = x[5] = 0;
+    }
+    s_out[i] = s;
+}
+
 // Static features (depend on the Jacobi diagonal and the mask only): slots
 // 6..15.  Bound by the gather of the neighbours' diagonals from L2.  The
 // 1-ring comes column-major (ell, as in k_feat_dyn), so each step's indices are
@@ -89,17 +123,7 @@ __global__ void __launch_bounds__(256) k_feat_static(int64_t n, const int64_t *_
         sd[0] += diag[3 * j], sd[1] += diag[3 * j + 1], sd[2] += diag[3 * j + 2];
         if (MASK) sm += __popc(nmask[j]);
     }
-    uint16_t x[10];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) x[c] = f2bf((float)log(di[c] / (sd[c] / (deg + 1))));
-    const float mi = MASK ? (float)__popc(nmask[i]) : 0.f;
-    x[3] = f2bf(mi / 3.f);
-    x[4] = f2bf((float)sm / (3.f * (float)max(deg, 1)));
-    x[5] = f2bf((float)deg / 26.f);
-    x[6] = x[7] = x[8] = x[9] = 0;
-    uint32_t *o = reinterpret_cast<uint32_t *>(X + i * kInPad + 6);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) o[k] = (uint32_t)x[2 * k] | (uint32_t)x[2 * k + 1] << 16;
+    store_static(X, i, deg, di, sd, MASK ? __popc(nmask[i]) : 0, sm);
 }
 
 // g = D^-1 r per node with |g|^2, one 16-byte record each, so that the
@@ -125,7 +149,6 @@ __global__ void k_feat_dyn(int64_t n, const int64_t *__restrict__ ptr, const int
     if (i >= n) return;
     const int deg = (int)(ptr[i + 1] - ptr[i]);
     const float4 gi = g4[i];
-    const float g0 = gi.x, g1 = gi.y, g2 = gi.z;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, q = gi.w;
     int k = 0;
     for (; k + 8 <= max_deg; k += 8) {   // four pairs in flight
@@ -157,16 +180,69 @@ __global__ void k_feat_dyn(int64_t n, const int64_t *__restrict__ ptr, const int
         s2 += a.z;
         q += a.w;
     }
-    const float s = sqrtf(q / (3.f * (float)(deg + 1)));
-    uint16_t *x = X + i * kInPad;
-    if (s > 0.f) {
-        const float rs = 1.f / s, rd = rs / (float)max(deg, 1);
-        x[0] = f2bf(g0 * rs), x[1] = f2bf(g1 * rs), x[2] = f2bf(g2 * rs);
-        x[3] = f2bf(s0 * rd), x[4] = f2bf(s1 * rd), x[5] = f2bf(s2 * rd);
-    } else {
-        x[0] = x[1] = x[2] = x[3] = x[4] = x[5] = 0;
+    store_dynamic(X, s_out, i, deg, gi, s0, s1, s2, q);
+}
+
+// Both at once, for an apply or training rows at a new diagonal: the 1-ring's
+// indices are read once, and a neighbour's diagonal, mask and g4 are in flight
+// together.  The sums run in the order of the two kernels above.  Bound by the
+// gather's loads (41 bytes in four loads a neighbour): 25 us for 274,625 nodes of
+// 26 neighbours, 30.5 us for the two kernels; the same within 1 us with two to
+// eight neighbours in flight (eight: 3 waves per SIMD with 64-bit indices, 33 us).
+template <bool MASK>
+__global__ void __launch_bounds__(256) k_feat_all(int64_t n, const int64_t *__restrict__ ptr,
+                                                  const int32_t *__restrict__ ell, int max_deg,
+                                                  const double *__restrict__ diag, const uint8_t *__restrict__ nmask,
+                                                  const float4 *__restrict__ g4, uint16_t *__restrict__ X,
+                                                  float *__restrict__ s_out)
+{
+    constexpr int kB = 4;   // neighbours in flight
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int deg = (int)(ptr[i + 1] - ptr[i]);
+    const float4 gi = g4[i];
+    const double di[3] = {diag[3 * i], diag[3 * i + 1], diag[3 * i + 2]};
+    double sd[3] = {di[0], di[1], di[2]};
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, q = gi.w;
+    int sm = 0;
+    auto add = [&](const float4 *v, const double (*d)[3], const int *m, int b) {
+        s0 += v[b].x + v[b + 1].x;
+        s1 += v[b].y + v[b + 1].y;
+        s2 += v[b].z + v[b + 1].z;
+        q += v[b].w + v[b + 1].w;
+#pragma unroll
+        for (int e = b; e < b + 2; ++e) {
+            sd[0] += d[e][0], sd[1] += d[e][1], sd[2] += d[e][2];
+            if (MASK) sm += __popc(m[e]);
+        }
+    };
+    // one neighbour's values; past the node's own ring (j = n) all are zero
+    auto load = [&](int32_t j, float4 &v, double d[3], int &m) {
+        v = g4[j];
+        const bool in = j < n;
+        const int32_t jj = in ? j : (int32_t)i;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double t = diag[3 * (int64_t)jj + c];
+            d[c] = in ? t : 0.0;
+        }
+        const int t = MASK ? nmask[jj] : 0;
+        m = in ? t : 0;
+    };
+    for (int k = 0; k < max_deg; k += kB) {
+        int32_t j[kB];
+        float4 v[kB];
+        double d[kB][3];
+        int m[kB];
+#pragma unroll
+        for (int b = 0; b < kB; ++b) j[b] = k + b < max_deg ? ell[(int64_t)(k + b) * n + i] : (int32_t)n;
+#pragma unroll
+        for (int b = 0; b < kB; ++b) load(j[b], v[b], d[b], m[b]);
+#pragma unroll
+        for (int b = 0; b < kB; b += 2) add(v, d, m, b);
     }
-    s_out[i] = s;
+    store_static(X, i, deg, di, sd, MASK ? __popc(nmask[i]) : 0, sm);
+    store_dynamic(X, s_out, i, deg, gi, s0, s1, s2, q);
 }
 
 // ------------------------------------------------------------- MLP forward
@@ -947,17 +1023,19 @@ hipError_t mlp_features_static(hipStream_t s, const MlpState &M, int64_t n, cons
     return hipGetLastError();
 }
 
-hipError_t mlp_dinv_g4(hipStream_t s, int64_t n, const double *diag, const uint8_t *nmask, const float *r,
-                       float *dinv, float4 *g4)
+hipError_t mlp_features(hipStream_t s, const MlpState &M, int64_t n, const double *diag, const uint8_t *nmask,
+                        const float *r, uint16_t *X)
 {
-    hipLaunchKernelGGL(k_dinv_g4, dim3(g256(n)), dim3(256), 0, s, n, diag, nmask, r, dinv, g4);
+    hipLaunchKernelGGL(k_dinv_g4, dim3(g256(n)), dim3(256), 0, s, n, diag, nmask, r, M.dinv, M.g4);
+    auto kern = nmask ? k_feat_all<true> : k_feat_all<false>;
+    hipLaunchKernelGGL(kern, dim3(g256(n)), dim3(256), 0, s, n, M.ptr, M.ell, M.max_deg, diag, nmask, M.g4, X, M.scale);
     return hipGetLastError();
 }
 
 hipError_t mlp_features_dyn(hipStream_t s, const MlpState &M, int64_t n, const float *r,
                             const float *dinv, uint16_t *X, float *scale, float4 *g4)
 {
-    if (r) hipLaunchKernelGGL(k_g4, dim3(g256(n)), dim3(256), 0, s, n, r, dinv, g4);
+    hipLaunchKernelGGL(k_g4, dim3(g256(n)), dim3(256), 0, s, n, r, dinv, g4);
     hipLaunchKernelGGL(k_feat_dyn, dim3(g256(n)), dim3(256), 0, s, n, M.ptr, M.ell, M.max_deg, g4, X, scale);
     return hipGetLastError();
 }

@@ -170,9 +170,7 @@ int efem_precond_apply(efem_ctx *ctx, const float *r, const double *diag, float 
         return EFEM_ERR_STATE;
     }
     const int64_t n = ctx->n_nodes;
-    TRY(mlp_dinv_g4(ctx->stream, n, diag, ctx->m.nmask, r, M->dinv, M->g4));
-    TRY(mlp_features_static(ctx->stream, *M, n, diag, ctx->m.nmask, M->X));
-    TRY(mlp_features_dyn(ctx->stream, *M, n, nullptr, M->dinv, M->X, M->scale, M->g4));
+    TRY(mlp_features(ctx->stream, *M, n, diag, ctx->m.nmask, r, M->X));
     TRY(mlp_apply(ctx->stream, M->W, n, M->X, r, M->dinv, M->scale, z, M->prz));
     return EFEM_OK;
 }
@@ -189,9 +187,7 @@ int efem_precond_rows(efem_ctx *ctx, const float *b, const double *diag, const f
         set_error("efem_precond_rows: call efem_set_mlp first (builds the node graph)");
         return EFEM_ERR_STATE;
     }
-    TRY(mlp_dinv_f32(ctx->stream, 3 * ctx->n_nodes, diag, ctx->m.nmask, M->dinv));
-    TRY(mlp_features_static(ctx->stream, *M, ctx->n_nodes, diag, ctx->m.nmask, X));
-    TRY(mlp_features_dyn(ctx->stream, *M, ctx->n_nodes, b, M->dinv, X, M->scale, M->g4));
+    TRY(mlp_features(ctx->stream, *M, ctx->n_nodes, diag, ctx->m.nmask, b, X));
     TRY(mlp_rows_aux(ctx->stream, ctx->n_nodes, b, M->dinv, t, M->scale, M->tt, n_total, aux));
     return EFEM_OK;
 }

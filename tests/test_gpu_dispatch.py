@@ -239,3 +239,41 @@ def test_default_blocks_by_mesh_size(elem, n, chunks):
     assert abs(float(a.energy(u)) - float(b.energy(u))) <= 1e-12 * abs(float(b.energy(u)))
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("mesh", ["tet1", "tet3s", "hex1", "hex3s", "fan9"])
+def test_features_at_ragged_rings(mesh, masked):
+    """Both kinds of node features in one pass, on 1-rings of 3 to 26 nodes
+    (the fan: a hub of 10, rims of 4), whose lengths leave every remainder of
+    the pass's four neighbours: within one bfloat16 ulp of the float64 features
+    (FP32 sums lie within 1e-6 of them, which can cross one rounding boundary)."""
+    from oracle import precond as P
+    from paper_2602_12365_amd import Operator, precond as PC
+    elem = I.HEX8 if mesh[:3] == "hex" else I.TET4
+    if mesh[:3] == "fan":
+        k = int(mesh[3:])
+        a = 2 * np.pi * np.arange(k) / k
+        X = np.concatenate([[[0.0, 0, 0], [0, 0, 1.0]], np.stack([np.cos(a), np.sin(a), 0 * a], 1)])
+        conn = np.stack([np.zeros(k), 2 + np.arange(k), 2 + (np.arange(k) + 1) % k, np.ones(k)], 1).astype(np.int32)
+    else:
+        m = I.make_mesh(elem, int(mesh[3]))
+        m = I.scrambled_mesh(m, 4) if mesh.endswith("s") else m
+        X, conn = m.X, m.conn
+    n = X.shape[0]
+    g = np.random.default_rng(n)
+    mask = (g.random(3 * n) < (0.3 if masked else 0.0)).astype(np.uint8)
+    op = Operator(elem, X, conn)
+    op.set_mlp(PC.init_params(1))
+    if masked:
+        op.set_dirichlet(dev(mask))
+    diag = np.exp(g.standard_normal((n, 3)))
+    r, t = (g.standard_normal((n, 3)).astype(np.float32) for _ in range(2))
+    rows, aux = op.precond_rows(dev(r), dev(diag), dev(t), 1.0)
+    ref, gref, sref = P.features(r, diag, mask, *P.node_neighbours(conn, n))
+    bits = rows.cpu().numpy().view(np.uint16).astype(np.uint32) << 16
+    got = bits.view(np.float32)[:, :12].astype(np.float64)
+    assert np.all(np.abs(got - P.bf16_round(ref.astype(np.float32))) <= 2.0 ** -7 * np.abs(ref) + 1e-6)
+    a = aux.cpu().numpy()
+    assert np.abs(a[:, :3] - gref).max() <= 1e-6 * np.abs(gref).max()
+    assert np.allclose(a[:, 9], sref, rtol=1e-5)
