@@ -205,7 +205,7 @@ struct Ctx {
     HaloMap halo;
     std::vector<Pass> passes;           // colour lists (Color) or one pass (Atomic)
     double *partials = nullptr;         // [n_blocks] per-block energy partials
-    uint32_t *counter = nullptr;        // last-block-done ticket
+    uint32_t *counter = nullptr;        // last-workgroup-done ticket, 0 between launches
     double *mu = nullptr, *lam = nullptr;
     uint8_t *nmask = nullptr;
     int32_t *flags = nullptr;

@@ -1767,6 +1767,81 @@ __device__ __forceinline__ void stage_nodes(const BlockMesh &m, const St &st, No
     }
 }
 
+// Second half of the halo scatter: shared node i = node[i] sums its halo
+// slots (its blocks or chunks in order; in FP64, so the result does not depend
+// on the schedule), then y = sum (ACC: y += sum); prescribed components get
+// fixed_val.  The slots of a node in segment c of the layout follow from the
+// thread's index, so the slot loads, the node id and the node's Dirichlet bits
+// are all one memory latency away (nodes past the segments read their range
+// first).  MASK: a Dirichlet mask is in force (a template flag, so that the
+// mask's load is not behind a branch whose merge would wait for it).
+// s += the N slots at p, in order (all loads before the first add)
+template <int N, class T>
+__device__ __forceinline__ void halo_sum(const T *__restrict__ p, double s[3])
+{
+    T h[N][3];
+#pragma unroll
+    for (int k = 0; k < N; ++k) h[k][0] = p[3 * k], h[k][1] = p[3 * k + 1], h[k][2] = p[3 * k + 2];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += (double)h[k][c];
+}
+
+// Shared node i of the halo layout: its slots summed in order, written to y.
+template <class T, bool ACC, bool MASK>
+__device__ __forceinline__ void gather_node(const HaloSegs &seg, const int32_t *__restrict__ gptr,
+                                            const int32_t *__restrict__ node, const T *__restrict__ halo,
+                                            T *__restrict__ y, const uint8_t *__restrict__ nmask, T fixed_val,
+                                            int i)
+{
+    int64_t k0, cnt;
+    if (i < seg.start[kSegMax + 1]) {
+        // the segment by selects over constant indices (a dynamic index would
+        // put the kernel-argument arrays behind a memory load)
+        int c = 2, st = seg.start[2], bs = seg.base[2];
+#pragma unroll
+        for (int cc = 3; cc <= kSegMax; ++cc) {
+            int sc = seg.start[cc], bc = seg.base[cc];
+            asm volatile("" : "+s"(sc), "+s"(bc));   // values in scalar registers, not re-read by index
+            const bool in = i >= sc;
+            c = in ? cc : c;
+            st = in ? sc : st;
+            bs = in ? bc : bs;
+        }
+        cnt = c;
+        k0 = bs + (int64_t)c * (i - st);
+    } else {
+        const int j = i - seg.start[kSegMax + 1];
+        k0 = gptr[j];
+        cnt = gptr[j + 1] - k0;
+    }
+    const int64_t g = node[i];
+    const uint8_t b = MASK ? nmask[g] : 0;
+    // exactly cnt slot loads, issued back to back (cnt is the same for the
+    // lanes of a wave but at segment boundaries)
+    double s[3] = {0.0, 0.0, 0.0};
+    switch (cnt) {
+        case 2: halo_sum<2>(halo + 3 * k0, s); break;
+        case 3: halo_sum<3>(halo + 3 * k0, s); break;
+        case 4: halo_sum<4>(halo + 3 * k0, s); break;
+        case 5: halo_sum<5>(halo + 3 * k0, s); break;
+        case 6: halo_sum<6>(halo + 3 * k0, s); break;
+        case 7: halo_sum<7>(halo + 3 * k0, s); break;
+        case 8: halo_sum<8>(halo + 3 * k0, s); break;
+        default:
+            for (int64_t k = 0; k < cnt; ++k)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s[c] += (double)halo[3 * (k0 + k) + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        T *dst = &y[3 * g + c];
+        if ((b >> c) & 1) *dst = fixed_val;
+        else *dst = ACC ? *dst + T(s[c]) : T(s[c]);
+    }
+}
+
 // ---------------------------------------------------------- block pass kernel
 
 // Waves per SIMD the register allocator must leave room for.  The FP64 Tet4
@@ -1797,13 +1872,40 @@ __device__ __forceinline__ void add_bucket(double v, double *red, double *bucket
     }
 }
 
+// Ticket of a launch whose last workgroup finishes its work: true in every
+// thread of the workgroup that comes last, with the others' stores visible.
+// One thread releases and acquires for the workgroup (the barriers order the
+// others' accesses around it): a fence acts on its XCD's whole L2, so this is
+// for grids of a few workgroups.  The ticket wraps to zero by itself.
+__device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t count)
+{
+    __shared__ uint32_t before;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        before = atomicInc(ticket, count - 1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    return before == count - 1;
+}
+
+// What a launch needs to gather the shared nodes itself (FIN)
+template <bool FIN> struct FinArgs {};
+template <> struct FinArgs<true> {
+    HaloMap h;
+    uint32_t *ticket;
+};
+
 // PQ (Krylov actions): v.K v, from the block's nodal sums and the v it staged.
-template <class E, class Op, class T, bool ACC, bool PQ>
+// FIN (halo scatter, few blocks): the workgroup that comes last also gathers.
+template <class E, class Op, class T, bool ACC, bool PQ, bool FIN = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MinWaves<E, Op>::value, 8)))
 k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
                                                     const int32_t *__restrict__ list, int count,
                                                     Scatter mode, int use_mask, T fixed_val,
-                                                    const int32_t *__restrict__ skip, double *__restrict__ pq)
+                                                    const int32_t *__restrict__ skip, double *__restrict__ pq,
+                                                    FinArgs<FIN> fin)
 {
     using Node = typename Op::Node;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1883,80 +1985,15 @@ k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
         __shared__ double wred[4];
         add_bucket(vf, wred, pq + (b & (kPqBuckets - 1)));
     }
-}
-
-// Second half of the halo scatter: shared node i = node[i] sums its halo
-// slots (its blocks or chunks in order; in FP64, so the result does not depend
-// on the schedule), then y = sum (ACC: y += sum); prescribed components get
-// fixed_val.  The slots of a node in segment c of the layout follow from the
-// thread's index, so the slot loads, the node id and the node's Dirichlet bits
-// are all one memory latency away (nodes past the segments read their range
-// first).  MASK: a Dirichlet mask is in force (a template flag, so that the
-// mask's load is not behind a branch whose merge would wait for it).
-// s += the N slots at p, in order (all loads before the first add)
-template <int N, class T>
-__device__ __forceinline__ void halo_sum(const T *__restrict__ p, double s[3])
-{
-    T h[N][3];
-#pragma unroll
-    for (int k = 0; k < N; ++k) h[k][0] = p[3 * k], h[k][1] = p[3 * k + 1], h[k][2] = p[3 * k + 2];
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) s[c] += (double)h[k][c];
-}
-
-// Shared node i of the halo layout: its slots summed in order, written to y.
-template <class T, bool ACC, bool MASK>
-__device__ __forceinline__ void gather_node(const HaloSegs &seg, const int32_t *__restrict__ gptr,
-                                            const int32_t *__restrict__ node, const T *__restrict__ halo,
-                                            T *__restrict__ y, const uint8_t *__restrict__ nmask, T fixed_val,
-                                            int i)
-{
-    int64_t k0, cnt;
-    if (i < seg.start[kSegMax + 1]) {
-        // the segment by selects over constant indices (a dynamic index would
-        // put the kernel-argument arrays behind a memory load)
-        int c = 2, st = seg.start[2], bs = seg.base[2];
-#pragma unroll
-        for (int cc = 3; cc <= kSegMax; ++cc) {
-            int sc = seg.start[cc], bc = seg.base[cc];
-            asm volatile("" : "+s"(sc), "+s"(bc));   // values in scalar registers, not re-read by index
-            const bool in = i >= sc;
-            c = in ? cc : c;
-            st = in ? sc : st;
-            bs = in ? bc : bs;
+    if constexpr (FIN) {
+        if (!last_workgroup(fin.ticket, (uint32_t)count)) return;
+        const T *halo = reinterpret_cast<const T *>(m.halo);
+        for (int i = threadIdx.x; i < fin.h.seg.n; i += nt) {
+            if (use_mask && m.nmask)
+                gather_node<T, false, true>(fin.h.seg, fin.h.gptr, fin.h.node, halo, y, m.nmask, fixed_val, i);
+            else
+                gather_node<T, false, false>(fin.h.seg, fin.h.gptr, fin.h.node, halo, y, nullptr, fixed_val, i);
         }
-        cnt = c;
-        k0 = bs + (int64_t)c * (i - st);
-    } else {
-        const int j = i - seg.start[kSegMax + 1];
-        k0 = gptr[j];
-        cnt = gptr[j + 1] - k0;
-    }
-    const int64_t g = node[i];
-    const uint8_t b = MASK ? nmask[g] : 0;
-    // exactly cnt slot loads, issued back to back (cnt is the same for the
-    // lanes of a wave but at segment boundaries)
-    double s[3] = {0.0, 0.0, 0.0};
-    switch (cnt) {
-        case 2: halo_sum<2>(halo + 3 * k0, s); break;
-        case 3: halo_sum<3>(halo + 3 * k0, s); break;
-        case 4: halo_sum<4>(halo + 3 * k0, s); break;
-        case 5: halo_sum<5>(halo + 3 * k0, s); break;
-        case 6: halo_sum<6>(halo + 3 * k0, s); break;
-        case 7: halo_sum<7>(halo + 3 * k0, s); break;
-        case 8: halo_sum<8>(halo + 3 * k0, s); break;
-        default:
-            for (int64_t k = 0; k < cnt; ++k)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) s[c] += (double)halo[3 * (k0 + k) + c];
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        T *dst = &y[3 * g + c];
-        if ((b >> c) & 1) *dst = fixed_val;
-        else *dst = ACC ? *dst + T(s[c]) : T(s[c]);
     }
 }
 
@@ -2298,10 +2335,31 @@ __device__ __forceinline__ double energy_point(double w, const double Jx[9], con
     return kk.wDe * (0.5 * mu * kk.I1m3 - mu * lnJ + 0.5 * lam * lnJ * lnJ);
 }
 
-template <class E, bool LIN>
+// One workgroup of 256: Neumaier sums of the block partials over a fixed strided
+// assignment, then a fixed tree (red: 256 doubles; the result in thread 0).
+__device__ __forceinline__ double sum_block_partials(const double *partials, int count, double *red)
+{
+    double s = 0.0, c = 0.0;
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        const double x = partials[i];
+        const double t = s + x;
+        if (isfinite(t)) c += (fabs(s) >= fabs(x)) ? ((s - t) + x) : ((x - t) + s);
+        s = t;
+    }
+    red[threadIdx.x] = isfinite(s) ? s + c : s;
+    __syncthreads();
+    for (int k = blockDim.x / 2; k > 0; k >>= 1) {
+        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+        __syncthreads();
+    }
+    return red[0];
+}
+
+// FIN (few blocks): the workgroup that comes last sums the partials into psi.
+template <class E, bool LIN, bool FIN>
 __global__ void __launch_bounds__(256) k_energy(BlockMesh m, const double *__restrict__ X,
                                                 const double *__restrict__ u,
-                                                double *__restrict__ partials)
+                                                double *partials, uint32_t *ticket, double *__restrict__ psi)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[256];
@@ -2370,29 +2428,21 @@ __global__ void __launch_bounds__(256) k_energy(BlockMesh m, const double *__res
         __syncthreads();
     }
     if (threadIdx.x == 0) partials[b] = red[0];
+    if constexpr (FIN) {
+        if (!last_workgroup(ticket, (uint32_t)count)) return;
+        const double s = sum_block_partials(partials, count, red);
+        if (threadIdx.x == 0) *psi = s;
+    }
 }
 
-// One workgroup: Neumaier sums of the block partials over a fixed strided
-// assignment, then a fixed tree.  A separate launch, so the partials of the
-// previous kernel are visible without device-wide fences.
+// A separate launch, so the partials of the previous kernel are visible without
+// device-wide fences, which cost more than the launch beyond a few blocks.
 __global__ void __launch_bounds__(256) k_sum_partials(const double *__restrict__ partials, int count,
                                                       double *__restrict__ out)
 {
     __shared__ double red[256];
-    double s = 0.0, c = 0.0;
-    for (int i = threadIdx.x; i < count; i += blockDim.x) {
-        const double x = partials[i];
-        const double t = s + x;
-        if (isfinite(t)) c += (fabs(s) >= fabs(x)) ? ((s - t) + x) : ((x - t) + s);
-        s = t;
-    }
-    red[threadIdx.x] = isfinite(s) ? s + c : s;
-    __syncthreads();
-    for (int k = blockDim.x / 2; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
+    const double s = sum_block_partials(partials, count, red);
+    if (threadIdx.x == 0) *out = s;
 }
 
 // ---------------------------------------------------- per-element adjoint kernels
@@ -2655,6 +2705,18 @@ static hipError_t run_chunks(const Ctx &c, const HvpOp<double> &op, double *y, b
     return hipGetLastError();
 }
 
+// Meshes of few blocks whose shared nodes are one round of a workgroup's threads
+// gather them at the end of the pass (FIN): a second launch costs the host 4 us
+// (action of 8^3 tetrahedra, 8 blocks and 217 shared nodes, call by call 10.4 and
+// 7.1 us) and its own memory latencies about what the ticket does (in a replayed
+// graph 6.8 and 6.65).  Two rounds are slower in a graph: 64^2 cells, 475 shared
+// nodes, 6.15 and 7.25; 10^3 tetrahedra, 856, 8.4 and 10.8.
+constexpr int kFinBlocks = 24;
+static bool gathers_itself(const Ctx &c)
+{
+    return c.m.n_blocks <= kFinBlocks && c.n_shared <= c.threads && c.passes.size() == 1;
+}
+
 // the symmetric tangent actions, which CG takes in mode Krylov
 template <class Op> struct TakesPq {
     static constexpr bool value = false;
@@ -2680,7 +2742,7 @@ static hipError_t run_accumulate(const Ctx &c, const Op &op, T *y, bool use_mask
             if (p.count == 0) continue;
             hipLaunchKernelGGL((k_accumulate<E, Op, T, true, false>), dim3(p.count), dim3(c.threads), lds,
                                c.stream, c.m, op, y, p.list, p.count, c.scatter, use_mask ? 1 : 0,
-                               fixed_val, skip, nullptr);
+                               fixed_val, skip, nullptr, FinArgs<false>{});
         }
         if (halo)
             launch_gather<T>(c, true, c.halo, reinterpret_cast<const T *>(c.m.halo), y, gmask, fixed_val, skip);
@@ -2691,13 +2753,20 @@ static hipError_t run_accumulate(const Ctx &c, const Op &op, T *y, bool use_mask
         hipLaunchKernelGGL((k_fill_nodal<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                            c.stream, n, y, use_mask ? c.m.nmask : nullptr, fixed_val);
     }
+    if (halo && mode != WriteMode::Krylov && gathers_itself(c)) {
+        const Pass &p = c.passes[0];
+        hipLaunchKernelGGL((k_accumulate<E, Op, T, false, false, true>), dim3(p.count), dim3(c.threads), lds, c.stream,
+                           c.m, op, y, p.list, p.count, c.scatter, use_mask ? 1 : 0, fixed_val, skip, nullptr,
+                           FinArgs<true>{c.halo, c.counter});
+        return hipGetLastError();
+    }
     for (const Pass &p : c.passes) {
         if (p.count == 0) continue;
         auto kern = k_accumulate<E, Op, T, false, false>;
         if constexpr (TakesPq<Op>::value)
             if (mode == WriteMode::Krylov) kern = k_accumulate<E, Op, T, false, true>;
         hipLaunchKernelGGL(kern, dim3(p.count), dim3(c.threads), lds, c.stream, c.m, op, y, p.list, p.count, c.scatter,
-                           use_mask ? 1 : 0, fixed_val, skip, pq);
+                           use_mask ? 1 : 0, fixed_val, skip, pq, FinArgs<false>{});
     }
     if (halo && mode != WriteMode::Krylov)
         launch_gather<T>(c, false, c.halo, reinterpret_cast<const T *>(c.m.halo), y, gmask, fixed_val, skip);
@@ -2812,24 +2881,26 @@ hipError_t launch_hvp_f32(const Ctx &c, const float *ulin, const float *v, float
     return dispatch(c, op, y, true, 0.0f, skip, mode, pq);
 }
 
+// The energy with the per-block partials in `partials`: two launches, or one where
+// the last workgroup sums (the same rule as for the gather, whatever is shared).
 template <class E, bool LIN>
-static void energy_pass(const Ctx &c, const double *u, size_t lds, double *partials)
-{
-    hipLaunchKernelGGL((k_energy<E, LIN>), dim3(c.m.n_blocks), dim3(256), lds, c.stream, c.m, c.m.X, u,
-                       partials);
-}
-
-// The energy's two launches with the per-block partials in `partials`.
-static hipError_t energy_into(const Ctx &c, const double *u, double *psi, double *partials)
+static void energy_pass(const Ctx &c, const double *u, double *psi, double *partials)
 {
     const size_t lds = sizeof(NodeXU) * (size_t)c.max_block_nodes;
+    const bool fin = c.m.n_blocks <= kFinBlocks;
+    hipLaunchKernelGGL((fin ? k_energy<E, LIN, true> : k_energy<E, LIN, false>), dim3(c.m.n_blocks), dim3(256), lds,
+                       c.stream, c.m, c.m.X, u, partials, c.counter, psi);
+    if (!fin) hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, c.stream, partials, c.m.n_blocks, psi);
+}
+
+static hipError_t energy_into(const Ctx &c, const double *u, double *psi, double *partials)
+{
     const bool lin = c.model == EFEM_MODEL_LINEAR;
     if (c.elem == EFEM_TET4)
-        lin ? energy_pass<Tet4Pair, true>(c, u, lds, partials) : energy_pass<Tet4Pair, false>(c, u, lds, partials);
+        lin ? energy_pass<Tet4Pair, true>(c, u, psi, partials) : energy_pass<Tet4Pair, false>(c, u, psi, partials);
     else if (c.elem == EFEM_TRI3)
-        lin ? energy_pass<Tri3, true>(c, u, lds, partials) : energy_pass<Tri3, false>(c, u, lds, partials);
-    else lin ? energy_pass<Hex8, true>(c, u, lds, partials) : energy_pass<Hex8, false>(c, u, lds, partials);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, c.stream, partials, c.m.n_blocks, psi);
+        lin ? energy_pass<Tri3, true>(c, u, psi, partials) : energy_pass<Tri3, false>(c, u, psi, partials);
+    else lin ? energy_pass<Hex8, true>(c, u, psi, partials) : energy_pass<Hex8, false>(c, u, psi, partials);
     return hipGetLastError();
 }
 
@@ -2873,7 +2944,7 @@ hipError_t launch_energy_noalloc(const Ctx &c, const double *u, double *psi)
         if (c.device >= 0 && c.device < kMaxDevices) p = g_scratch_ptr[c.device];
     }
     if (!p) return hipErrorNotInitialized;
-    // every partial is written by its block before k_sum_partials reads it,
+    // every partial is written by its block before the sum reads it,
     // so the array needs no clearing between calls
     return energy_into(c, u, psi, p);
 }

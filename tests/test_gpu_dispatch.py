@@ -277,3 +277,59 @@ def test_features_at_ragged_rings(mesh, masked):
     a = aux.cpu().numpy()
     assert np.abs(a[:, :3] - gref).max() <= 1e-6 * np.abs(gref).max()
     assert np.allclose(a[:, 9], sref, rtol=1e-5)
+
+
+@pytest.mark.parametrize("elem,n,block,threads", [
+    (I.TET4, 2, 4, 0), (I.TET4, 5, 40, 0), (I.TET4, 5, 40, 64), (I.TET4, 8, 0, 0), (I.HEX8, 6, 0, 0),
+    (I.HEX8, 7, 0, 0), (I.TRI3, 12, 18, 0), (I.TRI3, 12, 8, 0), (I.TRI3, 24, 0, 0), (I.TET4, 10, 0, 0)])
+def test_last_workgroup_finishes(elem, n, block, threads):
+    """Passes of few blocks whose last workgroup gathers the shared nodes and
+    sums the energy, and those just past that rule (more shared nodes than
+    threads, more blocks): against the colour scatter (1e-11, FP32 2e-5) and
+    the sum over its blocks (1e-12; the energy's bits never change, nodal sums
+    add in any order within a block), at every call and at every replay of a
+    graph with other calls between."""
+    from paper_2602_12365_amd import Operator
+    m = I.make_mesh(elem, n)
+    g = np.random.default_rng(n)
+    dim = m.X.shape[1]
+    u, v = (dev(s * g.standard_normal((m.n_nodes, dim))) for s in (0.01 / n, 1.0))
+    mu = dev(np.exp(0.3 * g.standard_normal(m.n_elems)))
+    mask = dev((g.random(dim * m.n_nodes) < 0.2).astype(np.uint8))
+    a = Operator(elem, m.X, m.conn, block_elems=block, threads=threads)
+    b = Operator(elem, m.X, m.conn, block_elems=block, scatter="color")
+    for op in (a, b):
+        op.set_material(mu, 1.5 * mu)
+    calls = (lambda op: op.residual(u), lambda op: op.jacobi_diag(u), lambda op: op.energy(u),
+             lambda op: op.hvp(v), lambda op: op.grad_coords(u))
+    for mk in (None, mask):
+        for op in (a, b):
+            op.set_dirichlet(mk)
+            op.linearize(u, "f64")
+        want = [f(b).cpu() for f in calls]
+        psi = calls[2](a).clone()
+
+        def check(outs):
+            assert torch.equal(outs[2], psi)
+            for got, ref in zip(outs, want):
+                assert rel(got.cpu(), ref) <= (1e-12 if ref.dim() == 0 else 1e-11)
+
+        for _ in range(4):
+            check([f(a) for f in calls])
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            outs = [f(a) for f in calls]
+        for _ in range(4):
+            for o in outs:
+                o.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            check(outs)
+            assert rel(calls[3](a).cpu(), want[3]) <= 1e-11
+        for op in (a, b):
+            op.linearize(u, "f32")
+        assert rel(a.hvp(v.float()).cpu(), b.hvp(v.float()).cpu()) <= 2e-5
+    a.close()
+    b.close()
