@@ -144,6 +144,11 @@ int efem_set_stream(efem_ctx *ctx, void *stream);
  * is the same in every element is detected and kept as two scalars. */
 int efem_set_material(efem_ctx *ctx, const double *mu, const double *lam);
 
+/* The material as efem_set_material, and efem_set_coords(coords) if any entry of
+ * coords (DEVICE float64 [3*n_nodes]) differs from the coordinates in use
+ * (*moved = 1, else 0), in one wait.  coords NULL: the material alone. */
+int efem_set_inputs(efem_ctx *ctx, const double *mu, const double *lam, const double *coords, int32_t *moved);
+
 /* Material model of the strain energy density: EFEM_MODEL_NEO_HOOKE (the
  * default) or EFEM_MODEL_LINEAR.  Every later operator call (energy,
  * residual, tangent action, diagonal, adjoints, solves, sparse tangent) uses

@@ -75,6 +75,7 @@ SIGNATURES = {
     "efem_destroy": (None, [c_void_p]),
     "efem_set_stream": (c_int32, [c_void_p, c_void_p]),
     "efem_set_material": (c_int32, [c_void_p, c_void_p, c_void_p]),
+    "efem_set_inputs": (c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, ctypes.POINTER(c_int32)]),
     "efem_set_model": (c_int32, [c_void_p, c_int32]),
     "efem_set_dirichlet": (c_int32, [c_void_p, c_void_p]),
     "efem_set_load": (c_int32, [c_void_p, c_void_p]),

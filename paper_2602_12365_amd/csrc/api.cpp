@@ -1091,12 +1091,29 @@ int efem_set_material(efem_ctx *ctx, const double *mu, const double *lam)
         set_error("efem_set_material: null pointer");
         return EFEM_ERR_INVALID;
     }
+    return efem_set_inputs(ctx, mu, lam, nullptr, nullptr);
+}
+
+int efem_set_inputs(efem_ctx *ctx, const double *mu, const double *lam, const double *coords, int32_t *moved)
+{
+    if (!ctx || !mu || !lam || (coords && !moved)) {
+        set_error("efem_set_inputs: null pointer");
+        return EFEM_ERR_INVALID;
+    }
     DeviceGuard dg(ctx->device);
     // a uniform field is passed to the kernels as two scalars (no per-element loads)
     UniformRecord *rec = ctx->uniform;
     ctx->uniform_calls = ctx->uniform_calls == INT32_MAX ? 1 : ctx->uniform_calls + 1;
-    HIP_TRY(launch_uniform_check(mu, lam, ctx->n_elems, ctx->uniform_calls, rec, ctx->stream));
+    HIP_TRY(launch_uniform_check(mu, lam, ctx->n_elems, ctx->uniform_calls, rec, ctx->stream, coords,
+                                 ctx->m.X, coords ? 3 * ctx->n_nodes : 0));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    if (coords) {
+        *moved = rec->xdiffers == ctx->uniform_calls;
+        if (*moved) {
+            const int rc = efem_set_coords(ctx, coords);
+            if (rc) return rc;
+        }
+    }
     if (rec->differs != ctx->uniform_calls) {
         ctx->m.mu = ctx->m.lam = nullptr;
         ctx->m.mu0 = rec->a0;

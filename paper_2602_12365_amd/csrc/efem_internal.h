@@ -169,13 +169,14 @@ hipError_t launch_cast_f32(const double *src, float *dst, int64_t n, hipStream_t
 // staging words of the chunk slots from cnode and the node mask (null = none)
 hipError_t launch_chunk_words(const Ctx &c);
 // Answer of a uniform check, in pinned host memory: differs == the call's
-// number if some a[i] != a[0] or b[i] != b[0]; a0 = a[0], b0 = b[0].
+// number if some a[i] != a[0] or b[i] != b[0]; a0 = a[0], b0 = b[0]; xdiffers
+// the same for x[i] != y[i].
 struct UniformRecord {
     double a0, b0;
-    int32_t differs;
+    int32_t differs, xdiffers;
 };
 hipError_t launch_uniform_check(const double *a, const double *b, int64_t n, int32_t call, UniformRecord *rec,
-                                hipStream_t s);
+                                hipStream_t s, const double *x = nullptr, const double *y = nullptr, int64_t nx = 0);
 
 // ---- context ---------------------------------------------------------------
 struct Ctx {

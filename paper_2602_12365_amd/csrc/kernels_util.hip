@@ -52,15 +52,34 @@ __global__ void k_cast_f32(const double *__restrict__ src, int64_t n, float *__r
 // now.  The word is compared with the call's own number, so nothing is
 // cleared in front, and the record lies in pinned host memory, so the answer
 // and both values are there when the stream is waited for, with no copies.
+// Workgroups from `g` on compare x and y entry by entry (coordinates), so that
+// a training step that may have moved the mesh waits once for both answers.
 __global__ void __launch_bounds__(256) k_uniform_check(const double *__restrict__ a, const double *__restrict__ b,
-                                                       int64_t n, int32_t call, UniformRecord *rec)
+                                                       int64_t n, int32_t call, UniformRecord *rec,
+                                                       unsigned g, const double *__restrict__ x,
+                                                       const double *__restrict__ y, int64_t nx)
 {
+    if (blockIdx.x >= g) {   // x and y, by the same scan
+        for (int64_t i0 = (blockIdx.x - g) * 1024ll; i0 < nx; i0 += (gridDim.x - g) * 1024ll) {
+            bool differs = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t i = i0 + 256 * k + threadIdx.x;
+                if (i < nx) differs |= x[i] != y[i];
+            }
+            if (__syncthreads_or(differs)) {
+                if (threadIdx.x == 0) rec->xdiffers = call;
+                return;
+            }
+        }
+        return;
+    }
     const double a0 = a[0], b0 = b[0];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         rec->a0 = a0;
         rec->b0 = b0;
     }
-    for (int64_t i0 = blockIdx.x * 1024ll; i0 < n; i0 += gridDim.x * 1024ll) {
+    for (int64_t i0 = blockIdx.x * 1024ll; i0 < n; i0 += g * 1024ll) {
         bool differs = false;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -77,10 +96,11 @@ __global__ void __launch_bounds__(256) k_uniform_check(const double *__restrict_
 static unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 hipError_t launch_uniform_check(const double *a, const double *b, int64_t n, int32_t call, UniformRecord *rec,
-                                hipStream_t s)
+                                hipStream_t s, const double *x, const double *y, int64_t nx)
 {
-    const unsigned g = (unsigned)((n + 1023) / 1024 < 512 ? (n + 1023) / 1024 : 512);
-    hipLaunchKernelGGL(k_uniform_check, dim3(g), dim3(256), 0, s, a, b, n, call, rec);
+    auto groups = [](int64_t k) { return (unsigned)((k + 1023) / 1024 < 512 ? (k + 1023) / 1024 : 512); };
+    const unsigned g = groups(n);
+    hipLaunchKernelGGL(k_uniform_check, dim3(g + groups(nx)), dim3(256), 0, s, a, b, n, call, rec, g, x, y, nx);
     return hipGetLastError();
 }
 

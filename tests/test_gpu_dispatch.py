@@ -333,3 +333,27 @@ def test_last_workgroup_finishes(elem, n, block, threads):
         assert rel(a.hvp(v.float()).cpu(), b.hvp(v.float()).cpu()) <= 2e-5
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("at", [0, 1023, 1024, 1028])
+def test_inputs_check_finds_a_moved_coordinate(at):
+    """A training step's coordinates, equal to the operator's or off in one
+    entry anywhere in the check's slices of 1024 (343 nodes, 1029 entries), with
+    a uniform and a varying material in the same wait: energies within 1e-12 of
+    the oracle's on those coordinates."""
+    from paper_2602_12365_amd import Operator, operator as ops
+    m = I.tet_mesh(6)
+    g = np.random.default_rng(at)
+    u = I.gaussian_field(m.n_nodes, 0.01, 3)
+    op = Operator(I.TET4, m.X, m.conn)
+    for bump in (0.0, 0.01, 0.0):
+        X = m.X.copy()
+        X.reshape(-1)[at] += bump
+        for mu in (np.full(m.n_elems, 1.25), np.exp(0.3 * g.standard_normal(m.n_elems))):
+            before = op.X
+            psi = ops.energy(op, dev(u), dev(mu), dev(2.0 * mu), dev(X))
+            ref = F.FEM(I.TET4, X, m.conn, mu, 2.0 * mu).energy(u)
+            assert abs(float(psi) - ref) <= 1e-12 * abs(ref)
+            assert (op.X is before) == bool(torch.equal(before, dev(X)))
+    with pytest.raises(TypeError):
+        ops.energy(op, dev(u), dev(mu), dev(mu), dev(m.X).float())
