@@ -25,6 +25,7 @@
 
 #include "efem_internal.h"
 #include "efem_sparse.h"
+#include "efem_wave.h"
 
 namespace efem {
 
@@ -1861,8 +1862,7 @@ template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
 // Sum over the workgroup's waves into bucket `b`: one add per workgroup.
 __device__ __forceinline__ void add_bucket(double v, double *red, double *bucket)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -9,6 +9,7 @@
 // float64 (plain solve) or float32 (mixed precision); every reduction
 // accumulates in float64.
 #include "efem_cg.h"
+#include "efem_wave.h"
 
 namespace efem {
 
@@ -21,14 +22,6 @@ __device__ __forceinline__ bool dof_fixed(const uint8_t *nmask, int64_t i)
 
 #define GRID_STRIDE(i, n) \
     for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < (n); i += (int64_t)gridDim.x * kThreads)
-
-// Sum over the 64 lanes of a wave; every lane gets the total.
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // Workgroup sums of one or two values per thread in a fixed order (the waves
 // by lane exchanges, then the four wave sums): one barrier where a tree in LDS
@@ -273,7 +266,7 @@ template <class T> __device__ __forceinline__ void load3(const T *__restrict__ p
 // k_cg_next.  Bound by launches and one memory latency each on small meshes,
 // by the vectors (10 passes) on large ones.  Per iteration against the five
 // launches before (gather and p.q on their own, x advanced in the update): 8^3
-// hexahedra 36 and 19 us (four-lane elements included), 64^3 tetrahedra, FP64,
+// hexahedra 36 and 17 us (four-lane elements and wave_sum included), 64^3 tetrahedra, FP64,
 // 54.6 and 45.8, FP32 48.4 and 38.2, 128^3 hexahedra FP32 242 and 221.
 //
 // k_cg_step: alpha = rz / pq (breakdown if pq <= 0 or not finite); r -= alpha q

@@ -2,6 +2,7 @@
 // multi-axpy of classical Gram-Schmidt, and a few elementwise helpers.  All
 // are bandwidth-bound passes over float64 vectors of length 3 n_nodes.
 #include "efem_gmres.h"
+#include "efem_wave.h"
 
 namespace efem {
 
@@ -47,9 +48,7 @@ __global__ void __launch_bounds__(kT) k_mdot(int64_t n, const double *__restrict
         }
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {
-            double v = acc[j];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            const double v = wave_sum(acc[j]);
             if (lane == 0) red[wave][j] = v;
         }
         __syncthreads();
