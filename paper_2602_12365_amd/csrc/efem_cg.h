@@ -20,6 +20,14 @@ struct CgScalars {
     int32_t done, breakdown, iter, fallback, stall[2];
 };
 
+// The scalars as the host reads them, in pinned memory: complete once stamp has
+// the number of the check.
+struct CgCheck {
+    CgScalars sc;
+    int32_t stamp;
+};
+hipError_t launch_cg_publish(hipStream_t s, const CgScalars *sc, CgCheck *out, int32_t stamp);
+
 // Reduction scratch: four arrays of per-workgroup partials and the buckets of p.q.
 struct CgWorkspace {
     double *partials = nullptr;   // [4 * kMaxRedBlocks + kPqBuckets]

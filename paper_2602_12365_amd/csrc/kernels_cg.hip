@@ -413,6 +413,19 @@ __global__ void __launch_bounds__(kThreads) k_cg_next(int64_t nn, T *__restrict_
     }
 }
 
+// The scalars to pinned host memory, then the stamp: one wave, so that the fence
+// waits for every lane's stores.
+__global__ void __launch_bounds__(64) k_cg_publish(const CgScalars *__restrict__ sc, CgCheck *out, int32_t stamp)
+{
+    static_assert(sizeof(CgScalars) % 4 == 0 && sizeof(CgScalars) <= 256, "one word a lane");
+    const int l = threadIdx.x;
+    if (l < (int)(sizeof(CgScalars) / 4))
+        __hip_atomic_store(reinterpret_cast<uint32_t *>(&out->sc) + l, reinterpret_cast<const uint32_t *>(sc)[l],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (l == 0) __hip_atomic_store(&out->stamp, stamp, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Where each node's sum lies under the halo scatter: (first slot, slots), or
 // slots = 0 for a node of one block, whose sum the block pass stores itself.
 __global__ void __launch_bounds__(kThreads) k_halo_index(HaloSegs seg, const int32_t *__restrict__ gptr,
@@ -588,6 +601,12 @@ hipError_t CgLaunch<T>::next(T *x, T *p, const T *r, const T *dinv, CgScalars *s
     auto kern = binv ? k_cg_next<T, true> : k_cg_next<T, false>;
     hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, s, nn, x, p, r, dinv, binv, sc, ws.partials + kMaxRedBlocks,
                        ws.partials + 2 * kMaxRedBlocks, g, ws.buckets(), j & 1, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_publish(hipStream_t s, const CgScalars *sc, CgCheck *out, int32_t stamp)
+{
+    hipLaunchKernelGGL(k_cg_publish, dim3(1), dim3(64), 0, s, sc, out, stamp);
     return hipGetLastError();
 }
 
