@@ -902,45 +902,48 @@ __global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(int64_t rows, c
     if (tid == 0) lpart[blockIdx.x] = (lred[0] + lred[1]) + (lred[2] + lred[3]);
 }
 
-// Column sums of gpart [G][kP] and the loss partials, in a fixed order: 64
-// columns per workgroup, 16 threads per column, so the partials stream in
-// parallel rows (one thread per column read them one after another: 299 us for
-// 1024 partials; 12 us for 512 here).  The last workgroup sums the loss.
+// Column sums of gpart [G][kP] and the loss partials, in a fixed order: 16
+// columns per workgroup, 64 threads per column, so that every CU pulls its share
+// and a column's partials are all in flight at once (one thread per column read
+// them one after another: 299 us for 1024 partials; for 512, 64 columns on 80
+// workgroups 12 us, 32 columns 8, 16 columns 6.5).  The last workgroup sums the loss.
+constexpr int kReduceCols = 16;
 __global__ void __launch_bounds__(1024) k_grad_reduce(int G, const float *__restrict__ gpart,
                                                       const double *__restrict__ lpart,
                                                       float *__restrict__ grad, double *__restrict__ loss)
 {
-    __shared__ double red[16][64];
-    const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
+    constexpr int kC = kReduceCols, kQ = 1024 / kC, kLoads = kGradBlocks / kQ;
+    __shared__ double red[kQ][kC];
+    const int c = threadIdx.x % kC, q = threadIdx.x / kC;
     double s = 0.0;
     if (blockIdx.x == gridDim.x - 1) {
         for (int b = threadIdx.x; b < G; b += 1024) s += lpart[b];
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
-        if (c == 0) red[q][0] = s;
+        double *waves = &red[0][0];
+        if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = s;
         __syncthreads();
         if (threadIdx.x == 0) {
             double t = 0.0;
-            for (int k = 0; k < 16; ++k) t += red[k][0];
+            for (int k = 0; k < 16; ++k) t += waves[k];
             *loss = t;
         }
         return;
     }
-    const int k = blockIdx.x * 64 + c;
-    if (k < kP)
-        for (int b = q; b < G; b += 512) {   // 32 loads in flight: all 512 partials in one latency
-            float p[32];
+    const int k = blockIdx.x * kC + c;
+    if (k < kP) {   // G <= kGradBlocks: all loads in flight at once
+        float p[kLoads];
 #pragma unroll
-            for (int j = 0; j < 32; ++j) p[j] = b + 16 * j < G ? gpart[(int64_t)(b + 16 * j) * kP + k] : 0.f;
+        for (int j = 0; j < kLoads; ++j) p[j] = q + kQ * j < G ? gpart[(int64_t)(q + kQ * j) * kP + k] : 0.f;
 #pragma unroll
-            for (int j = 0; j < 32; ++j) s += p[j];
-        }
+        for (int j = 0; j < kLoads; ++j) s += p[j];
+    }
     red[q][c] = s;
     __syncthreads();
     if (q == 0 && k < kP) {
         double t = 0.0;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) t += red[j][c];
+        for (int j = 0; j < kQ; ++j) t += red[j][c];
         grad[k] = (float)t;
     }
 }
@@ -1072,7 +1075,8 @@ hipError_t mlp_loss_grad(hipStream_t s, int64_t rows, const uint16_t *X, const f
                          double *loss)
 {
     hipLaunchKernelGGL(k_mlp_grad, dim3(G), dim3(64 * kGradWaves), 0, s, rows, X, aux, params, gpart, lpart);
-    hipLaunchKernelGGL(k_grad_reduce, dim3((kP + 63) / 64 + 1), dim3(1024), 0, s, G, gpart, lpart, grad, loss);
+    hipLaunchKernelGGL(k_grad_reduce, dim3((kP + kReduceCols - 1) / kReduceCols + 1), dim3(1024), 0, s, G, gpart,
+                       lpart, grad, loss);
     return hipGetLastError();
 }
 
