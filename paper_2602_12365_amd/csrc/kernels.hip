@@ -1847,8 +1847,10 @@ __device__ __forceinline__ void gather_node(const HaloSegs &seg, const int32_t *
 
 // Waves per SIMD the register allocator must leave room for.  The FP64 Tet4
 // pair pass needs 170 VGPRs unconstrained (2 waves per SIMD); held to 168 for
-// 3 waves it spills one register and runs about 3% faster.  The other item
-// kernels keep the compiler's choice.
+// 3 waves it spills one register and runs about 3% faster.  The FP32 hexahedra
+// take 82 (5 waves); held to 80 for 6 they spill none, and the six blocks of 256
+// that fit a CU's LDS are all resident: 96^3 72.6 and 71.4 us, 128^3 150.7 to
+// 153.0 and 148.0.  The other item kernels keep the compiler's choice.
 #ifndef EFEM_TET64_MIN_WAVES
 #define EFEM_TET64_MIN_WAVES 3
 #endif
@@ -1857,6 +1859,10 @@ template <class E, class Op> struct MinWaves {
 };
 template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
     static constexpr int value = EFEM_TET64_MIN_WAVES;
+};
+
+template <> struct MinWaves<Hex8, HvpOp<float>> {
+    static constexpr int value = 6;
 };
 
 // Sum over the workgroup's waves into bucket `b`: one add per workgroup.
@@ -1900,7 +1906,7 @@ template <> struct FinArgs<true> {
 // PQ (Krylov actions): v.K v, from the block's nodal sums and the v it staged.
 // FIN (halo scatter, few blocks): the workgroup that comes last also gathers.
 template <class E, class Op, class T, bool ACC, bool PQ, bool FIN = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MinWaves<E, Op>::value, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FIN ? 1 : MinWaves<E, Op>::value, 8)))
 k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
                                                     const int32_t *__restrict__ list, int count,
                                                     Scatter mode, int use_mask, T fixed_val,
