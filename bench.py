@@ -50,14 +50,12 @@ N_DIRS = 100
 # (5) and two entries of W (10), and its forces take 6 fewer: 583.
 FLOPS_PER_TET_HVP = 320
 FLOPS_PER_PAIR_HVP = 2 * FLOPS_PER_TET_HVP - 18 - 18 - 5 - 10 - 6
-# One Hex8 tangent action (2x2x2 Gauss) in the column form both precisions
-# evaluate: the 12 gradient columns of each of X, x (or u) and v from the 4
-# edge differences of each direction and two interpolations, 28 per
-# direction and component, 756; the point's tangent action as for a
-# tetrahedron without its gradients and forces, 8 x 290; the 36 column sums
-# of the point forces; columns back to edges, 216; edges to nodes, 48:
-# 3,376 per hexahedron (the node form took 6,928).
-FLOPS_PER_HEX_HVP = 756 + 8 * 290 + 36 + 216 + 48
+# One Hex8 tangent action (2x2x2 Gauss) on four lanes, one x-edge and two
+# points each, as both precisions evaluate it: per lane 25 flops a component
+# for the gradients of each of X, x (or u) and v and 30 a component for the
+# forces; per point the arithmetic of a tetrahedron without its gradients and
+# forces, 275: 3,460 per hexahedron.
+FLOPS_PER_HEX_HVP = 4 * (3 * 3 * 25 + 3 * 30) + 8 * 275
 
 
 def tet4_hvp_alg(n_elems, n_nodes, n_items):
