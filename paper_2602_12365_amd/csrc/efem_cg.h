@@ -36,6 +36,8 @@ struct CgWorkspace {
 
 int red_grid(int64_t n);
 
+constexpr int kOneNodes = 1024;       // largest mesh of the one-workgroup iteration
+
 template <class T>
 struct CgLaunch {
     int64_t n;          // vector length (3 * n_nodes)
@@ -61,6 +63,8 @@ struct CgLaunch {
     // p.q in the buckets (WriteMode::Krylov)
     hipError_t step(T *r, T *q, const T *dinv, CgScalars *sc, int j) const;
     hipError_t next(T *x, T *p, const T *r, const T *dinv, CgScalars *sc, int j) const;
+    // both at once, on meshes of at most kOneNodes nodes
+    hipError_t one(T *x, T *p, T *r, T *q, const T *dinv, CgScalars *sc, int j) const;
     hipError_t dinv_from_diag(const double *diag, const uint8_t *nmask, T *dinv) const;
     hipError_t axpy_state(const double *u, double alpha, const T *d, double *out) const;
     hipError_t scaled(const T *dinv, const double *b, double sign, T *x) const;

@@ -260,7 +260,28 @@ template <class T> __device__ __forceinline__ void load3(const T *__restrict__ p
     v[0] = p[3 * i], v[1] = p[3 * i + 1], v[2] = p[3 * i + 2];
 }
 
-// One PCG iteration is three launches: the tangent action, which also leaves
+// q of node i: its own entry, or the sum of its halo slots (first, count) in block
+// order, in FP64, as k_halo_gather sums them.
+template <class T>
+__device__ __forceinline__ void node_q(const T *__restrict__ q, int2 sh, const T *__restrict__ halo,
+                                       const uint8_t *__restrict__ nmask, int64_t i, T qi[3])
+{
+    if (sh.y == 0) {
+        load3(q, i, qi);
+        return;
+    }
+    double s[3] = {0.0, 0.0, 0.0};
+    const T *h = halo + 3 * (int64_t)sh.x;
+#pragma unroll 4
+    for (int k = 0; k < sh.y; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += (double)h[3 * k + c];
+    const int m = nmask ? nmask[i] : 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) qi[c] = (m >> c) & 1 ? T(0) : T(s[c]);
+}
+
+// One PCG iteration is three launches (two on meshes of one workgroup, k_cg_one): the tangent action, which also leaves
 // p.q (from the blocks' nodal sums, in kPqBuckets parts) and, under the halo scatter,
 // leaves the nodes shared between blocks in their halo slots; k_cg_step; and
 // k_cg_next.  Bound by launches and one memory latency each on small meshes,
@@ -290,20 +311,7 @@ __global__ void __launch_bounds__(kThreads) k_cg_step(int64_t nn, T *__restrict_
         const int2 sh = shared ? shared[i] : make_int2(0, 0);
         load3(r, i, ri);
         prec.load(dinv, binv, i);
-        if (sh.y == 0) {
-            load3(q, i, qi);
-        } else {
-            // the slots in block order, in FP64, as k_halo_gather sums them
-            double s[3] = {0.0, 0.0, 0.0};
-            const T *h = halo + 3 * (int64_t)sh.x;
-#pragma unroll 4
-            for (int k = 0; k < sh.y; ++k)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) s[c] += (double)h[3 * k + c];
-            const int m = nmask ? nmask[i] : 0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) qi[c] = (m >> c) & 1 ? T(0) : T(s[c]);
-        }
+        node_q(q, sh, halo, nmask, i, qi);
     };
     int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
@@ -409,6 +417,106 @@ __global__ void __launch_bounds__(kThreads) k_cg_next(int64_t nn, T *__restrict_
         for (int c = 0; c < 3; ++c) {
             x[3 * i + c] = xn[c];
             if (!stop) p[3 * i + c] = pn[c];
+        }
+    }
+}
+
+// Sums of one or two values per thread over a workgroup of 16 waves (red: 32 doubles).
+__device__ __forceinline__ void big_sum2(double &a, double &b, double *red)
+{
+    a = wave_sum(a);
+    b = wave_sum(b);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = a;
+        red[16 + (threadIdx.x >> 6)] = b;
+    }
+    __syncthreads();
+    a = b = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        a += red[w];
+        b += red[16 + w];
+    }
+}
+
+// k_cg_step and k_cg_next in one workgroup, one node per thread, for meshes of at
+// most kOneNodes nodes: a launch and two reads of the scalars less.  One CU's
+// memory path bounds it beyond that.  Per iteration, the two kernels and this
+// one (with the tangent action): 5^3 hexahedra FP64 13.0 and 10.4 us, 8^3 13.9
+// and 13.3, FP32 13.8 and 12.2; with several nodes per thread FP64 10^3 14.4 and
+// 16.7, 12^3 14.2 and 20.5.
+template <class T, bool BLOCK, bool CLEAR>
+__global__ void __launch_bounds__(kOneNodes) k_cg_one(int nn, T *__restrict__ x, T *__restrict__ p, T *__restrict__ r,
+                                                      T *__restrict__ q, const T *__restrict__ dinv,
+                                                      const uint16_t *__restrict__ binv,
+                                                      const int2 *__restrict__ shared, const T *__restrict__ halo,
+                                                      const uint8_t *__restrict__ nmask, CgScalars *sc,
+                                                      double *__restrict__ buckets, int par, int j)
+{
+    __shared__ double red[32];
+    const int i = threadIdx.x;
+    const bool mine = i < nn;
+    const double rz0 = sc->rz[par], tol2 = sc->tol2;
+    double pq = i < kPqBuckets ? buckets[i] : 0.0, none = 0.0;
+    const int done = sc->done;
+    T ri[3], qi[3], pi[3], xi[3], rn[3], z[3];
+    NodePrec<BLOCK, T> prec;
+    if (mine) {
+        const int2 sh = shared ? shared[i] : make_int2(0, 0);
+        load3(r, i, ri);
+        load3(p, i, pi);
+        load3(x, i, xi);
+        prec.load(dinv, binv, i);
+        node_q(q, sh, halo, nmask, i, qi);
+    }
+    if (done) return;
+    big_sum2(pq, none, red);
+    if (!(pq > 0.0) || !isfinite(pq)) {
+        if (i == 0) {
+            sc->pq = pq;
+            sc->breakdown = 1;
+            sc->done = 1;
+        }
+        return;
+    }
+    const double alpha = rz0 / pq;
+    const T a = (T)alpha;
+    double rr = 0.0, rz = 0.0;
+    if (mine) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) rn[c] = ri[c] - a * qi[c];
+        prec.apply(rn, z);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            r[3 * i + c] = rn[c];
+            if (CLEAR) q[3 * i + c] = T(0);
+            rr += (double)rn[c] * (double)rn[c];
+            rz += (double)rn[c] * (double)z[c];
+        }
+    }
+    big_sum2(rr, rz, red);
+    const bool stop = rr <= tol2 || !isfinite(rr);
+    const double beta = rz / rz0;
+    if (i < kPqBuckets) buckets[i] = 0.0;   // of the next tangent action
+    if (i == 0) {
+        sc->pq = pq;
+        sc->alpha = alpha;
+        sc->iter = j + 1;
+        sc->rr = rr;
+        if (stop) {
+            sc->done = 1;
+        } else {
+            sc->rz[par ^ 1] = rz;
+            sc->beta = beta;
+        }
+    }
+    if (mine) {
+        const T bt = (T)beta;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[3 * i + c] = xi[c] + a * pi[c];
+            if (!stop) p[3 * i + c] = z[c] + bt * pi[c];
         }
     }
 }
@@ -601,6 +709,16 @@ hipError_t CgLaunch<T>::next(T *x, T *p, const T *r, const T *dinv, CgScalars *s
     auto kern = binv ? k_cg_next<T, true> : k_cg_next<T, false>;
     hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, s, nn, x, p, r, dinv, binv, sc, ws.partials + kMaxRedBlocks,
                        ws.partials + 2 * kMaxRedBlocks, g, ws.buckets(), j & 1, j);
+    return hipGetLastError();
+}
+
+template <class T>
+hipError_t CgLaunch<T>::one(T *x, T *p, T *r, T *q, const T *dinv, CgScalars *sc, int j) const
+{
+    auto kern = binv ? (clear_q ? k_cg_one<T, true, true> : k_cg_one<T, true, false>)
+                     : (clear_q ? k_cg_one<T, false, true> : k_cg_one<T, false, false>);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kOneNodes), 0, s, (int)(n / 3), x, p, r, q, dinv, binv, shared, halo, nmask, sc,
+                       ws.buckets(), j & 1, j);
     return hipGetLastError();
 }
 

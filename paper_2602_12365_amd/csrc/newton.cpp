@@ -190,6 +190,10 @@ struct Solver {
     {
         L.nmask = c.m.nmask;
         TRY(hvp(p, q, &sc->done, WriteMode::Krylov));
+        if (c.n_nodes <= kOneNodes) {
+            TRY(L.one(x, p, rv, q, dinv, sc, j));
+            return EFEM_OK;
+        }
         TRY(L.step(rv, q, dinv, sc, j));
         TRY(L.next(x, p, rv, dinv, sc, j));
         return EFEM_OK;

@@ -357,3 +357,31 @@ def test_inputs_check_finds_a_moved_coordinate(at):
             assert (op.X is before) == bool(torch.equal(before, dev(X)))
     with pytest.raises(TypeError):
         ops.energy(op, dev(u), dev(mu), dev(mu), dev(m.X).float())
+
+
+@pytest.mark.parametrize("scatter", ["halo", "color", "atomic"])
+@pytest.mark.parametrize("elem,n", [(I.HEX8, 9), (I.HEX8, 10), (I.TET4, 9), (I.TET4, 10)])
+def test_krylov_on_both_sides_of_one_workgroup(elem, n, scatter):
+    """PCG on 1000 nodes (step and direction in one workgroup) and on 1331 (in
+    two kernels): FP64 true residuals meet the tolerance (1e-9, and 1e-10 for
+    the recursion's drift), FP32 ones 1e-3 (a condition number below 1e4 times
+    2^-24), with both preconditioners."""
+    from paper_2602_12365_amd import Operator
+    m = I.make_mesh(elem, n)
+    g = np.random.default_rng(n)
+    mu = np.exp(0.3 * g.standard_normal(m.n_elems))
+    mask = (m.X[:, 2:] < 1e-9).repeat(3, 1).astype(np.uint8).ravel()
+    free = 1.0 - mask.reshape(-1, 3)
+    u = 0.005 / n * g.standard_normal((m.n_nodes, 3)) * free
+    b = g.standard_normal((m.n_nodes, 3))
+    op = Operator(elem, m.X, m.conn, scatter=scatter)
+    op.set_material(dev(mu), dev(1.5 * mu))
+    op.set_dirichlet(dev(mask))
+    orc = F.FEM(elem, m.X, m.conn, mu, 1.5 * mu)
+    for precond in (0, 2):
+        for prec, rtol, tol in (("f64", 1e-9, 1.1e-9), ("f32", 1e-4, 1e-3)):
+            x, it, _ = op.linear_solve(dev(u), dev(b), rtol=rtol, hvp_prec=prec, precond=precond)
+            x = x.cpu().numpy()
+            assert it > 8 and np.all(x[mask.reshape(-1, 3) == 1] == 0.0)
+            assert np.linalg.norm((b - orc.hvp(u, x)) * free) <= tol * np.linalg.norm(b * free)
+    op.close()
