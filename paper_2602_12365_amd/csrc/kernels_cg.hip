@@ -281,14 +281,15 @@ __device__ __forceinline__ void node_q(const T *__restrict__ q, int2 sh, const T
     for (int c = 0; c < 3; ++c) qi[c] = (m >> c) & 1 ? T(0) : T(s[c]);
 }
 
-// One PCG iteration is three launches (two on meshes of one workgroup, k_cg_one): the tangent action, which also leaves
-// p.q (from the blocks' nodal sums, in kPqBuckets parts) and, under the halo scatter,
-// leaves the nodes shared between blocks in their halo slots; k_cg_step; and
-// k_cg_next.  Bound by launches and one memory latency each on small meshes,
-// by the vectors (10 passes) on large ones.  Per iteration against the five
-// launches before (gather and p.q on their own, x advanced in the update): 8^3
-// hexahedra 36 and 17 us (four-lane elements and wave_sum included), 64^3 tetrahedra, FP64,
-// 54.6 and 45.8, FP32 48.4 and 38.2, 128^3 hexahedra FP32 242 and 221.
+// One PCG iteration is three launches (two where one workgroup holds the mesh,
+// k_cg_one): the tangent action, which also leaves p.q (from the blocks' nodal
+// sums, in kPqBuckets parts) and, under the halo scatter, leaves the nodes shared
+// between blocks in their halo slots; k_cg_step; and k_cg_next.  Bound by launches
+// and one memory latency each on small meshes, by the vectors (10 passes) on large
+// ones.  Per iteration against the five launches before (gather and p.q on their
+// own, x advanced in the update): 8^3 hexahedra 36 and 13.9 us (four-lane elements,
+// wave_sum and the polled checks included), 64^3 tetrahedra, FP64, 54.6 and 45.8,
+// FP32 48.4 and 38.2, 128^3 hexahedra FP32 242 and 221.
 //
 // k_cg_step: alpha = rz / pq (breakdown if pq <= 0 or not finite); r -= alpha q
 // with a shared node's q summed from its slots; CLEAR: q = 0 for a next action
