@@ -1880,17 +1880,22 @@ __device__ __forceinline__ void add_bucket(double v, double *red, double *bucket
 
 // Ticket of a launch whose last workgroup finishes its work: true in every
 // thread of the workgroup that comes last, with the others' stores visible.
-// One thread releases and acquires for the workgroup (the barriers order the
-// others' accesses around it): a fence acts on its XCD's whole L2, so this is
-// for grids of a few workgroups.  The ticket wraps to zero by itself.
+// Every wave waits until its stores have reached the L2 before the barrier;
+// then one thread releases and acquires for the workgroup, and the second
+// barrier lets the others read after its invalidate (a fence acts on its XCD's
+// whole L2, so this is for grids of a few workgroups).  The ticket wraps to zero
+// by itself.
 __device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t count)
 {
     __shared__ uint32_t before;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    if (count == 1) return true;
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         before = atomicInc(ticket, count - 1);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
     return before == count - 1;
@@ -2712,11 +2717,14 @@ static hipError_t run_chunks(const Ctx &c, const HvpOp<double> &op, double *y, b
 }
 
 // Meshes of few blocks whose shared nodes are one round of a workgroup's threads
-// gather them at the end of the pass (FIN): a second launch costs the host 4 us
+// gather them at the end of the pass (FIN): a second launch costs the host 3 us
 // (action of 8^3 tetrahedra, 8 blocks and 217 shared nodes, call by call 10.4 and
-// 7.1 us) and its own memory latencies about what the ticket does (in a replayed
-// graph 6.8 and 6.65).  Two rounds are slower in a graph: 64^2 cells, 475 shared
-// nodes, 6.15 and 7.25; 10^3 tetrahedra, 856, 8.4 and 10.8.
+// 7.4 us) and its own memory latencies about what the ticket does (in a replayed
+// graph 6.8 both).  Two rounds are slower in a graph: 64^2 cells, 475 shared
+// nodes, 6.15 and 7.25; 10^3 tetrahedra, 856, 8.4 and 10.8.  The energy's sum over
+// the blocks follows the same block count: 9.8 and 6.2 us call by call, replayed
+// one block 5.3 and 4.6, 8 blocks 5.85 and 5.9, 27 blocks 6.1 and 6.3, 64 blocks
+// 5.95 and 6.8.
 constexpr int kFinBlocks = 24;
 static bool gathers_itself(const Ctx &c)
 {
