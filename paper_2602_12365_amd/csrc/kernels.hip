@@ -405,28 +405,43 @@ struct Hex8 {
 // lane, along y and z by exchanges with the lanes l ^ 1 and l ^ 2 (quad
 // permutes of registers).  The forces take the transposed route.
 //
-// Gradients are taken in reference coordinates of the lane's own,
-// xi' = (2 xi, -2 sy eta, -2 sz zeta) with sy, sz the signs of the lane's side:
-// every step is then a difference to the partner lane, with no signs.  The
-// element formulas hold in any reference coordinates when the weight carries
-// the determinant of the change, w' = w sy sz / 8 (both Jacobian determinants
-// change sign with it).
+// A gradient column is the difference along its edges, taken first, then
+// interpolated in the other two directions.  Nodal values of one element are
+// close to each other against their distance from zero (a mesh far from the
+// origin, a rigid displacement), so the differences are exact or nearly so, and
+// the interpolation adds terms of one sign and one column: a rounding of the
+// values themselves (interpolated before they are differenced: residual of a
+// mesh moved by 1e4 off by 1e-11, by 1e6 6e-10) or of another, larger column
+// (thin elements) never enters.
+//
+// Each interpolation is near + rho far, rho = wm / wp, its factor wp left out;
+// and every difference goes to the partner lane, with no signs.  The columns are
+// then gradients in reference coordinates of the lane's own, xi' = wp^2 / 2 (xi,
+// -sy eta, -sz zeta) with sy, sz the signs of the lane's side.  The element
+// formulas hold in any reference coordinates when the weight carries the
+// determinant of the change, w' = w sy sz (wp^2 / 2)^3 (both Jacobian
+// determinants change sign with it).
 //
 // Why four lanes: one lane's element holds 36 gradient values of each of three
 // fields and 36 force accumulators, which in FP64 took 256 VGPRs and 252 AGPRs,
 // one wave per SIMD, and 821 of its 3,729 instructions were moves between the
-// two files.  A lane of a quad holds 15 values per field and 142 VGPRs, three
+// two files.  A lane of a quad holds 15 values per field and 148 VGPRs, three
 // waves per SIMD, and a small mesh fills four times the lanes.  The exchanges
-// cost 144 register moves per lane (FP32: folded into the subtractions).
-// Bound by vector issue.  One lane against four, FP64 tangent action: 96^3
-// 162 and 101 us, 128^3 342 and 231, 12^3 21 and 8; FP32 79 and 72, 144 and
-// 152 (both at the issue limit there; the smaller blocks stage more), 17 and 7;
-// 96^3 residual 122 and 81, energy 90 and 60, material gradient 84 and 56.
+// cost 198 register moves per lane (FP32: operands of the arithmetic).  Bound by
+// vector issue.  One lane against four, replayed in a graph, lognormal material:
+// FP64 tangent action 8^3 18.2 and 8.0 us, 64^3 50 and 42, 96^3 170 and 118,
+// 128^3 355 and 246; FP32 8^3 13.6 and 7.1, 64^3 25.4 and 26.8, 96^3 79.7 and
+// 71.5, 128^3 145 and 144 (both at the issue limit there); 96^3 residual 125 and
+// 87, energy 90 and 66, material gradient 84 and 59.
 struct Hex8Quad {
     static constexpr double kWm = 0.5 * (1.0 - 0.57735026918962576451);   // weight of the far side
     static constexpr double kWp = 0.5 * (1.0 + 0.57735026918962576451);
-    // the x-difference at the two points is sqrt(3) times that of the x-interpolated
-    // values, so it needs no exchange of its own: wm sqrt(3)
+    static constexpr double kRho = 0.26794919243112270647;   // wm / wp = 2 - sqrt(3)
+    // 1/8 wp^6 and 1/8 wp^4 with wp = 1 / (1 + rho) of the rounded rho, so that its
+    // rounding leaves no factor in the volumes
+    static constexpr double kW6 = 0.0300814595564428020994, kW4 = 0.0483618167717899640382;
+    // (forces) the x-difference at the two points is sqrt(3) times that of the
+    // x-interpolated values, so it needs no exchange of its own: wm sqrt(3)
     static constexpr double kKx = 0.5 * (1.7320508075688772935 - 1.0);
     // the value of lane l ^ M (M = 1 or 2); mov_dpp, whose result has no
     // earlier value to keep (update_dpp clears its register first: 192 moves)
@@ -442,37 +457,108 @@ struct Hex8Quad {
     {
         return __hiloint2double(peer_bits<M>(__double2hiint(v)), peer_bits<M>(__double2loint(v)));
     }
-    // sign of det(d xi / d xi') times 1/8: the weight of a point
+    // the weight of a point: det(d xi' / d xi) (w = 1)
     template <class T> __device__ static __forceinline__ T weight(int l)
     {
-        return (l == 0 || l == 3) ? T(0.125) : T(-0.125);
+        constexpr T w = T(kW6);
+        return (l == 0 || l == 3) ? w : -w;
     }
+    // the weight of a point whose Q goes to forces(), which take derivatives in
+    // xi' / wp^2: a Q is linear in its weight
+    template <class T> __device__ static __forceinline__ T force_weight(int l)
+    {
+        constexpr T w = T(kW4);
+        return (l == 0 || l == 3) ? w : -w;
+    }
+    // a += rho * (the value of lane l ^ M).  FP32 takes the exchange as an operand of
+    // the FMA, which the compiler does not form (with its moves 96^3 took 74 us, 128^3 154,
+    // against 71.5 and 144).  A DPP operand is read two wait states after the vector
+    // write of it: one s_nop 1 in front of them all.
+#define EFEM_FAR(N, R, PERM) "v_fmac_f32_dpp %" #N ", %" #N ", %" #R " quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"
+#define EFEM_FAR3(PERM) "s_nop 1\n\t" EFEM_FAR(0, 3, PERM) EFEM_FAR(1, 3, PERM) EFEM_FAR(2, 3, PERM)
+#define EFEM_FAR6(PERM) "s_nop 1\n\t" EFEM_FAR(0, 6, PERM) EFEM_FAR(1, 6, PERM) EFEM_FAR(2, 6, PERM) \
+                        EFEM_FAR(3, 6, PERM) EFEM_FAR(4, 6, PERM) EFEM_FAR(5, 6, PERM)
+    template <int M> __device__ static __forceinline__ void far(float a[3])
+    {
+        const float rho = float(kRho);
+        if constexpr (M == 1) asm(EFEM_FAR3("[1,0,3,2]") : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]) : "v"(rho));
+        else asm(EFEM_FAR3("[2,3,0,1]") : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]) : "v"(rho));
+    }
+    template <int M> __device__ static __forceinline__ void far(float a[3], float b[3])
+    {
+        const float rho = float(kRho);
+        if constexpr (M == 1)
+            asm(EFEM_FAR6("[1,0,3,2]")
+                : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]) : "v"(rho));
+        else
+            asm(EFEM_FAR6("[2,3,0,1]")
+                : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]) : "v"(rho));
+    }
+#undef EFEM_FAR6
+#undef EFEM_FAR3
+#undef EFEM_FAR
     // gradient columns of a field at the lane's points: gx (both), gy[qx], gz[qx]
     template <class T> struct Field {
         T gx[3], gy[2][3], gz[2][3];
     };
     // VAL: the field's values at the points as well
-    template <bool VAL = false, class T>
-    __device__ static __forceinline__ void prep(const T f0[3], const T f1[3], Field<T> &F, T (*val)[3] = nullptr)
+    template <bool VAL = false>
+    __device__ static __forceinline__ void prep(const double f0[3], const double f1[3], Field<double> &F,
+                                                double (*val)[3] = nullptr)
     {
-        constexpr T wm = T(kWm), wp = T(kWp), kx = T(kKx);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const T d = f1[i] - f0[i];
-            const T u0 = fma(wm, d, f0[i]), u1 = fma(wp, d, f0[i]);
-            const T e0 = peer<1>(u0) - u0, e1 = peer<1>(u1) - u1;
-            const T dy = fma(kx, e1 - e0, d), v0 = fma(wm, e0, u0), v1 = fma(wm, e1, u1);
-            const T h0 = peer<2>(v0) - v0, h1 = peer<2>(v1) - v1;
-            F.gx[i] = fma(kx, h1 - h0, dy);
-            F.gy[0][i] = fma(wm, peer<2>(e0) - e0, e0);
-            F.gy[1][i] = fma(wm, peer<2>(e1) - e1, e1);
-            F.gz[0][i] = h0;
-            F.gz[1][i] = h1;
-            if constexpr (VAL) {
-                val[0][i] = fma(wm, h0, v0);
-                val[1][i] = fma(wm, h1, v1);
-            }
+            const double p0 = peer<1>(f0[i]), p1 = peer<1>(f1[i]);
+            const double d = f1[i] - f0[i];
+            const double a0 = p0 - f0[i], a1 = p1 - f1[i];
+            const double b0 = peer<2>(f0[i]) - f0[i], b1 = peer<2>(f1[i]) - f1[i];
+            const double a0z = fma(kRho, peer<2>(a0), a0), a1z = fma(kRho, peer<2>(a1), a1);
+            const double b0y = fma(kRho, peer<1>(b0), b0), b1y = fma(kRho, peer<1>(b1), b1);
+            columns(i, a0z, a1z, b0y, b1y, F);
+            const double dy = fma(kRho, p1 - p0, d);   // the partner's d, without its two moves
+            F.gx[i] = fma(kRho, peer<2>(dy), dy);
+            if constexpr (VAL) values(i, f0[i], f1[i], a0, a1, b0y, b1y, val);
         }
+    }
+    template <bool VAL = false>
+    __device__ static __forceinline__ void prep(const float f0[3], const float f1[3], Field<float> &F,
+                                                float (*val)[3] = nullptr)
+    {
+        float a0[3], a1[3], a0z[3], a1z[3], b0[3], b1[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            a0z[i] = a0[i] = peer<1>(f0[i]) - f0[i], a1z[i] = a1[i] = peer<1>(f1[i]) - f1[i];
+            b0[i] = peer<2>(f0[i]) - f0[i], b1[i] = peer<2>(f1[i]) - f1[i];
+            F.gx[i] = f1[i] - f0[i];
+        }
+        far<2>(a0z, a1z);
+        far<1>(F.gx);
+        far<1>(b0, b1);
+        far<2>(F.gx);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            columns(i, a0z[i], a1z[i], b0[i], b1[i], F);
+            if constexpr (VAL) values(i, f0[i], f1[i], a0[i], a1[i], b0[i], b1[i], val);
+        }
+    }
+    // the y and z columns from the differences at the lane's two nodes
+    template <class T>
+    __device__ static __forceinline__ void columns(int i, T a0z, T a1z, T b0y, T b1y, Field<T> &F)
+    {
+        constexpr T rho = T(kRho);
+        F.gy[0][i] = fma(rho, a1z, a0z);
+        F.gy[1][i] = fma(rho, a0z, a1z);
+        F.gz[0][i] = fma(rho, b1y, b0y);
+        F.gz[1][i] = fma(rho, b0y, b1y);
+    }
+    // the values at the points: wm of the way along y, z and x (b0y, b1y lack wp)
+    template <class T>
+    __device__ static __forceinline__ void values(int i, T f0, T f1, T a0, T a1, T b0y, T b1y, T (*val)[3])
+    {
+        constexpr T wm = T(kWm), wp = T(kWp), wmp = T(kWm * kWp);
+        const T v0 = fma(wmp, b0y, fma(wm, a0, f0)), v1 = fma(wmp, b1y, fma(wm, a1, f1));
+        val[0][i] = fma(wm, v1 - v0, v0);
+        val[1][i] = fma(wp, v1 - v0, v0);
     }
     template <class T> __device__ static __forceinline__ void grad(const Field<T> &F, int qx, T G[9])
     {
@@ -518,12 +604,13 @@ struct Hex8Quad {
     // shape function of node (ix, jy, jz) at the lane's point qx, with jy, jz =
     // 1 on the far side: one factor, and the derivatives in the lane's coordinates
     __device__ static constexpr double n1(int near) { return near ? kWp : kWm; }
+    __device__ static constexpr double r1(int near) { return near ? 1.0 : kRho; }
     __device__ static constexpr double N(int q, int ix, int jy, int jz) { return n1(ix == q) * n1(!jy) * n1(!jz); }
     __device__ static constexpr double dN(int q, int ix, int jy, int jz, int J)
     {
-        return J == 0   ? (ix ? 1.0 : -1.0) * n1(!jy) * n1(!jz)
-               : J == 1 ? n1(ix == q) * (jy ? 1.0 : -1.0) * n1(!jz)
-                        : n1(ix == q) * n1(!jy) * (jz ? 1.0 : -1.0);
+        return J == 0   ? (ix ? 1.0 : -1.0) * r1(!jy) * r1(!jz)
+               : J == 1 ? r1(ix == q) * (jy ? 1.0 : -1.0) * r1(!jz)
+                        : r1(ix == q) * r1(!jy) * (jz ? 1.0 : -1.0);
     }
     // sums d[ix][jy][jz] that the four lanes hold for the element's nodes, to
     // the lanes that own them
@@ -877,7 +964,7 @@ template <> struct HvpOp<double> {
         Hex8Quad::prep(n0.X, n1.X, FX);
         Hex8Quad::prep(n0.x, n1.x, Fx);
         Hex8Quad::prep(n0.v, n1.v, Fv);
-        const double w = Hex8Quad::weight<double>(l);
+        const double w = Hex8Quad::force_weight<double>(l);
         double Q[2][9];
         bool ok = true;
 #pragma unroll
@@ -1009,7 +1096,7 @@ template <> struct HvpOp<float> {
         Hex8Quad::prep(n0.X, n1.X, FX);
         Hex8Quad::prep(n0.u, n1.u, Fu);
         Hex8Quad::prep(n0.v, n1.v, Fv);
-        const float w = Hex8Quad::weight<float>(l);
+        const float w = Hex8Quad::force_weight<float>(l);
         float Q[2][9];
         bool ok = true;
 #pragma unroll
@@ -1121,7 +1208,7 @@ template <class Op, class Rec, class T> struct ForceForm {
             T Jx[9], G[9];
             Hex8Quad::grad(FX, q, Jx);
             Hex8Quad::grad(Fg, q, G);
-            ok &= Op::template point<true>(Hex8Quad::weight<T>(l), Jx, G, mu, lam, Q[q]);
+            ok &= Op::template point<true>(Hex8Quad::force_weight<T>(l), Jx, G, mu, lam, Q[q]);
         }
         Hex8Quad::forces(Q[0], Q[1], f0, f1);
         return ok;
@@ -1438,8 +1525,8 @@ template <class T> struct TransportOp {
                 if ((b >> i) & 1) n.v[i] = T(0);
         }
     }
-    // Q (diffusion) and g (advection and reaction) of a point
-    __device__ __forceinline__ void point(T w, const T Jx[9], const T Cxi[9], const T xq[3], const T cq[3], T D, T k,
+    // Q (diffusion, weight w) and g (advection and reaction, weight wv) of a point
+    __device__ __forceinline__ void point(T w, T wv, const T Jx[9], const T Cxi[9], const T xq[3], const T cq[3], T D, T k,
                                           T Q[9], T g[3]) const
     {
         T Ae[9], Gc[9];
@@ -1452,7 +1539,7 @@ template <class T> struct TransportOp {
             for (int J = 0; J < 3; ++J)
                 Q[sp * 3 + J] = w * D * (Gc[sp * 3 + 0] * Ae[J * 3 + 0] + Gc[sp * 3 + 1] * Ae[J * 3 + 1]
                                          + Gc[sp * 3 + 2] * Ae[J * 3 + 2]);
-        const T wDe = w * De;
+        const T wDe = wv * De;
 #pragma unroll
         for (int sp = 0; sp < 3; ++sp)
             g[sp] = wDe * (b0 * Gc[sp * 3 + 0] + b1 * Gc[sp * 3 + 1] + b2 * Gc[sp * 3 + 2] + k * cq[sp]);
@@ -1490,7 +1577,7 @@ template <class T> struct TransportOp {
                     cq[i] += Na * ce[a][i];
                 }
             }
-            point(E::template weight<T>(), Jx, Cxi, xq, cq, mu[E::sub(q)], lam[E::sub(q)], Q, g);
+            point(E::template weight<T>(), E::template weight<T>(), Jx, Cxi, xq, cq, mu[E::sub(q)], lam[E::sub(q)], Q, g);
             E::template add_forces_to<false>(Q, q, f);
 #pragma unroll
             for (int a = 0; a < E::NEN; ++a) {
@@ -1512,7 +1599,7 @@ template <class T> struct TransportOp {
             T Jx[9], Cxi[9];
             Hex8Quad::grad(FX, q, Jx);
             Hex8Quad::grad(Fc, q, Cxi);
-            point(Hex8Quad::weight<T>(l), Jx, Cxi, xq[q], cq[q], mu, lam, Q[q], g[q]);
+            point(Hex8Quad::force_weight<T>(l), Hex8Quad::weight<T>(l), Jx, Cxi, xq[q], cq[q], mu, lam, Q[q], g[q]);
         }
         Hex8Quad::forces(Q[0], Q[1], f0, f1);
         Hex8Quad::add_values(g[0], g[1], f0, f1);
@@ -1847,10 +1934,8 @@ __device__ __forceinline__ void gather_node(const HaloSegs &seg, const int32_t *
 
 // Waves per SIMD the register allocator must leave room for.  The FP64 Tet4
 // pair pass needs 170 VGPRs unconstrained (2 waves per SIMD); held to 168 for
-// 3 waves it spills one register and runs about 3% faster.  The FP32 hexahedra
-// take 82 (5 waves); held to 80 for 6 they spill none, and the six blocks of 256
-// that fit a CU's LDS are all resident: 96^3 72.6 and 71.4 us, 128^3 150.7 to
-// 153.0 and 148.0.  The other item kernels keep the compiler's choice.
+// 3 waves it spills one register and runs about 3% faster.  The other item kernels keep
+// the compiler's choice.
 #ifndef EFEM_TET64_MIN_WAVES
 #define EFEM_TET64_MIN_WAVES 3
 #endif
@@ -1859,10 +1944,6 @@ template <class E, class Op> struct MinWaves {
 };
 template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
     static constexpr int value = EFEM_TET64_MIN_WAVES;
-};
-
-template <> struct MinWaves<Hex8, HvpOp<float>> {
-    static constexpr int value = 6;
 };
 
 // Sum over the workgroup's waves into bucket `b`: one add per workgroup.
