@@ -52,12 +52,14 @@ struct BlockMesh {
 constexpr int kChunkCap = 1472;      // node slots per chunk (23 groups of 64)
 constexpr int kChunkThreads = 768;   // 12 waves per workgroup: 3 per SIMD
 // LDS of a chunk: five 16-byte record pieces and three FP64 sums per slot, and
-// one 64-slot group of staging words per wave, and the chunk's block table
+// one 64-slot group of staging words per wave, and the chunk's block table (3
+// (kChunkSteps + 1) + kChunkSteps words and one more, so that doubles can follow)
 constexpr int kPieceBytes = kChunkCap * 16;
 constexpr int kChunkSteps = 32;      // blocks per chunk at most
-constexpr int kChunkLds = 5 * kPieceBytes + kChunkCap * 24 + kChunkThreads * 4 + (4 * kChunkSteps + 3) * 4;
+constexpr int kChunkLds = 5 * kPieceBytes + kChunkCap * 24 + kChunkThreads * 4 + (4 * kChunkSteps + 4) * 4;
 // and, where it also takes v.K v, one double per thread
 constexpr int kChunkPqLds = kChunkThreads * 8;
+static_assert(kChunkLds % 8 == 0 && kPieceBytes % 16 == 0 && kChunkLds + kChunkPqLds <= 160 * 1024, "LDS of a chunk");
 // staging word of a chunk slot: global id | Dirichlet bits << 28
 constexpr uint32_t kStageGid = 0x0fffffffu;
 struct ChunkMesh {
