@@ -1,0 +1,49 @@
+"""PCG on tangent actions that leave p.Kp with the blocks or chunks they run
+by (the matrix-free solve of Eq. 3's operator)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import fem as F
+from paper_2602_12365_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a)).to("cuda", dtype=dtype)
+
+
+@pytest.mark.parametrize("precond", [0, 2])
+@pytest.mark.parametrize("material", ["uniform", "per_element"])
+@pytest.mark.parametrize("n,block,scramble", [(16, 16, None), (20, 100, None), (24, 64, 21), (32, 192, None)])
+def test_solve_on_chunks_of_several_steps(n, block, scramble, material, precond):
+    """p.Kp summed over a chunk's steps, as its nodes' sums become final, and the
+    chunks' shared nodes summed by the step: the true residual meets the
+    tolerance (1e-9, and 1e-10 for the recursion's drift), and the iteration
+    count is the block pass's to two (sums in another order)."""
+    from paper_2602_12365_amd import Operator
+    m = I.tet_mesh(n)
+    if scramble is not None:
+        m = I.scrambled_mesh(m, scramble)
+    print(f"\n[chunk solve] n={n} block={block} {material} precond={precond}", flush=True)
+    mu = I.lognormal_field(m.n_elems, 0.3, 4) if material == "per_element" else I.constant_field(m.n_elems, 1.0)
+    mask = I.clamp_top_bottom(m.X, 0.1)[0]
+    free = 1.0 - mask.reshape(-1, 3)
+    u = 0.2 * I.gaussian_field(m.n_nodes, I.cube_amplitude(n), 0) * free
+    b = I.unit_direction(m.n_nodes, 1)
+    orc = F.FEM(I.TET4, m.X, m.conn, mu, 1.5 * mu)
+    count = {}
+    for chunks in (True, False):
+        op = Operator(I.TET4, m.X, m.conn, block_elems=block, chunks=chunks)
+        info = op.info()
+        assert not chunks or info["n_blocks"] > info["n_chunks"] > 0
+        op.set_material(dev(mu), dev(1.5 * mu))
+        op.set_dirichlet(dev(mask, torch.uint8))
+        x, count[chunks], _ = op.linear_solve(dev(u), dev(b), rtol=1e-9, precond=precond)
+        x = x.cpu().numpy()
+        assert np.all(x[free == 0.0] == 0.0)
+        assert np.linalg.norm((b - orc.hvp(u, x)) * free) <= (1e-9 + 1e-10) * np.linalg.norm(b * free)
+        op.close()
+    assert abs(count[True] - count[False]) <= 2
