@@ -915,6 +915,21 @@ __device__ __forceinline__ double write_out(const BlockMesh &m, const uint32_t *
     return vf;
 }
 
+// The thread's share of v.K v again, without the prescribed components.  Their v
+// is 0, but their sums need not be finite (a clamped region with an infinite
+// stiffness), and 0 times such a sum is not: taken only where a share is not
+// finite, so that the write-out reads no mask for it.
+template <class Node>
+__device__ __forceinline__ double free_share(const BlockMesh &m, const uint32_t *bnode, int nn, const double *acc,
+                                             const Node *sn)
+{
+    double vf = 0.0;
+    for (int l = threadIdx.x; l < nn; l += blockDim.x)
+        for (int c = 0; c < 3; ++c)
+            if (!comp_fixed(m.nmask, bnode[l] & kGidMask, c)) vf += (double)sn[l].v[c] * acc[l * 3 + c];
+    return vf;
+}
+
 // --------------------------------------------------------------- operations
 
 // Every op provides: Node (LDS record), stage(), element<Elem>(), and whether
@@ -2071,9 +2086,10 @@ k_accumulate(BlockMesh m, Op op, T *__restrict__ y,
     }
     if (bad) flag_inverted(m.flags);
     __syncthreads();
-    const double vf = write_out<ACC, PQ>(m, sbn, nn, acc, y, mode, use_mask != 0, fixed_val,
-                                         reinterpret_cast<T *>(m.halo), m.hslot ? m.hslot + n0 : nullptr, sn);
+    double vf = write_out<ACC, PQ>(m, sbn, nn, acc, y, mode, use_mask != 0, fixed_val,
+                                   reinterpret_cast<T *>(m.halo), m.hslot ? m.hslot + n0 : nullptr, sn);
     if constexpr (PQ) {
+        if (m.nmask && !isfinite(vf)) vf = free_share(m, sbn, nn, acc, sn);
         __shared__ double wred[4];
         add_bucket(vf, wred, pq + (b & (kPqBuckets - 1)));
     }
@@ -2384,10 +2400,25 @@ k_chunk_hvp64(BlockMesh m, ChunkMesh ch, const double *__restrict__ xrec, const 
     // the slots final after the last step
     for (int j = t_fin[nsteps - 1] + (int)threadIdx.x; j < t_fin[nsteps]; j += kChunkThreads)
         chunk_fin_store<ACC, PQ>(acc, ch.fin_slot[j], ch.fin_dst[j], y, ch.halo, masked, fixed_val, smem, vf);
-    // the staging words' space is free after the last step
-    if constexpr (PQ)
+    if constexpr (PQ) {
+        // as in free_share, over the slots this thread wrote
+        if (masked && !isfinite(*vf)) {
+            double s = 0.0;
+            for (int t = 0; t < nsteps; ++t)
+                for (int j = t_fin[t] + (int)threadIdx.x; j < t_fin[t + 1]; j += kChunkThreads) {
+                    const int slot = ch.fin_slot[j];
+                    const double *p3 = reinterpret_cast<const double *>(smem + 3 * kPieceBytes + 16 * slot);
+                    const double v2 = reinterpret_cast<const double *>(smem + 4 * kPieceBytes + 16 * slot)[1];
+                    const uint32_t bits = cword[slot] >> 28;
+                    for (int c = 0; c < 3; ++c)
+                        if (!((bits >> c) & 1u)) s += (c == 2 ? v2 : p3[c]) * acc[3 * slot + c];
+                }
+            *vf = s;
+        }
+        // the staging words' space is free after the last step
         add_bucket(*vf, reinterpret_cast<double *>(smem + 5 * kPieceBytes + kChunkCap * 24),
                    pq + (c & (kPqBuckets - 1)));
+    }
 }
 
 // ------------------------------------------------------------------- energy

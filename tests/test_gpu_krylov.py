@@ -47,3 +47,44 @@ def test_solve_on_chunks_of_several_steps(n, block, scramble, material, precond)
         assert np.linalg.norm((b - orc.hvp(u, x)) * free) <= (1e-9 + 1e-10) * np.linalg.norm(b * free)
         op.close()
     assert abs(count[True] - count[False]) <= 2
+
+
+@pytest.mark.parametrize("model", ["neo_hookean", "linear"])
+@pytest.mark.parametrize("elem,n,block,scatter", [
+    (I.TET4, 4, 0, "halo"), (I.TET4, 16, 16, "halo"), (I.HEX8, 4, 0, "halo"), (I.HEX8, 12, 40, "halo"),
+    (I.HEX8, 6, 9, "color"), (I.TET4, 4, 40, "atomic"), (I.TRI3, 12, 20, "halo")])
+def test_sums_at_prescribed_components_do_not_enter(elem, n, block, scatter, model):
+    """Elements all of whose components are prescribed (a clamped layer given an
+    infinite stiffness) leave sums that are not finite at those components; no
+    solve sees them, in either precision: true residuals as without them (1e-9
+    and the recursion's drift, 1e-10; FP32 1e-4 of the FP64 solution).  (No mesh
+    here pairs such a tetrahedron with a free one, whose diagonal the pair's zero
+    shape functions would take 0 times infinity into.)"""
+    from paper_2602_12365_amd import Operator
+    m = I.make_mesh(elem, n)
+    print(f"\n[prescribed layer] elem={elem} n={n} block={block} {scatter} {model}", flush=True)
+    g = np.random.default_rng(n)
+    axis = 1 if elem == I.TRI3 else 2
+    low = m.X[:, axis] <= 1.0 / n + 1e-9
+    rigid = low[m.conn].all(axis=1)
+    assert 0 < rigid.sum() < m.n_elems
+    mask = np.repeat(low[:, None], 3, axis=1)
+    if elem == I.TRI3:
+        mask[:, 2] = True
+    free = 1.0 - mask
+    mu = np.exp(0.3 * g.standard_normal(m.n_elems))
+    stiff = np.where(rigid, np.inf, mu)
+    u = 0.005 / n * g.standard_normal((m.n_nodes, 3)) * free
+    b = g.standard_normal((m.n_nodes, 3))
+    orc = F.FEM(elem, m.X, m.conn, mu, 1.5 * mu, model=model)
+    op = Operator(elem, m.X, m.conn, block_elems=block, scatter=scatter, model=model)
+    op.set_material(dev(stiff), dev(1.5 * stiff))
+    op.set_dirichlet(dev(mask, torch.uint8))
+    for precond in (0, 2):
+        x, it, _ = op.linear_solve(dev(u), dev(b), rtol=1e-9, precond=precond)
+        x = x.cpu().numpy()
+        assert it > 4 and np.all(x[mask] == 0.0)
+        assert np.linalg.norm((b - orc.hvp(u, x)) * free) <= (1e-9 + 1e-10) * np.linalg.norm(b * free)
+        x32 = op.linear_solve(dev(u), dev(b), rtol=1e-6, hvp_prec="f32", precond=precond)[0].cpu().numpy()
+        assert np.abs(x32 - x).max() <= 1e-4 * np.abs(x).max()
+    op.close()
