@@ -250,7 +250,11 @@ static int pair_tets(const double *X, const int32_t *conn, std::vector<int32_t> 
 // 10.0, 13.9, 21.3; 64^3 39.8, 37.8, 38.5; 96^3 102 in 256s, 159 in 512s.
 // Beyond 2^23 hexahedra 512 (even at 128^3: 231 and 234), which keeps the block
 // count of every mesh that efem_energy_noalloc's 65,536 partials can hold.
-static int default_block_elems(int elem, int64_t ne, int n_cu)
+// Fewer threads than 256 leave fewer waves to a block's LDS, so a hexahedral block
+// has no more elements than the workgroup threads (within the same block count):
+// FP64 action of 64^3 on 64 threads 96 us in 256s, 47 in 64s, on 128 threads 53 and
+// 45 in 128s; one lane per element in 512s 75 and 48.
+static int default_block_elems(int elem, int64_t ne, int n_cu, int threads)
 {
     if (elem == EFEM_TET4) {
         if (ne <= 512 * 1536) return (int)std::max<int64_t>(384, (ne + 511) / 512);
@@ -259,7 +263,8 @@ static int default_block_elems(int elem, int64_t ne, int n_cu)
     }
     if (elem == EFEM_TRI3) return ne <= 768 ? 768 : (ne <= (1 << 18) ? 256 : (ne <= (1 << 24) ? 512 : 768));
     for (int be : {64, 128})
-        if (ne <= 512 * (int64_t)be) return be;
+        if (ne <= 512 * (int64_t)be && be <= threads) return be;
+    if (threads < 256 && ne <= (int64_t)threads << 15) return threads;
     return ne <= ((int64_t)1 << 23) ? 256 : 512;
 }
 
@@ -854,7 +859,7 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    int be = default_block_elems(elem, n_elems, std::max(n_cu, 1));
+    int be = 0;
     int bn = elem == EFEM_HEX8 ? 768 : 600;
     int scatter = EFEM_SCATTER_HALO;
     int threads = 256;
@@ -868,6 +873,7 @@ int efem_create(efem_ctx **out, int32_t elem, int64_t n_nodes, int64_t n_elems,
         }
         if (opts->threads > 0) threads = opts->threads;
     }
+    if (be == 0) be = default_block_elems(elem, n_elems, std::max(n_cu, 1), threads);
     // 768 nodes x (80-byte record + 24-byte FP64 sums + 4-byte node word) =
     // 81 KB of LDS, within a workgroup's 160 KB
     if (bn < nen || bn > 768 || be < 1 || threads < 64 || threads > 256 || threads % 64) {
