@@ -552,8 +552,10 @@ __global__ void k_rows_aux(int64_t n, const float *__restrict__ b, const float *
 // What bounds it: issue and latency at 2 waves per SIMD (the gradient's 112
 // accumulators take the registers of a third): 1,650 VALU instructions, 208
 // matrix instructions (4,800 cycles) and 185 LDS instructions per 16 rows.
-// Weight fragments lie in LDS in lane order.  179,685 rows: 80 us, against 667
-// us for a form on the vector units whose weight reads met 16-way LDS bank
+// Weight fragments lie in LDS in lane order.  Loss and gradient of 179,685 rows,
+// with the reduction below: 79 us, of 16 rows 21 (latency: the parameters to LDS,
+// their fragments, one step, the sums of the four waves), of 2,048 rows 22; 944,
+// 22 and 56 for a form on the vector units whose weight reads met 16-way LDS bank
 // conflicts.  The gradient's error against float64 is unchanged.
 typedef uint32_t __attribute__((may_alias)) u32a;
 typedef s4 __attribute__((may_alias)) s4a;
@@ -570,7 +572,8 @@ constexpr int kBiasBytes = (2 * kHid + 4) * 4;
 constexpr int kWaveBytes = 5 * kPlane + 2 * kSmallPlane;   // three delta planes, h1, h2, x, do
 constexpr int kGradLds = kFragBytes + kBiasBytes + kGradWaves * kWaveBytes;
 static_assert(2 * kP * 4 <= kFragBytes + kBiasBytes + kGradWaves * kWaveBytes, "two sets of gradient sums share the LDS");
-static_assert(kP * 4 <= kGradWaves * kWaveBytes, "the parameters are staged in the planes' space");
+static_assert((kP + 2 * kHid) * 2 <= kGradWaves * kWaveBytes, "the parameters are staged in the planes' space");
+static_assert(kFrags == 44 && kGradWaves == 4, "eleven fragments a wave");
 
 // orders LDS accesses within the wave for the compiler (the LDS itself serves
 // a wave's accesses in order)
@@ -648,33 +651,50 @@ __global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(int64_t rows, c
     unsigned char *pd = mine, *ph1 = mine + 3 * kPlane, *ph2 = ph1 + kPlane, *px = ph2 + kPlane, *pdo = px + kSmallPlane;
     // operand fragments: entry f * 64 + l holds lane l's four values, for the
     // forward (W1, W2, W3) those of four FP32 steps v (m = l % 16, k = 4 v +
-    // l / 16 of its 16), else one bf16 operand (m = l % 16, k = 4 (l / 16) + v)
-    // (from a copy of the parameters in the planes' space: the gathers then cost
-    // LDS reads instead of memory latencies)
-    float *pl = reinterpret_cast<float *>(smem + kFragBytes + kBiasBytes);
-    for (int k = tid; k < kP; k += 64 * kGradWaves) pl[k] = bfr(params[k]);
+    // l / 16 of its 16), else one bf16 operand (m = l % 16, k = 4 (l / 16) + v).
+    // They are gathered from a copy of the parameters in the planes' space, whose
+    // W2 rows are two apart of 64 (rows 128 bytes apart lie on the same banks).
+    // Wave w gathers fragments w, w + 4, ...: four of a kind at a time, so that the
+    // eleven rounds are one straight run of independent reads (a loop that looked up
+    // each fragment's kind took 5.4 us, as long as 16 rows).
+    auto at = [](int k) { return k < kOffW2 ? k : (k < kOffB2 ? k + 2 * ((k - kOffW2) >> 6) : k + 2 * kHid); };
+    uint16_t *pl = reinterpret_cast<uint16_t *>(smem + kFragBytes + kBiasBytes);
+    constexpr int kU = 10;   // loads in flight
+    for (int k0 = tid; k0 < kP; k0 += kU * 64 * kGradWaves) {
+        float t[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) t[u] = params[min(k0 + u * 64 * kGradWaves, kP - 1)];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (k0 + u * 64 * kGradWaves < kP) pl[at(k0 + u * 64 * kGradWaves)] = f2bf(t[u]);
+    }
     __syncthreads();
-    for (int i = tid; i < kFrags * 64; i += 64 * kGradWaves) {
-        const int f = i >> 6, c = i & 15, q = (i & 63) >> 4;
-        s4 w;
+    {
+        constexpr int kRow = kHid + 2;   // of W2's copy
+        const uint16_t *w1 = pl + (16 * wave + col) * kIn, *w2 = pl + kOffW2, *w3 = pl + at(kOffW3);
+        s4 f[kFrags / 4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int k = 4 * q + v, kf = 4 * v + q;
-            int at;
-            if (f < 4) at = kf < kIn ? kOffW1 + (16 * f + c) * kIn + kf : -1;
-            else if (f < 20) at = kOffW2 + (16 * ((f - 4) & 3) + c) * kHid + 16 * ((f - 4) >> 2) + kf;   // group, tile
-            else if (f < 24) at = c < kOut ? kOffW3 + c * kHid + 16 * (f - 20) + kf : -1;
-            else if (f < 28) at = k < 9 ? kOffW3 + (k % 3) * kHid + 16 * (f - 24) + c : -1;   // k = 3 term + c
-            else at = kOffW2 + (16 * ((f - 28) & 3) + k) * kHid + 16 * ((f - 28) >> 2) + c;   // tile t1, t
-            w[v] = at >= 0 ? (short)f2bf(pl[at]) : (short)0;
+            const int k = 4 * quad + v, kf = 4 * v + quad;
+            const short a = (short)w1[kOffW1 + min(kf, kIn - 1)], b = (short)w3[min(col, kOut - 1) * kHid + 16 * wave + kf],
+                        c = (short)w3[(k % 3) * kHid + 16 * wave + col];
+            f[0][v] = kf < kIn ? a : (short)0;      // W1, tile `wave`
+            f[5][v] = col < kOut ? b : (short)0;    // W3, group `wave`
+            f[6][v] = k < 9 ? c : (short)0;         // W3^T, tile `wave`: k = 3 term + c
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                f[1 + g][v] = (short)w2[(16 * wave + col) * kRow + 16 * g + kf];   // W2: group g, tile `wave`
+                f[7 + g][v] = (short)w2[(16 * wave + k) * kRow + 16 * g + col];    // W2^T: tile g of t1, t = `wave`
+            }
         }
-        F1[i] = w;
+#pragma unroll
+        for (int r = 0; r < kFrags / 4; ++r) F1[(4 * r + wave) * 64 + lane] = f[r];
     }
     if (tid < kHid) {
-        bias[tid] = pl[kOffB1 + tid];
-        bias[kHid + tid] = pl[kOffB2 + tid];
+        bias[tid] = bf2f(pl[at(kOffB1 + tid)]);
+        bias[kHid + tid] = bf2f(pl[at(kOffB2 + tid)]);
     }
-    if (tid < 4) bias[2 * kHid + tid] = tid < kOut ? pl[kOffB3 + tid] : 0.f;
+    if (tid < 4) bias[2 * kHid + tid] = tid < kOut ? bf2f(pl[at(kOffB3 + tid)]) : 0.f;
     __syncthreads();
     // rows 9..15 of the output-delta plane stay 0
     for (int i = lane; i < kSmallPlane / 4; i += 64) *reinterpret_cast<u32a *>(pdo + 4 * i) = 0u;
@@ -871,31 +891,38 @@ __global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(int64_t rows, c
         w3[t][1] = g3[t][1] + (q1[0] + q1[3]);
         w3[t][2] = g3[t][2] + (q1[1] + q2);
     }
-    // the four waves' sums in a fixed order, (0 + 1) + (2 + 3), through two sets in LDS
+    // the four waves' sums in a fixed order, (0 + 1) + (2 + 3), through two sets in LDS:
+    // the odd waves store theirs, the even ones add, a tile's entries all read before
+    // the first is stored (read and stored one by one, 5.2 us)
     float *gs = reinterpret_cast<float *>(smem) + (wave >> 1) * kP;
-    auto each = [&](auto f) {
+    auto each = [&](int t, auto f) {   // the lane's entries of tile t: f(n, index, value)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int v = 0; v < 4; ++v) {
+            const int h = 16 * t + 4 * quad + v;
+            if (col <= kIn) f(v, col < kIn ? kOffW1 + h * kIn + col : kOffB1 + h, g1[t][v]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int h = 16 * t + 4 * quad + v;
-                if (col <= kIn) f(col < kIn ? kOffW1 + h * kIn + col : kOffB1 + h, g1[t][v]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) f(kOffW2 + h * kHid + 16 * j + col, g2[t][j][v]);
-                if (col == 0) f(kOffB2 + h, gb2[t][v]);
-            }
-            if (quad == 0)
-#pragma unroll
-                for (int c = 0; c < kOut; ++c) f(kOffW3 + c * kHid + 16 * t + col, w3[t][c]);
+            for (int j = 0; j < 4; ++j) f(4 + 4 * v + j, kOffW2 + h * kHid + 16 * j + col, g2[t][j][v]);
+            if (col == 0) f(20 + v, kOffB2 + h, gb2[t][v]);
         }
-        if (lane == 0)
+        if (quad == 0)
 #pragma unroll
-            for (int c = 0; c < kOut; ++c) f(kOffB3 + c, gb3[c]);
+            for (int c = 0; c < kOut; ++c) f(24 + c, kOffW3 + c * kHid + 16 * t + col, w3[t][c]);
+        if (t == 0 && lane == 0)
+#pragma unroll
+            for (int c = 0; c < kOut; ++c) f(27 + c, kOffB3 + c, gb3[c]);
     };
     __syncthreads();
-    if (wave & 1) each([&](int k, float g) { gs[k] = g; });
+    if (wave & 1)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) each(t, [&](int, int k, float g) { gs[k] = g; });
     __syncthreads();
-    if (!(wave & 1)) each([&](int k, float g) { gs[k] = g + gs[k]; });
+    if (!(wave & 1))
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float sum[27 + kOut];
+            each(t, [&](int n, int k, float g) { sum[n] = g + gs[k]; });
+            each(t, [&](int n, int k, float) { gs[k] = sum[n]; });
+        }
     __syncthreads();
     gs = reinterpret_cast<float *>(smem);
     for (int k = tid; k < kP; k += 64 * kGradWaves) gpart[(int64_t)blockIdx.x * kP + k] = gs[k] + gs[kP + k];
