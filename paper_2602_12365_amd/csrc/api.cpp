@@ -243,17 +243,21 @@ static int pair_tets(const double *X, const int32_t *conn, std::vector<int32_t> 
 // 39.6 and 37.7); 768 for one block, and beyond 2^24 (the block count that
 // efem_energy_noalloc's 65,536 partials can hold).
 // Hexahedra (an element on four lanes, so 64 of them fill a workgroup's four
-// waves): the smallest of 64, 128 and 256 that leaves at most two blocks per
-// CU, else 256.  A mesh in few blocks leaves CUs idle, small blocks stage more
-// shared nodes, and 256 keeps three workgroups' LDS per CU where 512 keeps two.
-// FP64 tangent action: 16^3 7.5 us in 64s, 13.1 in 256s, 20.7 in 512s; 32^3
-// 10.0, 13.9, 21.3; 64^3 39.8, 37.8, 38.5; 96^3 102 in 256s, 159 in 512s.
+// waves): 64 or 128 if that leaves at most two blocks per CU, else 256.  A mesh in
+// few blocks leaves CUs idle, small blocks stage more shared nodes, and 256 keeps
+// three workgroups' LDS per CU where 512 keeps two.  FP64 tangent action: 16^3 7.5
+// us in 64s, 13.1 in 256s, 20.7 in 512s; 32^3 10.0, 13.9, 21.3; 64^3 in 128s 43, 256s
+// 41, 512s 43; 96^3 117 in 256s, 165 in 512s (replayed graphs).
+// A few 256s per CU can fall unevenly: 192 or 128 where the fullest CU then has at
+// most 7/8 of the wave steps (64 elements).  256, 192 and 128: 42^3 (8, 6, 6 steps)
+// 22.6, 19.5, 19.4 us, 48^3 (8, 9, 8) 24.1, 25.1, 24.6, 52^3 (12, 9, 10) 31.7, 27.4,
+// 29.1, 53^3 (12, 12, 10) 31.8, 32.4, 29.5, 60^3 (16, 15, 14) 41.0, 39.5, 39.5.
 // Beyond 2^23 hexahedra 512 (even at 128^3: 231 and 234), which keeps the block
 // count of every mesh that efem_energy_noalloc's 65,536 partials can hold.
 // Fewer threads than 256 leave fewer waves to a block's LDS, so a hexahedral block
 // has no more elements than the workgroup threads (within the same block count):
-// FP64 action of 64^3 on 64 threads 96 us in 256s, 47 in 64s, on 128 threads 53 and
-// 45 in 128s; one lane per element in 512s 75 and 48.
+// FP64 action of 64^3 on 64 threads 96 us in 256s, 50 in 64s, on 128 threads 53 and
+// 48 in 128s; one lane per element in 512s 75 and 48.
 static int default_block_elems(int elem, int64_t ne, int n_cu, int threads)
 {
     if (elem == EFEM_TET4) {
@@ -265,7 +269,12 @@ static int default_block_elems(int elem, int64_t ne, int n_cu, int threads)
     for (int be : {64, 128})
         if (ne <= 512 * (int64_t)be && be <= threads) return be;
     if (threads < 256 && ne <= (int64_t)threads << 15) return threads;
-    return ne <= ((int64_t)1 << 23) ? 256 : 512;
+    if (ne > (int64_t)1 << 23) return 512;
+    auto steps = [&](int b) { return ((ne + b - 1) / b + n_cu - 1) / n_cu * (b / 64); };   // of the fullest CU
+    int be = 256;
+    for (int b : {192, 128})
+        if (8 * steps(b) <= 7 * steps(256) && steps(b) < steps(be)) be = b;
+    return be;
 }
 
 static void build_blocks(int elem, int64_t nn, int64_t ne, const double *X, const int32_t *conn,
