@@ -430,9 +430,10 @@ struct Hex8 {
 // cost 198 register moves per lane (FP32: operands of the arithmetic).  Bound by
 // vector issue.  One lane against four, replayed in a graph, lognormal material:
 // FP64 tangent action 8^3 18.2 and 8.0 us, 64^3 50 and 42, 96^3 170 and 118,
-// 128^3 355 and 246; FP32 8^3 13.6 and 7.1, 64^3 25.4 and 26.8, 96^3 79.7 and
-// 71.5, 128^3 145 and 144 (both at the issue limit there); 96^3 residual 125 and
-// 87, energy 90 and 66, material gradient 84 and 59.
+// 128^3 355 and 246; FP32 8^3 13.6 and 7.1, 64^3 25.4 and 26.3, 96^3 79.6 and
+// 70.5, 128^3 145 and 142 (both at the issue limit there); 96^3 residual 125 and
+// 86, energy 90 and 67, material gradient 84 and 60; FP32 linear model 64^3 19.1 and
+// 19.7, 96^3 51.9 and 50.0.
 struct Hex8Quad {
     static constexpr double kWm = 0.5 * (1.0 - 0.57735026918962576451);   // weight of the far side
     static constexpr double kWp = 0.5 * (1.0 + 0.57735026918962576451);
@@ -472,7 +473,7 @@ struct Hex8Quad {
     }
     // a += rho * (the value of lane l ^ M).  FP32 takes the exchange as an operand of
     // the FMA, which the compiler does not form (with its moves 96^3 took 74 us, 128^3 154,
-    // against 71.5 and 144).  A DPP operand is read two wait states after the vector
+    // against 70.5 and 142).  A DPP operand is read two wait states after the vector
     // write of it: one s_nop 1 in front of them all.
 #define EFEM_FAR(N, R, PERM) "v_fmac_f32_dpp %" #N ", %" #N ", %" #R " quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"
 #define EFEM_FAR3(PERM) "s_nop 1\n\t" EFEM_FAR(0, 3, PERM) EFEM_FAR(1, 3, PERM) EFEM_FAR(2, 3, PERM)
@@ -569,23 +570,36 @@ struct Hex8Quad {
             G[i * 3 + 2] = F.gz[qx][i];
         }
     }
-    // nodal forces of the lane's two nodes from the two points' Q
+    // a0 += rho * (the value of lane l ^ 2), a1 the same
+    __device__ static __forceinline__ void far_z(double a0[3], double a1[3])
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            a0[i] = fma(kRho, peer<2>(a0[i]), a0[i]);
+            a1[i] = fma(kRho, peer<2>(a1[i]), a1[i]);
+        }
+    }
+    __device__ static __forceinline__ void far_z(float a0[3], float a1[3]) { far<2>(a0, a1); }
+    // nodal forces of the lane's two nodes from the two points' Q (e0, e1, u0, u1
+    // lack a factor wp until the end)
     template <class T>
     __device__ static __forceinline__ void forces(const T Q0[9], const T Q1[9], T f0[3], T f1[3])
     {
-        constexpr T wm = T(kWm), wp = T(kWp), kx = T(kKx);
+        // wm wp as wp - wp^2, so that a constant stress leaves f0 = f1 from y and z
+        constexpr T rho = T(kRho), wp = T(kWp), wpp = T(kWp * kWp), wmp = wp - wpp, kx = T(kKx), ke = T(kKx / kWp);
+        T y0[3] = {Q0[1], Q0[4], Q0[7]}, y1[3] = {Q1[1], Q1[4], Q1[7]};
+        far_z(y0, y1);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const T g = Q0[i * 3] + Q1[i * 3], kg = kx * g;
-            const T h0 = Q0[i * 3 + 2] - kg, h1 = Q1[i * 3 + 2] + kg;
+            const T g = Q0[i * 3] + Q1[i * 3];
+            const T h0 = fma(-kx, g, Q0[i * 3 + 2]), h1 = fma(kx, g, Q1[i * 3 + 2]);
             const T v0 = peer<2>(h0) - h0, v1 = peer<2>(h1) - h1;
-            const T e0 = fma(wm, peer<2>(Q0[i * 3 + 1]), fma(wp, Q0[i * 3 + 1], -kg));
-            const T e1 = fma(wm, peer<2>(Q1[i * 3 + 1]), fma(wp, Q1[i * 3 + 1], kg));
-            const T u0 = fma(wp, v0, peer<1>(fma(wm, v0, e0)) - e0);
-            const T u1 = fma(wp, v1, peer<1>(fma(wm, v1, e1)) - e1);
-            const T t = fma(wm, u0, fma(wp, u1, g));
+            const T e0 = fma(-ke, g, y0[i]), e1 = fma(ke, g, y1[i]);
+            const T u0 = v0 + (peer<1>(fma(rho, v0, e0)) - e0);
+            const T u1 = v1 + (peer<1>(fma(rho, v1, e1)) - e1);
+            const T t = fma(wmp, u0, fma(wpp, u1, g));
             f1[i] = t;
-            f0[i] = (u0 + u1) - t;
+            f0[i] = fma(wp, u0 + u1, -t);
         }
     }
     // the transpose of VAL: g0, g1 at the points times N_a onto the lane's nodes
@@ -785,13 +799,27 @@ __device__ __forceinline__ void lin_invariants(const T H[9], T &ee, T &tr)
 
 // Nodal forces of the linear model at one point: Q = w det Jx sigma Jx^-T =
 // w sigma Ae^T.  Linear in Hxi, so the residual (Hxi of u) and the tangent
-// action (Hxi of v) are the same map.
+// action (Hxi of v) are the same map.  FP32 takes 1 / De and w into the moduli,
+// 16 operations fewer (its error is that of the nodal values' rounding; FP64 keeps
+// its own, which the shared rounding of the moduli would raise by 5%).
 template <class T>
 __device__ __forceinline__ void qp_linear(T w, const T Jx[9], const T Hxi[9], T mu, T lam, T Q[9])
 {
     T Ae[9], H[9], S[9];
-    lin_grad(Jx, Hxi, Ae, H);
-    lin_stress(H, mu, lam, S);
+    if constexpr (sizeof(T) == 4) {
+        const T c = w * rcp(adj_det(Jx, Ae));
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int L = 0; L < 3; ++L)
+                H[i * 3 + L] = Hxi[i * 3 + 0] * Ae[0 * 3 + L] + Hxi[i * 3 + 1] * Ae[1 * 3 + L]
+                             + Hxi[i * 3 + 2] * Ae[2 * 3 + L];
+        lin_stress(H, c * mu, c * lam, S);
+        w = T(1);
+    } else {
+        lin_grad(Jx, Hxi, Ae, H);
+        lin_stress(H, mu, lam, S);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
