@@ -3,13 +3,15 @@
 // Every operator is one pass over element blocks, one workgroup per block:
 //   1. stage the block's distinct nodes (coordinates, state, direction) from
 //      HBM into LDS, once per block (the gather of Alg. 1);
-//   2. one thread per element: reference-space gradients, quadrature-point
-//      math, element forces accumulated into LDS with LDS atomics;
+//   2. one thread per tetrahedron pair or triangle, four lanes per hexahedron:
+//      reference-space gradients, quadrature-point math, element forces
+//      accumulated into LDS with LDS atomics;
 //   3. write the block's nodal sums out: nodes owned by this block alone with
 //      plain stores, nodes shared with other blocks with global atomics (or,
 //      in the colour scatter, with a plain read-modify-write per colour).
-// The energy reduces per block and a one-workgroup kernel sums the block
-// partials in block order, so the energy is bitwise deterministic.  Nodal sums
+// The energy reduces per block, and one workgroup (the last of the pass on small
+// meshes, else one of its own) sums the block partials in block order, so the
+// energy is bitwise deterministic.  Nodal sums
 // are accumulated in FP64 in LDS for both precisions.
 //
 // Quadrature-point math (Eq. 2 and its exact derivatives, Eqs. 1 and 3) is
@@ -410,9 +412,9 @@ struct Hex8 {
 // close to each other against their distance from zero (a mesh far from the
 // origin, a rigid displacement), so the differences are exact or nearly so, and
 // the interpolation adds terms of one sign and one column: a rounding of the
-// values themselves (interpolated before they are differenced: residual of a
-// mesh moved by 1e4 off by 1e-11, by 1e6 6e-10) or of another, larger column
-// (thin elements) never enters.
+// values themselves or of another, larger column (thin elements) never enters.
+// Interpolated before they are differenced, the residual of a mesh moved by 1e4
+// is off by 7e-12, now 8e-15; by 1e6 4e-10 and 5e-13.
 //
 // Each interpolation is near + rho far, rho = wm / wp, its factor wp left out;
 // and every difference goes to the partner lane, with no signs.  The columns are
@@ -424,7 +426,7 @@ struct Hex8 {
 //
 // Why four lanes: one lane's element holds 36 gradient values of each of three
 // fields and 36 force accumulators, which in FP64 took 256 VGPRs and 252 AGPRs,
-// one wave per SIMD, and 821 of its 3,729 instructions were moves between the
+// one wave per SIMD, and 821 of its 3,657 instructions were moves between the
 // two files.  A lane of a quad holds 15 values per field and 148 VGPRs, three
 // waves per SIMD, and a small mesh fills four times the lanes.  The exchanges
 // cost 198 register moves per lane (FP32: operands of the arithmetic).  Bound by
@@ -1989,7 +1991,8 @@ template <> struct MinWaves<Tet4Pair, HvpOp<double>> {
     static constexpr int value = EFEM_TET64_MIN_WAVES;
 };
 
-// Sum over the workgroup's waves into bucket `b`: one add per workgroup.
+// Sum over the workgroup's waves into its bucket: one atomic add per workgroup,
+// so a bucket of three or more blocks takes them in the order they arrive.
 __device__ __forceinline__ void add_bucket(double v, double *red, double *bucket)
 {
     v = wave_sum(v);
@@ -2008,7 +2011,9 @@ __device__ __forceinline__ void add_bucket(double v, double *red, double *bucket
 // then one thread releases and acquires for the workgroup, and the second
 // barrier lets the others read after its invalidate (a fence acts on its XCD's
 // whole L2, so this is for grids of a few workgroups).  The ticket wraps to zero
-// by itself.
+// after `count` workgroups, and every launch on a context counts the same ones
+// (its blocks), so it stands at zero when all have ended, in whatever order they
+// came: nothing is left over for a later launch.
 __device__ __forceinline__ bool last_workgroup(uint32_t *ticket, uint32_t count)
 {
     __shared__ uint32_t before;

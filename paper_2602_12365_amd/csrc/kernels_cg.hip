@@ -1,10 +1,13 @@
 // Streaming kernels of the Krylov solve.  CG scalars live on the device so a
 // batch of iterations runs without host round trips.  Reductions are split
-// across kernel boundaries instead of device-wide fences: a kernel writes one
-// partial per workgroup with plain stores, and every workgroup of the next
-// kernel sums those partials in the same fixed order, so all of them derive
-// identical scalars (alpha, beta, convergence) and the result is
-// deterministic.  Workgroup 0 publishes the scalars the host reads.  Once
+// across kernel boundaries instead of device-wide fences: a kernel leaves
+// partials, and every workgroup of the next kernel sums them in the same fixed
+// order, so all of them derive identical scalars (alpha, beta, convergence).
+// r.r and r.z are one plain store per workgroup, in a fixed order from run to
+// run.  p.q is not: the blocks of the tangent action add their shares into
+// kPqBuckets buckets with FP64 atomics, in the order they end (their nodal sums
+// come from LDS atomics in any order as well), so alpha may differ in its last
+// bits between runs.  Workgroup 0 publishes the scalars the host reads.  Once
 // `done` is set, every later kernel of the batch returns at once.  Vectors are
 // float64 (plain solve) or float32 (mixed precision); every reduction
 // accumulates in float64.
@@ -24,8 +27,8 @@ __device__ __forceinline__ bool dof_fixed(const uint8_t *nmask, int64_t i)
     for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < (n); i += (int64_t)gridDim.x * kThreads)
 
 // Workgroup sums of one or two values per thread in a fixed order (the waves
-// by lane exchanges, then the four wave sums): one barrier where a tree in LDS
-// takes nine, which is most of a small vector's time.  red: kThreads doubles.
+// by lane exchanges, then the four wave sums): two barriers where a tree in LDS
+// takes ten, which is most of a small vector's time.  red: kThreads doubles.
 __device__ __forceinline__ double block_sum(double v, double *red)
 {
     v = wave_sum(v);
